@@ -225,84 +225,6 @@ qcdw_status qcdw_clover_invert(qcdw_ctx* ctx, const qcdw_lattice* lat, const voi
     return QCDW_OK;
 }
 
-qcdw_status qcdw_hop(qcdw_ctx* ctx, const qcdw_lattice* lat, const void* U, const void* psi, void* out, int out_parity)
-{
-    if (!ctx) return QCDW_EINVAL;
-    DeviceGuard dg(ctx->device);
-    Geom g;
-    CHK(check_lattice(ctx, lat, g));
-    CHK(check_dev(ctx, U, "U"));
-    CHK(check_dev(ctx, psi, "psi"));
-    CHK(check_dev(ctx, out, "out"));
-    if (out_parity != 0 && out_parity != 1) return fail(ctx, QCDW_EINVAL, "out_parity must be 0 or 1");
-    if (psi == out) return fail(ctx, QCDW_EINVAL, "out must not alias psi");
-    const size_t vb = 12UL * g.Vh * 16;
-    DevBuf gauge, in, res;
-    HIPCHK(ctx, gauge.alloc(8UL * g.Vh * 9 * 16));
-    HIPCHK(ctx, in.alloc(vb));
-    HIPCHK(ctx, res.alloc(vb));
-    hipStream_t s = ctx->stream;
-    HIPCHK(ctx, launch_pack_gauge(s, F64, 18, g, U, gauge.p));
-    HIPCHK(ctx, launch_pack_spinor(s, F64, g, psi, 1 - out_parity, in.p, 1.0));
-    HopArgs a = hop_args(g, out_parity);
-    a.psi = in.p;
-    a.out = res.p;
-    a.gauge = gauge.p;
-    HIPCHK(ctx, launch_hop(s, F64, 18, EPI_NONE, RED_NONE, a));
-    HIPCHK(ctx, launch_unpack_spinor(s, F64, g, res.p, out_parity, out, 1.0));
-    HIPCHK(ctx, hipMemsetAsync((char*)out + (size_t)(1 - out_parity) * vb, 0, vb, s));
-    HIPCHK(ctx, hipStreamSynchronize(s));
-    return QCDW_OK;
-}
-
-qcdw_status qcdw_dslash(qcdw_ctx* ctx, const qcdw_lattice* lat, const void* U, const void* clover, const void* psi,
-                        void* out, double kappa, double csw)
-{
-    if (!ctx) return QCDW_EINVAL;
-    DeviceGuard dg(ctx->device);
-    Geom g;
-    CHK(check_lattice(ctx, lat, g));
-    CHK(check_dev(ctx, U, "U"));
-    if (clover) CHK(check_dev(ctx, clover, "clover"));
-    CHK(check_dev(ctx, psi, "psi"));
-    CHK(check_dev(ctx, out, "out"));
-    if (psi == out) return fail(ctx, QCDW_EINVAL, "out must not alias psi");
-    hipStream_t s = ctx->stream;
-    const size_t vb = 12UL * g.Vh * 16;
-    DevBuf gauge, clov, Apaper, A[2], in[2], res;
-    HIPCHK(ctx, gauge.alloc(8UL * g.Vh * 9 * 16));
-    HIPCHK(ctx, Apaper.alloc(144UL * g.Vh * 8));
-    for (int p = 0; p < 2; p++) {
-        HIPCHK(ctx, A[p].alloc(clov_reals(g.Vh) * 8));
-        HIPCHK(ctx, in[p].alloc(vb));
-    }
-    HIPCHK(ctx, res.alloc(vb));
-    HIPCHK(ctx, launch_pack_gauge(s, F64, 18, g, U, gauge.p));
-    if (!clover) {
-        HIPCHK(ctx, clov.alloc(144UL * g.Vh * 8));
-        HIPCHK(ctx, launch_clover_build(s, g, U, clov.p));
-        clover = clov.p;
-    }
-    HIPCHK(ctx, launch_clover_to_A(s, g, clover, kappa, csw, Apaper.p));
-    for (int p = 0; p < 2; p++) {
-        HIPCHK(ctx, launch_pack_clover(s, F64, g, Apaper.p, p, A[p].p));
-        HIPCHK(ctx, launch_pack_spinor(s, F64, g, psi, p, in[p].p, 1.0));
-    }
-    for (int p = 0; p < 2; p++) {
-        HopArgs a = hop_args(g, p);
-        a.psi = in[1 - p].p;
-        a.out = res.p;
-        a.gauge = gauge.p;
-        a.clov = A[p].p;
-        a.y = in[p].p;
-        a.a = kappa;
-        HIPCHK(ctx, launch_hop(s, F64, 18, EPI_XPAY_CLOVY, RED_NONE, a));
-        HIPCHK(ctx, launch_unpack_spinor(s, F64, g, res.p, p, out, 1.0));
-    }
-    HIPCHK(ctx, hipStreamSynchronize(s));
-    return QCDW_OK;
-}
-
 // Form of the operator's single-RHS hop in precision prec: sites per thread along t (nt), c-tiles
 // per group swept along t (cg) and the arithmetic form (fma).  The cached choice for this lattice
 // (code nt + 16 cg + 4096 fma), else the fastest candidate timed on scratch vectors.

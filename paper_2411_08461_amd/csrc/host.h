@@ -346,6 +346,56 @@ using Precond = std::function<qcdw_status(const void* v, void* z)>;
 qcdw_status fgmres_run(qcdw_op* op, const Precond* precond, const void* b, void* x, const qcdw_solver_params* params,
                        qcdw_solve_info* info);
 
+// ---------------------------------------------------------------------------
+// calls that read their caller's fields in place (the full operator, the standalone hop)
+// ---------------------------------------------------------------------------
+// whether [in, in + n) and [out, out + no) share memory
+inline bool meets(const void* in, size_t n, const void* out, size_t no)
+{
+    return (const char*)in < (const char*)out + no && (const char*)out < (const char*)in + n;
+}
+
+struct OperatorInputs {
+    const void *U, *clover, *psi;
+};
+
+// The kernels read neighbours of every site they write, so an input that shares memory with the output field
+// is replaced by a copy in memory handed out by take(bytes) (nullptr: none left).
+template <class Take>
+inline qcdw_status detach(qcdw_ctx* ctx, const Geom& g, OperatorInputs& in, const void* out, Take&& take)
+{
+    const size_t field = 24UL * g.Vh * 16;
+    struct {
+        const void** p;
+        size_t n;
+    } all[] = {{&in.U, 8UL * g.Vh * 9 * 16}, {&in.clover, 144UL * g.Vh * 8}, {&in.psi, field}};
+    for (auto& a : all) {
+        if (!*a.p || !meets(*a.p, a.n, out, field)) continue;
+        void* copy = take(a.n);
+        if (!copy) return fail(ctx, QCDW_ENOMEM, "out of device memory for an input that overlaps the output");
+        HIPCHK(ctx, hipMemcpyAsync(copy, *a.p, a.n, hipMemcpyDeviceToDevice, ctx->stream));
+        *a.p = copy;
+    }
+    return QCDW_OK;
+}
+
+// scratch of one call from the block cache; the stream is drained before the blocks go back
+struct CallScratch {
+    static constexpr int MAX = 4;
+    hipStream_t s;
+    PoolBuf buf[MAX];
+    int used = 0;
+    explicit CallScratch(hipStream_t stream) : s(stream) {}
+    ~CallScratch()
+    {
+        if (used) (void)hipStreamSynchronize(s);
+    }
+    void* operator()(size_t n)
+    {
+        return used < MAX && buf[used].alloc(n) == hipSuccess ? buf[used++].p : nullptr;
+    }
+};
+
 inline qcdw_status read_double(qcdw_ctx* ctx, const double* dev, double& out)
 {
     HIPCHK(ctx, hipMemcpyAsync(ctx->host_d, dev, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));

@@ -102,6 +102,12 @@ __host__ __device__ inline int hop_blocks_nt(const Geom& g, int nt, int cg)
 hipError_t launch_hop(hipStream_t s, int prec, int recon, int epi, int red, const HopArgs& a,
                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 
+// the full operator A psi - kappa H psi, and H psi on one parity (zeros on the other), on the paper's layouts
+// (dslash.hip); out must not share memory with an input
+hipError_t launch_dslash_paper(hipStream_t s, const Geom& g, const void* U, const void* clover, const void* psi,
+                               void* out, double kappa, double csw);
+hipError_t launch_hop_paper(hipStream_t s, const Geom& g, const void* U, const void* psi, void* out, int parity);
+
 // BiCGStab scalars kept on the device (complex values as re, im pairs)
 hipError_t launch_hop_batch(hipStream_t s, int prec, int epi, int red, const BatchHopArgs& b, int grid,
                             hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);

@@ -36,7 +36,10 @@ hipError_t noalloc_scratch_init(int device)
     return hipSuccess;
 }
 
-// bytes of workspace qcdw_dslash_noalloc needs for a lattice of Vh sites per parity
+// Size by which lattices are admitted, for Vh sites per parity: links, packed A, (the clover field) and three
+// spinors of one parity.  The operator runs on the caller's fields and needs less (the clover field it builds,
+// copies of inputs that share memory with the output, each of them counted here), but the lattices that the
+// call takes are part of its interface.
 size_t noalloc_dslash_bytes(long Vh, bool build_clover)
 {
     const size_t vb = round256(12UL * Vh * 16);           // one internal spinor parity, FP64
@@ -79,35 +82,15 @@ extern "C" qcdw_status qcdw_dslash_noalloc(qcdw_ctx* ctx, const qcdw_lattice* la
         w += round256(n);
         return p;
     };
-    const size_t vb = 12UL * g.Vh * 16;
-    void* gauge = take(8UL * g.Vh * 9 * 16);
-    void* Apaper = take(144UL * g.Vh * 8);
-    void* A[2] = {take(clov_reals(g.Vh) * 8), take(clov_reals(g.Vh) * 8)};
-    void* in[2] = {take(vb), take(vb)};
-    void* res = take(vb);
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, launch_pack_gauge(s, F64, 18, g, U, gauge));
+    OperatorInputs in{U, clover, psi};
+    CHK(detach(ctx, g, in, out, take));
     if (!clover) {
-        void* clov = take(144UL * g.Vh * 8);
-        HIPCHK(ctx, launch_clover_build(s, g, U, clov));
-        clover = clov;
+        void* c = take(144UL * g.Vh * 8);
+        HIPCHK(ctx, launch_clover_build(s, g, in.U, c));
+        in.clover = c;
     }
-    HIPCHK(ctx, launch_clover_to_A(s, g, clover, kappa, csw, Apaper));
-    for (int p = 0; p < 2; p++) {
-        HIPCHK(ctx, launch_pack_clover(s, F64, g, Apaper, p, A[p]));
-        HIPCHK(ctx, launch_pack_spinor(s, F64, g, psi, p, in[p], 1.0));
-    }
-    for (int p = 0; p < 2; p++) {
-        HopArgs a = hop_args(g, p);
-        a.psi = in[1 - p];
-        a.out = res;
-        a.gauge = gauge;
-        a.clov = A[p];
-        a.y = in[p];
-        a.a = kappa;
-        HIPCHK(ctx, launch_hop(s, F64, 18, EPI_XPAY_CLOVY, RED_NONE, a));
-        HIPCHK(ctx, launch_unpack_spinor(s, F64, g, res, p, out, 1.0));
-    }
+    HIPCHK(ctx, launch_dslash_paper(s, g, in.U, in.clover, in.psi, out, kappa, csw));
     HIPCHK(ctx, hipStreamSynchronize(s));
     return QCDW_OK;
 }
