@@ -185,7 +185,8 @@ qcdw_status qcdw_clover_build(qcdw_ctx* ctx, const qcdw_lattice* lat, const void
     CHK(check_lattice(ctx, lat, g));
     CHK(check_dev(ctx, U, "U"));
     CHK(check_dev(ctx, clover, "clover"));
-    HIPCHK(ctx, launch_clover_build(ctx->stream, g, U, clover));
+    CallScratch scratch(ctx->stream);
+    HIPCHK(ctx, clover_from_paper(ctx->stream, g, U, clover, scratch(8UL * g.Vh * 9 * 16)));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return QCDW_OK;
 }
@@ -350,34 +351,25 @@ static qcdw_status op_create(qcdw_ctx* ctx, const qcdw_lattice* lat, const void*
         return st;
     };
     const int R = recon == 18 ? 9 : 6;
-    PoolBuf clov, inv, Ap;  // released after the stream synchronisation below (or in cleanup)
-    if (op->gauge64.alloc(8UL * g.Vh * R * 16) != hipSuccess || clov.alloc(144UL * g.Vh * 8) != hipSuccess ||
-        inv.alloc(144UL * g.Vh * 8) != hipSuccess || Ap.alloc(144UL * g.Vh * 8) != hipSuccess)
+    const int lrecon = (inner == QCDW_F32) ? recon : 12, lR = lrecon == 18 ? 9 : 6;
+    PoolBuf row2;  // released after the stream synchronisation below (or in cleanup)
+    if (op->gauge64.alloc(8UL * g.Vh * R * 16) != hipSuccess ||
+        (R == 6 && row2.alloc(8UL * g.Vh * 3 * 16) != hipSuccess) ||
+        (inner != QCDW_F64 && op->gauge_lo.alloc(8UL * g.Vh * lR * cplx_bytes(inner)) != hipSuccess))
         return cleanup(fail(ctx, QCDW_ENOMEM, "out of device memory creating the operator"));
     for (int p = 0; p < 2; p++)
-        if (op->Ainv64[p].alloc(clov_reals(g.Vh) * 8) != hipSuccess || op->A64[p].alloc(clov_reals(g.Vh) * 8) != hipSuccess)
+        if (op->Ainv64[p].alloc(clov_reals(g.Vh) * 8) != hipSuccess ||
+            op->A64[p].alloc(clov_reals(g.Vh) * 8) != hipSuccess ||
+            (inner != QCDW_F64 && op->Ainv_lo[p].alloc(clov_reals(g.Vh) * real_bytes(inner)) != hipSuccess))
             return cleanup(fail(ctx, QCDW_ENOMEM, "out of device memory creating the operator"));
-    hipError_t e = launch_pack_gauge(s, F64, recon, g, U, op->gauge64.p);
-    if (e == hipSuccess) e = launch_clover_build(s, g, U, clov.p, wt, ws);
+    void* const A[2] = {op->A64[0].p, op->A64[1].p};
+    void* const inv[2] = {op->Ainv64[0].p, op->Ainv64[1].p};
+    void* const lo[2] = {op->Ainv_lo[0].p, op->Ainv_lo[1].p};
+    hipError_t e = launch_pack_links(s, g, U, recon, op->gauge64.p, row2.p, inner, lrecon, op->gauge_lo.p);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->dev_int, 0, sizeof(int), s);
-    if (e == hipSuccess) e = launch_clover_invert(s, g, clov.p, kappa, csw, inv.p, ctx->dev_int);
-    if (e == hipSuccess) e = launch_clover_to_A(s, g, clov.p, kappa, csw, Ap.p);
-    for (int p = 0; p < 2 && e == hipSuccess; p++) {
-        e = launch_pack_clover(s, F64, g, inv.p, p, op->Ainv64[p].p);
-        if (e == hipSuccess) e = launch_pack_clover(s, F64, g, Ap.p, p, op->A64[p].p);
-    }
-    if (e == hipSuccess && inner != QCDW_F64) {
-        const int lrecon = (inner == QCDW_F32) ? recon : 12;
-        const int lR = lrecon == 18 ? 9 : 6;
-        if (op->gauge_lo.alloc(8UL * g.Vh * lR * cplx_bytes(inner)) != hipSuccess)
-            return cleanup(fail(ctx, QCDW_ENOMEM, "out of device memory creating the operator"));
-        e = launch_pack_gauge(s, inner, lrecon, g, U, op->gauge_lo.p);
-        for (int p = 0; p < 2 && e == hipSuccess; p++) {
-            if (op->Ainv_lo[p].alloc(clov_reals(g.Vh) * real_bytes(inner)) != hipSuccess)
-                return cleanup(fail(ctx, QCDW_ENOMEM, "out of device memory creating the operator"));
-            e = launch_pack_clover(s, inner, g, inv.p, p, op->Ainv_lo[p].p);
-        }
-    }
+    if (e == hipSuccess)
+        e = launch_clover_op(s, g, link_planes(op->gauge64.p, recon, row2.p, g.Vh), wt, ws, kappa, csw, A, inv, inner,
+                             lo, ctx->dev_int);
     if (e == hipSuccess) e = hipMemcpyAsync(ctx->host_d, ctx->dev_int, sizeof(int), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return cleanup(fail(ctx, QCDW_EHIP, "operator setup failed: %s", hipGetErrorString(e)));
@@ -437,10 +429,12 @@ qcdw_status qcdw_op_matpc(qcdw_op* op, qcdw_prec prec, const void* in_e, void* o
         return fail(ctx, QCDW_EINVAL, "prec must be F64 or the operator's inner precision");
     const Geom& g = op->g;
     const long n = 12L * g.Vh;
-    DevBuf in, out, tmp;
-    HIPCHK(ctx, in.alloc(n * cplx_bytes(prec)));
-    HIPCHK(ctx, out.alloc(n * cplx_bytes(prec)));
-    HIPCHK(ctx, tmp.alloc(n * cplx_bytes(prec)));
+    CallScratch scratch(ctx->stream);
+    struct {
+        void* p;
+    } in, out, tmp;
+    for (auto* f : {&in, &out, &tmp})
+        if (!(f->p = scratch(n * cplx_bytes(prec)))) return fail(ctx, QCDW_ENOMEM, "out of device memory");
     hipStream_t s = ctx->stream;
     const PrecView v = view(op, prec);
     HIPCHK(ctx, launch_pack_spinor(s, prec, g, in_e, 0, in.p, 1.0));
@@ -465,10 +459,12 @@ qcdw_status qcdw_op_matpc_multi(qcdw_op* op, qcdw_prec prec, int nrhs, const voi
     const Geom& g = op->g;
     const long n = 12L * g.Vh;
     const size_t half = (size_t)n * 16;  // bytes of one even-site FP64 field
-    DevBuf in, out, tmp;
-    HIPCHK(ctx, in.alloc(nrhs * n * cplx_bytes(prec)));
-    HIPCHK(ctx, out.alloc(nrhs * n * cplx_bytes(prec)));
-    HIPCHK(ctx, tmp.alloc(nrhs * n * cplx_bytes(prec)));
+    CallScratch scratch(ctx->stream);
+    struct {
+        void* p;
+    } in, out, tmp;
+    for (auto* f : {&in, &out, &tmp})
+        if (!(f->p = scratch(nrhs * n * cplx_bytes(prec)))) return fail(ctx, QCDW_ENOMEM, "out of device memory");
     hipStream_t s = ctx->stream;
     const PrecView v = view(op, prec);
     for (int k = 0; k < nrhs; k++)

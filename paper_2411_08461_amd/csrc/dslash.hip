@@ -12,7 +12,7 @@
 // projections of directions 2 gq and 2 gq + 1, so a site's four lanes share its loads and 4 V threads hide the
 // latency.  A block takes 64 sites of one parity; the blocks of the two parities of a tile run next to each
 // other, so that a link read as the forward link of one is still in the XCD's L2 as the backward link of the
-// other, and slices that are whole tiles are swept along t group by group (dslash_group).
+// other, and slices that are whole tiles are swept along t group by group (grouped_order).
 //
 // Measured, one call with its synchronisation: 24^3x64 400 us = 3.4 TB/s of the 1536 B per site (a device copy of
 // this part reaches 5.2 TB/s), 16^3x32 60 us, 4^4 20 us.  The pack-then-hop form took 1.6 ms of kernels at
@@ -88,21 +88,10 @@ __global__ __launch_bounds__(256) void k_dslash_paper(Geom g, const double2* __r
                                                       double kappa, double kc, int hop_p, int G)
 {
     const int b = xcd_tile(blockIdx.x, gridDim.x);
-    const int p = b & 1, tile = b >> 1;
+    const int p = b & 1, site = grouped_tile(g, b >> 1, G) * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
     const long Vh = g.Vh;
-    int site;
-    bool valid;
-    if (G > 0) {  // c-tile in its group of G, then t, then group
-        const int St = g.Lxh * g.Ly * g.Lz;
-        const int grp = tile / (G * g.Lt), r = tile - grp * G * g.Lt;
-        const int t = r / G, c = (grp * G + (r - t * G)) * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
-        site = t * St + c;
-        valid = c < St;
-    } else {
-        site = tile * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
-        valid = site < g.Vh;
-    }
     const int q = threadIdx.x & 3, gq = q >> 1, k = q & 1;
+    const bool valid = site < g.Vh;
     double2* o = out + ((long)p * Vh + site) * 12 + 3 * q;
     if (!CLOV && p != hop_p) {
         if (valid) {
@@ -160,25 +149,14 @@ __global__ __launch_bounds__(256) void k_dslash_paper(Geom g, const double2* __r
     }
 }
 
-// Tile order (see the kernel): 0 the eo order, else the c-tiles of a group swept along t, for slices that are
-// whole tiles (padded slices would leave lanes idle).  The group is the largest divisor of a slice's tiles up to
-// 32: 24^3x64 takes 27 of 108 (437 -> 400 us; 12, 18, 36, 54: 421, 416, 412, 404), 16^3x32 its 16 (64 -> 60 us).
-static int dslash_group(const Geom& g)
-{
-    if ((g.Lxh * g.Ly * g.Lz) % HOP_SITES_PER_BLOCK) return 0;
-    const int nct = hop_ctiles(g);
-    for (int d = nct < 32 ? nct : 32; d >= 4; d--)
-        if (nct % d == 0) return d;
-    return 0;
-}
-
 hipError_t launch_dslash_paper(hipStream_t s, const Geom& g, const void* U, const void* clover, const void* psi,
                                void* out, double kappa, double csw)
 {
-    // without padding both orders have the same blocks: two parities of every tile
+    // Groups in tile order: 24^3x64 takes 27 of 108 tiles (437 -> 400 us; 12, 18, 36, 54: 421, 416, 412, 404),
+    // 16^3x32 its 16 (64 -> 60 us).
     hipLaunchKernelGGL(k_dslash_paper<true>, dim3(2 * hop_blocks(g.Vh)), dim3(256), 0, s, g, (const double2*)U,
                        (const double*)clover, (const double2*)psi, (double2*)out, kappa, kappa * csw, 0,
-                       dslash_group(g));
+                       grouped_order(g));
     return hipGetLastError();
 }
 
@@ -186,7 +164,7 @@ hipError_t launch_hop_paper(hipStream_t s, const Geom& g, const void* U, const v
 {
     hipLaunchKernelGGL(k_dslash_paper<false>, dim3(2 * hop_blocks(g.Vh)), dim3(256), 0, s, g, (const double2*)U,
                        (const double*)nullptr, (const double2*)psi, (double2*)out, 1.0, 0.0, parity,
-                       dslash_group(g));
+                       grouped_order(g));
     return hipGetLastError();
 }
 
@@ -230,7 +208,7 @@ extern "C" qcdw_status qcdw_dslash(qcdw_ctx* ctx, const qcdw_lattice* lat, const
     if (!clover) {
         void* c = scratch(144UL * g.Vh * 8);
         if (!c) return fail(ctx, QCDW_ENOMEM, "out of device memory for the clover field");
-        HIPCHK(ctx, launch_clover_build(ctx->stream, g, in.U, c));
+        HIPCHK(ctx, clover_from_paper(ctx->stream, g, in.U, c, scratch(8UL * g.Vh * 9 * 16)));
         in.clover = c;
     }
     HIPCHK(ctx, launch_dslash_paper(ctx->stream, g, in.U, in.clover, in.psi, out, kappa, csw));

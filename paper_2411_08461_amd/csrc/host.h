@@ -67,6 +67,7 @@ namespace qcdw_host {
 struct BlockCache {
     std::mutex m;
     std::map<int, std::multimap<size_t, void*>> free;  // device -> (size, block)
+    std::map<int, size_t> held, limit;  // bytes in the cache, and at most a quarter of the device's memory
     // smallest cached block of at least `bytes` and at most a quarter (plus 1 MiB) larger
     void* take(int dev, size_t bytes, size_t& got)
     {
@@ -76,13 +77,26 @@ struct BlockCache {
         if (it == f.end() || it->first > bytes + bytes / 4 + (1u << 20)) return nullptr;
         void* q = it->second;
         got = it->first;
+        held[dev] -= got;
         f.erase(it);
         return q;
     }
     void give(int dev, void* q, size_t n)
     {
-        std::lock_guard<std::mutex> lk(m);
-        free[dev].emplace(n, q);
+        {
+            std::lock_guard<std::mutex> lk(m);
+            size_t& cap = limit[dev];
+            if (cap == 0) {
+                hipDeviceProp_t prop;
+                cap = hipGetDeviceProperties(&prop, dev) == hipSuccess ? prop.totalGlobalMem / 4 : 1;
+            }
+            if (held[dev] + n <= cap) {
+                free[dev].emplace(n, q);
+                held[dev] += n;
+                return;
+            }
+        }
+        (void)hipFree(q);
     }
     // return every cached block of the device to the runtime (the current device must be dev)
     void trim(int dev)
@@ -90,6 +104,7 @@ struct BlockCache {
         std::lock_guard<std::mutex> lk(m);
         for (auto& kv : free[dev]) (void)hipFree(kv.second);
         free[dev].clear();
+        held[dev] = 0;
     }
 };
 inline BlockCache& block_cache()
@@ -381,7 +396,7 @@ inline qcdw_status detach(qcdw_ctx* ctx, const Geom& g, OperatorInputs& in, cons
 
 // scratch of one call from the block cache; the stream is drained before the blocks go back
 struct CallScratch {
-    static constexpr int MAX = 4;
+    static constexpr int MAX = 5;
     hipStream_t s;
     PoolBuf buf[MAX];
     int used = 0;
@@ -395,6 +410,14 @@ struct CallScratch {
         return used < MAX && buf[used].alloc(n) == hipSuccess ? buf[used++].p : nullptr;
     }
 };
+
+// the clover field of the paper's links; planes: 9 complex per link of scratch (nullptr: out of memory)
+inline hipError_t clover_from_paper(hipStream_t s, const Geom& g, const void* U, void* clover, void* planes)
+{
+    if (!planes) return hipErrorOutOfMemory;
+    const hipError_t e = launch_pack_links(s, g, U, 18, planes, nullptr, F64, 18, nullptr);
+    return e != hipSuccess ? e : launch_clover_build(s, g, link_planes(planes, 18, nullptr, g.Vh), clover);
+}
 
 inline qcdw_status read_double(qcdw_ctx* ctx, const double* dev, double& out)
 {

@@ -91,6 +91,24 @@ __host__ __device__ inline bool hop_cgroup_fits(const Geom& g, int cg)
 {
     return cg == 0 || (cg > 0 && hop_ctiles(g) % cg == 0);
 }
+// Order of the 64-site tiles in kernels that run the two parities of a tile next to each other: 0 the eo order,
+// else the tiles of a group of G swept along t, so that what slice t shares with t - 1 and t + 1 is G tiles apart and
+// still in the XCD's L2.  Only for slices that are whole tiles (padded ones would leave lanes idle).
+inline int grouped_order(const Geom& g)
+{
+    if ((g.Lxh * g.Ly * g.Lz) % 64) return 0;
+    const int nct = hop_ctiles(g);
+    for (int d = nct < 32 ? nct : 32; d >= 4; d--)
+        if (nct % d == 0) return d;
+    return 0;
+}
+// the eo tile of place k in that order
+__device__ __forceinline__ int grouped_tile(const Geom& g, int k, int G)
+{
+    if (G == 0) return k;
+    const int grp = k / (G * g.Lt), r = k - grp * G * g.Lt, t = r / G;
+    return t * hop_ctiles(g) + grp * G + (r - t * G);
+}
 // blocks (and reduction partials) of one single-RHS hop launch
 __host__ __device__ inline int hop_blocks_nt(const Geom& g, int nt, int cg)
 {
@@ -225,8 +243,23 @@ hipError_t launch_pack_spinor(hipStream_t s, int prec, const Geom& g, const void
                               double scale);
 hipError_t launch_unpack_spinor(hipStream_t s, int prec, const Geom& g, const void* internal, int parity, void* paper,
                                 double scale);
-hipError_t launch_pack_gauge(hipStream_t s, int prec, int recon, const Geom& g, const void* paper, void* internal);
-hipError_t launch_pack_clover(hipStream_t s, int prec, const Geom& g, const void* paper, int parity, void* internal);
+// the paper's links into plane-major FP64 entries 0 .. R-1 (top; R = 6 or 9 for recon 12 or 18), plane-major
+// entries 6 .. 8 (low) and the inner precision's links (lo); each may be nullptr
+hipError_t launch_pack_links(hipStream_t s, const Geom& g, const void* paper, int recon, void* top, void* low,
+                             int prec_lo, int recon_lo, void* lo);
+
+// FP64 links, one plane of Vh sites per entry: entry e < 6 of (mu, p) at top + ((2 mu + p) top_rec + e) Vh + site,
+// entry e >= 6 at low + ((2 mu + p) low_rec + e - 6) Vh + site
+struct LinkPlanes {
+    const double2 *top, *low;
+    int top_rec, low_rec;
+    long Vh;
+};
+inline LinkPlanes link_planes(const void* top, int recon, const void* low, long Vh)
+{
+    if (recon == 18) return {(const double2*)top, (const double2*)top + 6 * Vh, 9, 9, Vh};
+    return {(const double2*)top, (const double2*)low, 6, 3, Vh};
+}
 
 // clover kernels on the paper layouts (FP64)
 // the 12 wall sources on slice t0 with spatial momentum mom (12 paper-layout fields into out)
@@ -239,16 +272,19 @@ hipError_t launch_meson_2pt(hipStream_t s, const Geom& g, const void* S, const v
 hipError_t launch_seq_sources(hipStream_t s, const Geom& g, const void* S, int t_f, int g_f, const int mom[3],
                               void* out);
 // C = wt sum_i sigma_i4 F_i4 + ws sum_{i<j} sigma_ij F_ij (wt = ws = 1: the isotropic clover field)
-hipError_t launch_clover_build(hipStream_t s, const Geom& g, const void* U, void* clover, double wt = 1.0,
+hipError_t launch_clover_build(hipStream_t s, const Geom& g, const LinkPlanes& U, void* clover, double wt = 1.0,
                                double ws = 1.0);
+// A = 1 - kappa csw C and its inverse per parity in the internal packing, the inverse also in prec_lo (F64: not);
+// notpd_count is raised by the blocks that are not positive definite
+hipError_t launch_clover_op(hipStream_t s, const Geom& g, const LinkPlanes& U, double wt, double ws, double kappa,
+                            double csw, void* const A[2], void* const inv[2], int prec_lo, void* const lo[2],
+                            int* notpd_count);
 hipError_t launch_clover_apply(hipStream_t s, const Geom& g, const void* clover, const void* psi, void* out,
                                double kappa, double csw);
 hipError_t launch_clover_invert(hipStream_t s, const Geom& g, const void* clover, double kappa, double csw,
                                 void* inv, int* notpd_count);
-// packed A = 1 - kappa csw C (paper clover layout) for the full-operator epilogue
 // clover fermion force of the bilinear 2 Re(Y^+ M X) (force.hip); Gam: scratch of 6 x 144 V bytes
 hipError_t launch_clover_force(hipStream_t s, const Geom& g, const void* U, const void* X, const void* Y,
                                double kappa, double csw, void* Gam, void* H);
-hipError_t launch_clover_to_A(hipStream_t s, const Geom& g, const void* clover, double kappa, double csw, void* A);
 
 }  // namespace qcdw

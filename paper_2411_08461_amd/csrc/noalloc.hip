@@ -87,7 +87,7 @@ extern "C" qcdw_status qcdw_dslash_noalloc(qcdw_ctx* ctx, const qcdw_lattice* la
     CHK(detach(ctx, g, in, out, take));
     if (!clover) {
         void* c = take(144UL * g.Vh * 8);
-        HIPCHK(ctx, launch_clover_build(s, g, in.U, c));
+        HIPCHK(ctx, clover_from_paper(s, g, in.U, c, take(8UL * g.Vh * 9 * 16)));
         in.clover = c;
     }
     HIPCHK(ctx, launch_dslash_paper(s, g, in.U, in.clover, in.psi, out, kappa, csw));

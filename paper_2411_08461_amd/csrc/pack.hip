@@ -31,51 +31,45 @@ __global__ void k_unpack_spinor(const void* in, double2* __restrict__ paper, int
     paper[((long)parity * Vh + site) * 12 + s * 3 + c] = make_double2(scale * (double)v.re, scale * (double)v.im);
 }
 
-// gauge: paper [4][2][Vh][3][3]  ->  internal links of R entries (rows 0..R/3-1) at link_base
-template <class P, int R>
-__global__ void k_pack_gauge(const double2* __restrict__ paper, void* out, int Vh)
+// Links: paper [4][2][Vh][3][3] into everything that is kept of them, in one pass.  A block stages 256 links of
+// one direction and parity in LDS (36 kB, whole runs in), then writes
+//   top: entries 0 .. R-1 plane-major in FP64 ([mu][p][R][Vh], the FP64 hop's layout), or nothing (nullptr);
+//   low: entries 6 .. 8 plane-major ([mu][p][3][Vh]; for the clover build when R = 6), or nothing;
+//   lo:  the inner precision's RL entries at link_base, or nothing.
+// At 16^3x32 with FP64 and BF16 links 36 us = 4.5 TB/s; a pass over the paper's field for each output took 45 us
+// and left out the third rows.
+template <int R, class PL, int RL>
+__global__ __launch_bounds__(256) void k_pack_links(const double2* __restrict__ paper, double2* __restrict__ top,
+                                                    double2* __restrict__ low, void* lo, int Vh)
 {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= 8L * Vh * R) return;
-    const int j = (int)(e % R);
-    const long link = e / R;  // (mu*2 + parity)*Vh + site
-    const int site = (int)(link % Vh), mp = (int)(link / Vh);
-    const double2 v = paper[link * 9 + j];
-    using T = typename P::real;
-    constexpr bool soa = link_soa_for(P::cbytes);
-    P::st(out, link_base(mp >> 1, mp & 1, site, Vh, R, soa) + j * link_stride(Vh, soa), cx<T>{(T)v.x, (T)v.y});
-}
-
-// clover: paper [2][Vh][2][36] -> internal (one parity) [Vh][2][36] in the reordered packing
-//   [d0 d1 d2 | L10 L20 L21 | L30 L31 L32 L40 L41 L42 L50 L51 L52 | d3 d4 d5 | L43 L53 L54]
-// The paper packing is [d0..d5 | L10 L20 L21 L30 L31 L32 L40 L41 L42 L43 L50 .. L54].
-__device__ __forceinline__ int clover_src_pos(int m)
-{
-    // lower slot s of (j,k) in the paper packing is j(j-1)/2 + k at reals 6+2s, 7+2s
-    if (m < 3) return m;                      // d0..d2
-    if (m < 9) return 6 + (m - 3);            // L10 L20 L21  (slots 0..2)
-    if (m < 27) {                             // L3x (slots 3..5), L4x (6..8), L5x (10..12)
-        const int q = (m - 9) >> 1, ri = (m - 9) & 1;
-        const int row = q / 3, col = q % 3;   // row 0..2 -> j = 3..5
-        const int j = 3 + row;
-        const int slot = j * (j - 1) / 2 + col;
-        return 6 + 2 * slot + ri;
+    __shared__ double2 u[256 * 9];
+    const int mp = blockIdx.y, s0 = blockIdx.x * 256;
+    const int n = Vh - s0 < 256 ? Vh - s0 : 256;
+    const double2* in = paper + ((long)mp * Vh + s0) * 9;
+    for (int e = threadIdx.x; e < n * 9; e += 256) u[e] = in[e];
+    __syncthreads();
+    if ((int)threadIdx.x < n) {
+        const double2* mine = u + threadIdx.x * 9;
+        const int site = s0 + threadIdx.x;
+        if (top) {
+#pragma unroll
+            for (int e = 0; e < R; e++) top[((long)mp * R + e) * Vh + site] = mine[e];
+        }
+        if (low) {
+#pragma unroll
+            for (int e = 0; e < 3; e++) low[((long)mp * 3 + e) * Vh + site] = mine[6 + e];
+        }
     }
-    if (m < 30) return 3 + (m - 27);          // d3..d5
-    const int q = (m - 30) >> 1, ri = (m - 30) & 1;  // L43 (9), L53 (13), L54 (14)
-    const int slot = q == 0 ? 9 : (q == 1 ? 13 : 14);
-    return 6 + 2 * slot + ri;
-}
-
-template <class P>
-__global__ void k_pack_clover(const double* __restrict__ paper, void* out, int Vh, int parity)
-{
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;  // = clov_index(site, chi, m)
-    if (e >= clov_reals(Vh)) return;
-    const int m = (int)(e % 36);
-    const long blk = e / 36;  // site * 2 + chirality
-    using T = typename P::real;
-    P::str(out, e, (T)paper[((long)parity * Vh * 2 + blk) * 36 + clover_src_pos(m)]);
+    if (lo) {
+        using T = typename PL::real;
+        constexpr bool soa = link_soa_for(PL::cbytes);
+        for (int e = threadIdx.x; e < n * RL; e += 256) {
+            const int k = e / RL, j = e - k * RL;
+            const double2 v = u[k * 9 + j];
+            PL::st(lo, link_base(mp >> 1, mp & 1, s0 + k, Vh, RL, soa) + j * link_stride(Vh, soa),
+                   cx<T>{(T)v.x, (T)v.y});
+        }
+    }
 }
 
 static inline dim3 grid_for(long n) { return dim3((unsigned)((n + 255) / 256)); }
@@ -112,40 +106,38 @@ hipError_t launch_unpack_spinor(hipStream_t s, int prec, const Geom& g, const vo
     return hipGetLastError();
 }
 
-hipError_t launch_pack_gauge(hipStream_t s, int prec, int recon, const Geom& g, const void* paper, void* internal)
+hipError_t launch_pack_links(hipStream_t s, const Geom& g, const void* paper, int recon, void* top, void* low,
+                             int prec_lo, int recon_lo, void* lo)
 {
-    const double2* pp = (const double2*)paper;
-    const int R = recon == 18 ? 9 : 6;
-    const long n = 8L * g.Vh * R;
-    if (n == 0) return hipSuccess;
-    if (R == 9) {
-        if (prec == F64) hipLaunchKernelGGL((k_pack_gauge<P64, 9>), grid_for(n), dim3(256), 0, s, pp, internal, g.Vh);
-        else if (prec == F32) hipLaunchKernelGGL((k_pack_gauge<P32, 9>), grid_for(n), dim3(256), 0, s, pp, internal, g.Vh);
-        else return hipErrorInvalidValue;
+    static_assert(link_soa_for(P64::cbytes), "the FP64 links are written plane-major");
+    if (g.Vh == 0) return hipSuccess;
+    const dim3 grid((unsigned)((g.Vh + 255) / 256), 8), block(256);
+#define QCDW_PACK(R, P, RL)                                                                                  \
+    hipLaunchKernelGGL((k_pack_links<R, P, RL>), grid, block, 0, s, (const double2*)paper, (double2*)top,    \
+                       (double2*)low, lo, g.Vh)
+    if (!lo) {
+        if (recon == 18)
+            QCDW_PACK(9, P32, 6);
+        else
+            QCDW_PACK(6, P32, 6);
+    } else if (recon_lo == 18) {
+        if (prec_lo != F32 || recon != 18) return hipErrorInvalidValue;
+        QCDW_PACK(9, P32, 9);
+    } else if (recon == 18) {
+        switch (prec_lo) {
+        case BF16: QCDW_PACK(9, PBF16, 6); break;
+        case F16: QCDW_PACK(9, PF16, 6); break;
+        default: return hipErrorInvalidValue;
+        }
     } else {
-        switch (prec) {
-        case F64: hipLaunchKernelGGL((k_pack_gauge<P64, 6>), grid_for(n), dim3(256), 0, s, pp, internal, g.Vh); break;
-        case F32: hipLaunchKernelGGL((k_pack_gauge<P32, 6>), grid_for(n), dim3(256), 0, s, pp, internal, g.Vh); break;
-        case BF16: hipLaunchKernelGGL((k_pack_gauge<PBF16, 6>), grid_for(n), dim3(256), 0, s, pp, internal, g.Vh); break;
-        case F16: hipLaunchKernelGGL((k_pack_gauge<PF16, 6>), grid_for(n), dim3(256), 0, s, pp, internal, g.Vh); break;
+        switch (prec_lo) {
+        case F32: QCDW_PACK(6, P32, 6); break;
+        case BF16: QCDW_PACK(6, PBF16, 6); break;
+        case F16: QCDW_PACK(6, PF16, 6); break;
         default: return hipErrorInvalidValue;
         }
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_pack_clover(hipStream_t s, int prec, const Geom& g, const void* paper, int parity, void* internal)
-{
-    const long n = clov_reals(g.Vh);
-    if (n == 0) return hipSuccess;
-    const double* pp = (const double*)paper;
-    switch (prec) {
-    case F64: hipLaunchKernelGGL(k_pack_clover<P64>, grid_for(n), dim3(256), 0, s, pp, internal, g.Vh, parity); break;
-    case F32: hipLaunchKernelGGL(k_pack_clover<P32>, grid_for(n), dim3(256), 0, s, pp, internal, g.Vh, parity); break;
-    case BF16: hipLaunchKernelGGL(k_pack_clover<PBF16>, grid_for(n), dim3(256), 0, s, pp, internal, g.Vh, parity); break;
-    case F16: hipLaunchKernelGGL(k_pack_clover<PF16>, grid_for(n), dim3(256), 0, s, pp, internal, g.Vh, parity); break;
-    default: return hipErrorInvalidValue;
-    }
+#undef QCDW_PACK
     return hipGetLastError();
 }
 
