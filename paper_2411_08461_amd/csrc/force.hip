@@ -16,9 +16,20 @@
 //     forward leaves are the four corners of the plaquette on the +sig side when rho is the plane's first
 //     direction (on the -sig side when it is the second), the backward leaves the four corners of the
 //     other plaquette.
-// Fields in the paper layouts (Sec. II.A), FP64: one thread per site computes Gam for the six planes,
-// then one thread per link the force (prefix and suffix products of each plaquette share the work of its
-// four corners).
+// Gam is anti-Hermitian, so the two kinds of leaves are one: with S = U2 U3 U4 the staple from x+rho round a
+// plaquette to x and d = +-sig its side, both are +-U_rho(x) T,
+//   T = Gam(x+rho) S + U2 (Gam(x+rho+d) U3 U4 + U3 (Gam(x+d) U4 + U4 Gam(x))),
+// a backward leaf as the adjoint of the same expression; likewise -A2 U^+ gives the part of U A2^+.  A link's
+// six plaquettes and its hop term are summed before the one product with U: 8 products a plaquette instead of 12.
+//
+// Three kernels.  The links go to plane-major copies (launch_pack_links, 9 entries).  k_force_gamma takes 64 sites
+// per block, stages X and Y in LDS, writes Gam as 8 real planes per lattice plane and X and Y as 12 complex
+// planes each.  k_force_link takes 64 sites of one parity per block, a wave per link direction and a lane per site,
+// so every load is a whole run; H leaves through LDS.  From the paper's records (144 and 192 bytes, a cache line
+// per lane and load) with Gam in full matrices the link kernel took 574 us at 16^3x32, bound by the address path.
+// Measured at 16^3x32, one call: 606 -> 238 us (link copies 32, Gam 30, links 170 us).  The link kernel's multiply-adds
+// need 88 us at the full FP64 rate; two waves per SIMD (256 VGPRs) hide the loads better than one (215 us) and than
+// three, which spill (395 us).
 #include "host.h"
 
 namespace qcdw {
@@ -27,38 +38,25 @@ namespace {
 
 using c3 = cx<double>[3][3];
 
-struct FGeom {
-    int L[4];
-    int Lxh, Vh;
-    int t_bc;
+// the site reached from c by a step s1 along m1 and s2 along m2 (each -1, 0 or 1; the directions uniform over the
+// wave): its parity and checkerboard index
+struct Site {
+    int parity, cb;
 };
-
-// eo index (parity * Vh + site) of full coordinates, periodic
-__device__ __forceinline__ int eo_of(const FGeom& g, int x, int y, int z, int t)
+__device__ __forceinline__ Site step(const Geom& g, const int (&c)[4], int m1, int s1, int m2, int s2)
 {
-    const int p = (x + y + z + t) & 1;
-    return p * g.Vh + ((t * g.L[2] + z) * g.L[1] + y) * g.Lxh + (x >> 1);
-}
-__device__ __forceinline__ void coords_of(const FGeom& g, int e, int (&c)[4])
-{
-    const int p = e >= g.Vh, i = e - p * g.Vh;
-    const int xh = i % g.Lxh;
-    int r = i / g.Lxh;
-    c[1] = r % g.L[1];
-    r /= g.L[1];
-    c[2] = r % g.L[2];
-    c[3] = r / g.L[2];
-    c[0] = 2 * xh + ((p + c[1] + c[2] + c[3]) & 1);
-}
-__device__ __forceinline__ int shifted(const FGeom& g, const int (&c)[4], int mu, int d)
-{
-    int q[4] = {c[0], c[1], c[2], c[3]};
-    q[mu] = (q[mu] + d + g.L[mu]) % g.L[mu];
-    return eo_of(g, q[0], q[1], q[2], q[3]);
+    const int L[4] = {g.Lx, g.Ly, g.Lz, g.Lt};
+    int o[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int v = c[i] + (i == m1 ? s1 : 0) + (i == m2 ? s2 : 0);
+        o[i] = v < 0 ? L[i] - 1 : (v == L[i] ? 0 : v);
+    }
+    return {(o[0] + o[1] + o[2] + o[3]) & 1, ((o[3] * g.Lz + o[2]) * g.Ly + o[1]) * g.Lxh + (o[0] >> 1)};
 }
 
 // DeGrand-Rossi gamma_mu: one nonzero per row, gamma_mu[s][perm] = ph
-__device__ __forceinline__ int gperm(int mu, int s) { return mu < 2 ? 3 - s : (s + 2) & 3; }
+__device__ __forceinline__ constexpr int gperm(int mu, int s) { return mu < 2 ? 3 - s : (s + 2) & 3; }
 __device__ __forceinline__ cx<double> gph(int mu, int s)
 {
     switch (mu) {
@@ -69,280 +67,304 @@ __device__ __forceinline__ cx<double> gph(int mu, int s)
     }
 }
 
-__device__ __forceinline__ void ld3(const double2* p, c3& m)
-{
-#pragma unroll
-    for (int i = 0; i < 9; i++) m[i / 3][i % 3] = {p[i].x, p[i].y};
-}
-__device__ __forceinline__ void dag(const c3& a, c3& o)
-{
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) o[i][j] = conj(a[j][i]);
-}
-__device__ __forceinline__ void mul(const c3& a, const c3& b, c3& o)
-{
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            cx<double> s = a[i][0] * b[0][j];
-            s = s + a[i][1] * b[1][j];
-            s = s + a[i][2] * b[2][j];
-            o[i][j] = s;
-        }
-}
-__device__ __forceinline__ void addto(c3& o, const c3& a)
-{
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) o[i][j] = o[i][j] + a[i][j];
-}
-// o += w (G - G^+) / (2i)
-__device__ __forceinline__ void add_herm(c3& o, const c3& G, double w)
-{
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            const cx<double> d = G[i][j] - conj(G[j][i]);  // G - G^+
-            o[i][j] = o[i][j] + cx<double>{w * d.im * 0.5, -w * d.re * 0.5};  // d / (2i)
-        }
-}
-
 // plane index of (mu, nu), mu < nu: (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
 __device__ __forceinline__ int plane_of(int mu, int nu)
 {
     return mu == 0 ? nu - 1 : (mu == 1 ? nu + 1 : 5);
 }
 
-}  // namespace
-
-// Gam[p][e] (6 planes, V sites in eo order) = traceless part of (L - L^+), L = sum_s (sigma X)_s Y_s^+,
-// sigma_{mu nu} = g_mu g_nu (mu != nu, the DeGrand-Rossi gammas anticommute)
-__global__ __launch_bounds__(256) void k_force_gamma(FGeom g, const double2* __restrict__ X,
-                                                     const double2* __restrict__ Y, double2* Gam)
+// t = u t, in place column by column
+__device__ __forceinline__ void left_mul(const c3& u, c3& t)
 {
-    const int V = 2 * g.Vh;
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= V) return;
-    cx<double> xs[4][3], ys[4][3];
 #pragma unroll
-    for (int s = 0; s < 4; s++)
+    for (int j = 0; j < 3; j++) {
+        const cx<double> a = t[0][j], b = t[1][j], c = t[2][j];
 #pragma unroll
-        for (int c = 0; c < 3; c++) {
-            const double2 a = X[(long)e * 12 + 3 * s + c], b = Y[(long)e * 12 + 3 * s + c];
-            xs[s][c] = {a.x, a.y};
-            ys[s][c] = {b.x, b.y};
+        for (int i = 0; i < 3; i++) {
+            cx<double> s = u[i][0] * a;
+            cmac(s, u[i][1], b);
+            cmac(s, u[i][2], c);
+            t[i][j] = s;
         }
-#pragma unroll
-    for (int mu = 0; mu < 4; mu++)
-#pragma unroll
-        for (int nu = mu + 1; nu < 4; nu++) {
-            c3 Lm;
-#pragma unroll
-            for (int i = 0; i < 3; i++)
-#pragma unroll
-                for (int j = 0; j < 3; j++) Lm[i][j] = {0.0, 0.0};
-#pragma unroll
-            for (int s = 0; s < 4; s++) {
-                const int s1 = gperm(mu, s), s2 = gperm(nu, s1);
-                const cx<double> ph = gph(mu, s) * gph(nu, s1);  // (g_mu g_nu)[s][s2]
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    const cx<double> sx = ph * xs[s2][i];
-#pragma unroll
-                    for (int j = 0; j < 3; j++) Lm[i][j] = Lm[i][j] + sx * conj(ys[s][j]);
-                }
-            }
-            c3 Gm;
-#pragma unroll
-            for (int i = 0; i < 3; i++)
-#pragma unroll
-                for (int j = 0; j < 3; j++) Gm[i][j] = Lm[i][j] - conj(Lm[j][i]);
-            const cx<double> tr3 = {(Gm[0][0].re + Gm[1][1].re + Gm[2][2].re) / 3.0,
-                                    (Gm[0][0].im + Gm[1][1].im + Gm[2][2].im) / 3.0};
-#pragma unroll
-            for (int i = 0; i < 3; i++) Gm[i][i] = Gm[i][i] - tr3;
-            double2* o = Gam + ((long)plane_of(mu, nu) * V + e) * 9;
-#pragma unroll
-            for (int i = 0; i < 9; i++) o[i] = make_double2(Gm[i / 3][i % 3].re, Gm[i / 3][i % 3].im);
-        }
+    }
 }
 
-// H for every link (rho, e), one thread per link; U, H: paper gauge layout [4][V][3][3]
-__global__ __launch_bounds__(256) void k_force_link(FGeom g, const double2* __restrict__ U,
-                                                    const double2* __restrict__ X, const double2* __restrict__ Y,
-                                                    const double2* __restrict__ Gam, double kappa, double csw,
-                                                    double2* H)
-{
-    const int V = 2 * g.Vh;
-    const long tid = (long)blockIdx.x * 256 + threadIdx.x;
-    if (tid >= 4L * V) return;
-    const int rho = (int)(tid / V), e = (int)(tid - (long)rho * V);
-    int c[4];
-    coords_of(g, e, c);
-    const int ep = shifted(g, c, rho, 1);
-    auto link = [&](int mu, int site, c3& m) { ld3(U + ((long)mu * V + site) * 9, m); };
-    auto gam = [&](int p, int site, c3& m) { ld3(Gam + ((long)p * V + site) * 9, m); };
-    c3 u, ud, K;
-    link(rho, e, u);
-    dag(u, ud);
-#pragma unroll
-    for (int i = 0; i < 3; i++)
-#pragma unroll
-        for (int j = 0; j < 3; j++) K[i][j] = {0.0, 0.0};
-
-    // hop term: B = s (U A1 - A2 U^+)
+// A traceless anti-Hermitian matrix by its 8 reals: Im of entries 00 and 11, then entries 01, 02, 12
+struct Anti {
+    double r[8];
+    __device__ __forceinline__ double diag(int i) const { return i < 2 ? r[i] : -(r[0] + r[1]); }
+    __device__ __forceinline__ cx<double> at(int i, int j) const  // i != j
     {
-        c3 A1, A2;
-#pragma unroll
-        for (int i = 0; i < 3; i++)
-#pragma unroll
-            for (int j = 0; j < 3; j++) A1[i][j] = A2[i][j] = {0.0, 0.0};
-        for (int s = 0; s < 4; s++) {
-            const int so = gperm(rho, s);
-            const cx<double> ph = gph(rho, s);
-            for (int i = 0; i < 3; i++) {
-                const double2 xa = X[(long)ep * 12 + 3 * s + i], xb = X[(long)ep * 12 + 3 * so + i];
-                const double2 xc = X[(long)e * 12 + 3 * s + i], xd = X[(long)e * 12 + 3 * so + i];
-                const cx<double> w1 = cx<double>{xa.x, xa.y} - ph * cx<double>{xb.x, xb.y};  // (1 - g) X(x+rho)
-                const cx<double> w2 = cx<double>{xc.x, xc.y} + ph * cx<double>{xd.x, xd.y};  // (1 + g) X(x)
-                for (int j = 0; j < 3; j++) {
-                    const double2 ya = Y[(long)e * 12 + 3 * s + j], yb = Y[(long)ep * 12 + 3 * s + j];
-                    A1[i][j] = A1[i][j] + w1 * cx<double>{ya.x, -ya.y};
-                    A2[i][j] = A2[i][j] + w2 * cx<double>{yb.x, -yb.y};
-                }
-            }
-        }
-        c3 B, T;
-        mul(u, A1, B);
-        mul(A2, ud, T);
-#pragma unroll
-        for (int i = 0; i < 3; i++)
-#pragma unroll
-            for (int j = 0; j < 3; j++) B[i][j] = B[i][j] - T[i][j];
-        const double sgn = (rho == 3 && g.t_bc < 0 && c[3] == g.L[3] - 1) ? -1.0 : 1.0;
-        add_herm(K, B, kappa * sgn);
+        const int k = 2 * (i + j);
+        return i < j ? cx<double>{r[k], r[k + 1]} : cx<double>{-r[k], r[k + 1]};
     }
+};
 
-    // clover term: the two plaquettes through the link in each plane (rho, sig)
-    const double wcl = kappa * csw / 8.0;
-    for (int sig = 0; sig < 4; sig++) {
-        if (sig == rho) continue;
-        const int p = rho < sig ? plane_of(rho, sig) : plane_of(sig, rho);
-        const int dfw = rho < sig ? 1 : -1;  // side of the plaquette run forward
-        for (int side = 0; side < 2; side++) {
-            const int d = side == 0 ? dfw : -dfw;  // plaquette on the d sig side of the link
-            const int e_d = shifted(g, c, sig, d);  // y + d sig
-            int cd[4] = {c[0], c[1], c[2], c[3]};
-            cd[sig] = (cd[sig] + d + g.L[sig]) % g.L[sig];
-            const int e_dr = shifted(g, cd, rho, 1);  // y + d sig + rho
-            const int e_dmr = d > 0 ? ep : shifted(g, cd, rho, 1);  // base of the sig link on the y+rho side
-            c3 a, b, G0, G1, G2, G3;
-            if (side == 0) {
-                // forward: G = U U2 U3 U4 with Gam at y+rho, y+rho+d, y+d, y (after U, U2, U3, U4)
-                c3 U2, U3, U4, t1;
-                if (d > 0) {
-                    link(sig, ep, U2);                  // U_sig(y+rho)
-                } else {
-                    link(sig, e_dmr, t1);               // U_sig(y+rho-sig)^+
-                    dag(t1, U2);
-                }
-                link(rho, e_d, t1);                     // U_rho(y+d)^+
-                dag(t1, U3);
-                if (d > 0) {
-                    link(sig, e, t1);                   // U_sig(y)^+
-                    dag(t1, U4);
-                } else {
-                    link(sig, e_d, U4);                 // U_sig(y-sig)
-                }
-                c3 S34, S234, P12, P123, P1234;
-                mul(U3, U4, S34);
-                mul(U2, S34, S234);
-                mul(u, U2, P12);
-                mul(P12, U3, P123);
-                mul(P123, U4, P1234);
-                c3 G;
-                gam(p, ep, G0);
-                mul(G0, S234, a);
-                mul(u, a, G);
-                gam(p, e_dr, G1);
-                mul(G1, S34, a);
-                mul(P12, a, b);
-                addto(G, b);
-                gam(p, e_d, G2);
-                mul(G2, U4, a);
-                mul(P123, a, b);
-                addto(G, b);
-                gam(p, e, G3);
-                mul(P1234, G3, b);
-                addto(G, b);
-                add_herm(K, G, wcl);
-            } else {
-                // backward: G' = V1 V2 V3 U^+ with Gam at y, y+d, y+d+rho, y+rho (before V1, V2, V3, U^+)
-                c3 V1, V2, V3, t1;
-                if (d > 0) {
-                    link(sig, e, V1);                   // U_sig(y)
-                } else {
-                    link(sig, e_d, t1);                 // U_sig(y-sig)^+
-                    dag(t1, V1);
-                }
-                link(rho, e_d, V2);                     // U_rho(y+d)
-                if (d > 0) {
-                    link(sig, ep, t1);                  // U_sig(y+rho)^+
-                    dag(t1, V3);
-                } else {
-                    link(sig, e_dmr, V3);               // U_sig(y+rho-sig)
-                }
-                c3 R3, R23, R123, Q12, Q123;
-                mul(V3, ud, R3);
-                mul(V2, R3, R23);
-                mul(V1, R23, R123);
-                mul(V1, V2, Q12);
-                mul(Q12, V3, Q123);
-                c3 G;
-                gam(p, e, G0);
-                mul(G0, R123, G);
-                gam(p, e_d, G1);
-                mul(G1, R23, a);
-                mul(V1, a, b);
-                addto(G, b);
-                gam(p, e_dr, G2);
-                mul(G2, R3, a);
-                mul(Q12, a, b);
-                addto(G, b);
-                gam(p, ep, G3);
-                mul(G3, ud, a);
-                mul(Q123, a, b);
-                addto(G, b);
-                add_herm(K, G, -wcl);
-            }
-        }
-    }
-    // traceless part
-    const double tr = (K[0][0].re + K[1][1].re + K[2][2].re) / 3.0;
-    double2* o = H + tid * 9;
+// t += G m, and t += m G
+__device__ __forceinline__ void add_gm(c3& t, const Anti& G, const c3& m)
+{
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
         for (int j = 0; j < 3; j++) {
-            const cx<double> v = K[i][j];
-            o[3 * i + j] = make_double2(i == j ? v.re - tr : v.re, i == j ? 0.0 : v.im);
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                if (k == i) {
+                    t[i][j].re -= G.diag(i) * m[i][j].im;
+                    t[i][j].im += G.diag(i) * m[i][j].re;
+                } else {
+                    cmac(t[i][j], G.at(i, k), m[k][j]);
+                }
+            }
+        }
+}
+__device__ __forceinline__ void add_mg(c3& t, const c3& m, const Anti& G)
+{
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                if (k == j) {
+                    t[i][j].re -= G.diag(j) * m[i][j].im;
+                    t[i][j].im += G.diag(j) * m[i][j].re;
+                } else {
+                    cmac(t[i][j], G.at(k, j), m[i][k]);
+                }
+            }
         }
 }
 
-hipError_t launch_clover_force(hipStream_t s, const Geom& g, const void* U, const void* X, const void* Y,
-                               double kappa, double csw, void* Gam, void* H)
+constexpr int FS = 64;  // sites per block
+
+// Gam of plane (MU, NU) at a site: the traceless part of L - L^+, L = sum_s (sigma X)_s Y_s^+, sigma_{mu nu} = g_mu g_nu
+// (mu != nu, the DeGrand-Rossi gammas anticommute)
+template <int MU, int NU>
+__device__ __forceinline__ Anti gamma_plane(const double2* x, const double2* y)
 {
-    FGeom f{{g.Lx, g.Ly, g.Lz, g.Lt}, g.Lxh, g.Vh, g.t_bc};
-    const int V = 2 * g.Vh;
-    hipLaunchKernelGGL(k_force_gamma, dim3((V + 255) / 256), dim3(256), 0, s, f, (const double2*)X,
-                       (const double2*)Y, (double2*)Gam);
-    hipLaunchKernelGGL(k_force_link, dim3((unsigned)((4L * V + 255) / 256)), dim3(256), 0, s, f, (const double2*)U,
-                       (const double2*)X, (const double2*)Y, (const double2*)Gam, kappa, csw, (double2*)H);
+    c3 L;
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) L[i][j] = {0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        const int s1 = gperm(MU, s), s2 = gperm(NU, s1);
+        const cx<double> ph = gph(MU, s) * gph(NU, s1);  // (g_mu g_nu)[s][s2]
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const double2 v = x[3 * s2 + i];
+            const cx<double> sx = ph * cx<double>{v.x, v.y};
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const double2 w = y[3 * s + j];
+                cmac_conj(L[i][j], {w.x, w.y}, sx);
+            }
+        }
+    }
+    const double tr = (L[0][0].im + L[1][1].im + L[2][2].im) * (2.0 / 3.0);
+    Anti G;
+    G.r[0] = 2.0 * L[0][0].im - tr;
+    G.r[1] = 2.0 * L[1][1].im - tr;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int i = k == 2 ? 1 : 0, j = k == 0 ? 1 : 2;
+        G.r[2 + 2 * k] = L[i][j].re - L[j][i].re;
+        G.r[3 + 2 * k] = L[i][j].im + L[j][i].im;
+    }
+    return G;
+}
+
+}  // namespace
+
+// Gam[(8 plane + k) V + e] (6 planes, V sites in eo order) and XY[c V + e]: the 12 components of X, then of Y
+__global__ __launch_bounds__(384) void k_force_gamma(int V, const double2* __restrict__ X,
+                                                     const double2* __restrict__ Y, double* __restrict__ Gam,
+                                                     double2* __restrict__ XY)
+{
+    constexpr int ROW = 13;  // 12 complex padded: a lane's row starts in another bank than its neighbours'
+    __shared__ double2 sx[FS * ROW], sy[FS * ROW];
+    const int e0 = blockIdx.x * FS, n = V - e0 < FS ? V - e0 : FS;
+    for (int k = threadIdx.x; k < n * 12; k += 384) {
+        sx[k / 12 * ROW + k % 12] = X[(long)e0 * 12 + k];
+        sy[k / 12 * ROW + k % 12] = Y[(long)e0 * 12 + k];
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, plane = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (lane >= n) return;
+    const double2 *x = sx + lane * ROW, *y = sy + lane * ROW;
+    for (int c = plane; c < 24; c += 6) XY[(long)c * V + e0 + lane] = c < 12 ? x[c] : y[c - 12];
+    Anti G;
+    switch (plane) {
+    case 0: G = gamma_plane<0, 1>(x, y); break;
+    case 1: G = gamma_plane<0, 2>(x, y); break;
+    case 2: G = gamma_plane<0, 3>(x, y); break;
+    case 3: G = gamma_plane<1, 2>(x, y); break;
+    case 4: G = gamma_plane<1, 3>(x, y); break;
+    default: G = gamma_plane<2, 3>(x, y); break;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) Gam[(long)(8 * plane + k) * V + e0 + lane] = G.r[k];
+}
+
+namespace {
+
+// what a lane of k_force_link reads
+struct ForceFields {
+    LinkPlanes U;
+    const double* Gam;
+    const double2* XY;
+    long V;
+    // link (mu, site), adjoint if DAG
+    template <bool DAG>
+    __device__ __forceinline__ void link(int mu, Site s, c3& m) const
+    {
+        const double2* p = U.top + (long)(mu * 2 + s.parity) * U.top_rec * U.Vh + s.cb;
+        const double2* q = U.low + (long)(mu * 2 + s.parity) * U.low_rec * U.Vh + s.cb;
+#pragma unroll
+        for (int e = 0; e < 9; e++) {
+            const double2 v = e < 6 ? p[e * U.Vh] : q[(e - 6) * U.Vh];
+            if (DAG)
+                m[e % 3][e / 3] = {v.x, -v.y};
+            else
+                m[e / 3][e % 3] = {v.x, v.y};
+        }
+    }
+    __device__ __forceinline__ Anti gam(int p, Site s) const
+    {
+        Anti G;
+#pragma unroll
+        for (int k = 0; k < 8; k++) G.r[k] = Gam[(long)(8 * p + k) * V + s.parity * U.Vh + s.cb];
+        return G;
+    }
+    // row k of the half-spinor (1 + sg gamma_mu) projects a spinor on (X: first = 0, Y: first = 12), see hop_common.h
+    __device__ __forceinline__ void half(int first, Site s, int mu, int k, double sg, cx<double> (&h)[3]) const
+    {
+        const long e = s.parity * U.Vh + s.cb;
+        const int l = gperm(mu, k);
+        const cx<double> c = gph(mu, k);
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const double2 a = XY[(first + 3 * k + i) * V + e], b = XY[(first + 3 * l + i) * V + e];
+            const cx<double> w = c * cx<double>{b.x, b.y};
+            h[i] = {a.x + sg * w.re, a.y + sg * w.im};
+        }
+    }
+};
+
+// acc += sgn T for the plaquette of (rho, sig) on side D = +-1 (file header)
+template <int D>
+__device__ __forceinline__ void add_plaquette(const ForceFields& f, const Geom& g, const int (&c)[4], int rho, int sig,
+                                              int p, double sgn, Site y, Site yr, c3& acc)
+{
+    const Site yd = step(g, c, sig, D, sig, 0), yrd = step(g, c, rho, 1, sig, D);
+    c3 S, t, u;
+    f.link<(D > 0)>(sig, D > 0 ? y : yd, S);  // U4: from x+d to x
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) t[i][j] = {0.0, 0.0};
+    add_gm(t, f.gam(p, yd), S);
+    add_mg(t, S, f.gam(p, y));
+    f.link<true>(rho, yd, u);  // U3: from x+rho+d to x+d
+    left_mul(u, t);
+    left_mul(u, S);
+    add_gm(t, f.gam(p, yrd), S);
+    f.link<(D < 0)>(sig, D > 0 ? yr : yrd, u);  // U2: from x+rho to x+rho+d
+    left_mul(u, t);
+    left_mul(u, S);
+    add_gm(t, f.gam(p, yr), S);
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            acc[i][j].re += sgn * t[i][j].re;
+            acc[i][j].im += sgn * t[i][j].im;
+        }
+}
+
+}  // namespace
+
+// H (paper gauge layout [4][2][Vh][3][3]): a block takes 64 sites of one parity, wave rho their links rho
+__global__ __launch_bounds__(256, 2) void k_force_link(Geom g, ForceFields f, double kappa, double csw,
+                                                    double2* __restrict__ H, int G)
+{
+    __shared__ double2 stage[4][FS * 9];
+    const int blk = xcd_tile(blockIdx.x, gridDim.x);
+    const int parity = blk & 1, tile = grouped_tile(g, blk >> 1, G);
+    const int lane = threadIdx.x & 63, rho = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int site = tile * FS + lane;
+    int c[4];
+    site_coords(g, site < g.Vh ? site : g.Vh - 1, parity, c[0], c[1], c[2], c[3]);
+    const Site y = step(g, c, 0, 0, 0, 0), yr = step(g, c, rho, 1, rho, 0);
+    c3 acc;
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++) acc[i][j] = {0.0, 0.0};
+    // clover term: the two plaquettes through the link in each plane (rho, sig)
+    const double wcl = kappa * csw / 8.0;
+#pragma unroll 1
+    for (int sig = 0; sig < 4; sig++) {
+        if (sig == rho) continue;
+        const int p = rho < sig ? plane_of(rho, sig) : plane_of(sig, rho);
+        const double w = rho < sig ? wcl : -wcl;  // the side whose plaquette runs the link forward
+        add_plaquette<1>(f, g, c, rho, sig, p, w, y, yr, acc);
+        add_plaquette<-1>(f, g, c, rho, sig, p, -w, y, yr, acc);
+    }
+    // hop term: kappa s (A1 + A2^+), A1 = sum_s [(1 - g) X(x+rho)]_s Y(x)_s^+ = sum_k h_k(X(x+rho)) h_k(Y(x))^+ over
+    // the two rows of the half-spinors, A2^+ = sum_k h_k(Y(x+rho)) h_k(X(x))^+ with 1 + g
+    const double sk = (rho == 3 && g.t_bc < 0 && c[3] == g.Lt - 1) ? -kappa : kappa;
+#pragma unroll 1
+    for (int k = 0; k < 2; k++) {
+        cx<double> a[3], b[3];
+        f.half(0, yr, rho, k, -1.0, a);
+        f.half(12, y, rho, k, -1.0, b);
+#pragma unroll
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) cmac_conj(acc[i][j], {sk * b[j].re, sk * b[j].im}, a[i]);
+        f.half(12, yr, rho, k, 1.0, a);
+        f.half(0, y, rho, k, 1.0, b);
+#pragma unroll
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) cmac_conj(acc[i][j], {sk * b[j].re, sk * b[j].im}, a[i]);
+    }
+    // H = the traceless Hermitian part (B - B^+) / (2i) of B = U acc
+    c3 u;
+    f.link<false>(rho, y, u);
+    left_mul(u, acc);
+    double2* o = stage[rho] + lane * 9;
+    const double tr = (acc[0][0].im + acc[1][1].im + acc[2][2].im) / 3.0;
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+            o[3 * i + j] = i == j ? make_double2(acc[i][i].im - tr, 0.0)
+                                  : make_double2(0.5 * (acc[i][j].im + acc[j][i].im),
+                                                 -0.5 * (acc[i][j].re - acc[j][i].re));
+    __syncthreads();
+    const int left = g.Vh - tile * FS, n = (left < FS ? left : FS) * 9;
+    double2* h = H + ((long)(2 * rho + parity) * g.Vh + (long)tile * FS) * 9;
+    for (int e = lane; e < n; e += 64) h[e] = stage[rho][e];
+}
+
+hipError_t launch_clover_force(hipStream_t s, const Geom& g, const void* U, const void* X, const void* Y,
+                               double kappa, double csw, void* scratch, void* H)
+{
+    const long V = 2L * g.Vh;
+    double2* planes = (double2*)scratch;  // links [4][2][9][Vh], X and Y [24][V], Gam [48][V] reals
+    double2* XY = planes + 36 * V;
+    double* Gam = (double*)(XY + 24 * V);
+    hipError_t e = launch_pack_links(s, g, U, 18, planes, nullptr, F64, 18, nullptr);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_force_gamma, dim3((unsigned)((V + FS - 1) / FS)), dim3(384), 0, s, (int)V, (const double2*)X,
+                       (const double2*)Y, Gam, XY);
+    const ForceFields f{link_planes(planes, 18, nullptr, g.Vh), Gam, XY, V};
+    hipLaunchKernelGGL(k_force_link, dim3(2 * ((g.Vh + FS - 1) / FS)), dim3(256), 0, s, g, f, kappa, csw, (double2*)H,
+                       grouped_order(g));
     return hipGetLastError();
 }
 
@@ -361,11 +383,10 @@ extern "C" qcdw_status qcdw_clover_force(qcdw_ctx* ctx, const qcdw_lattice* lat,
     CHK(check_dev(ctx, H, "H"));
     if (H == U || H == X || H == Y) return fail(ctx, QCDW_EINVAL, "H must not alias U, X or Y");
     if (!std::isfinite(kappa) || !std::isfinite(csw)) return fail(ctx, QCDW_EINVAL, "kappa and csw must be finite");
-    PoolBuf gam;  // Gam for the six planes, [6][V][3][3] complex; the stream is drained before it goes back
-    HIPCHK(ctx, gam.alloc(6UL * 2 * g.Vh * 9 * 16));
-    const hipError_t launched = launch_clover_force(ctx->stream, g, U, X, Y, kappa, csw, gam.p, H);
-    const hipError_t drained = hipStreamSynchronize(ctx->stream);
-    HIPCHK(ctx, launched);
-    HIPCHK(ctx, drained);
+    CallScratch scratch(ctx->stream);
+    void* work = scratch(2UL * g.Vh * FORCE_SITE_BYTES);
+    if (!work) return fail(ctx, QCDW_ENOMEM, "out of device memory for the force's workspace");
+    HIPCHK(ctx, launch_clover_force(ctx->stream, g, U, X, Y, kappa, csw, work, H));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return QCDW_OK;
 }

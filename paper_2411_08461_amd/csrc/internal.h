@@ -283,8 +283,9 @@ hipError_t launch_clover_apply(hipStream_t s, const Geom& g, const void* clover,
                                double kappa, double csw);
 hipError_t launch_clover_invert(hipStream_t s, const Geom& g, const void* clover, double kappa, double csw,
                                 void* inv, int* notpd_count);
-// clover fermion force of the bilinear 2 Re(Y^+ M X) (force.hip); Gam: scratch of 6 x 144 V bytes
+// clover fermion force of the bilinear 2 Re(Y^+ M X) (force.hip); scratch: FORCE_SITE_BYTES per site
+constexpr size_t FORCE_SITE_BYTES = (36 + 24) * 16 + 48 * 8;
 hipError_t launch_clover_force(hipStream_t s, const Geom& g, const void* U, const void* X, const void* Y,
-                               double kappa, double csw, void* Gam, void* H);
+                               double kappa, double csw, void* scratch, void* H);
 
 }  // namespace qcdw
