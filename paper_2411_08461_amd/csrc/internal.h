@@ -222,11 +222,23 @@ hipError_t launch_hop_rhs(hipStream_t s, int prec, int epi, int red, const HopAr
 hipError_t launch_net_layer(hipStream_t s, int pin, int pout, int cin, int cout, const void* in, void* out,
                             const void* gauge32, const void* W, const Geom& g,
                             int mfma = 0);
-// out[2 cin cout] (+)= weight gradient of hop a: sum_x g_{c'} conj(T_a phi_c); partials: [blocks][2 cin cout]
-hipError_t launch_net_wgrad(hipStream_t s, int cin, int cout, const void* phi, const void* gz, const void* gauge32,
-                            const Geom& g, int a, double* partials, double* out, int accumulate);
+// training (net.hip): what a pair's loss and gradients are formed from.  r: FP32 residual on even sites; gz, hid,
+// gh: scratch; W1, W2 the layers, Wt the adjoint of layer 2; partials: train_partials() doubles, kept over the pairs of
+// a batch
+struct TrainFields {
+    const void *gauge32, *r;
+    void *gz, *hid, *gh;
+    const void *W1, *W2, *Wt;
+    double* partials;
+};
+size_t train_partials(const Geom& g, int hidden);
+// adds a pair's gradients to the partial sums (first: starts them) and writes dn = ||P(r) - e||^2; e: paper field of
+// the even sites, en: its squared norm on the device
+hipError_t launch_train_pair(hipStream_t s, int hidden, const Geom& g, const TrainFields& f, const void* e,
+                             const double* en, double* dn, bool first);
+// the sums of the pairs since the first one into G1 [9][hidden][4] and G2 [9][4][hidden] (FP64 complex)
+hipError_t launch_train_finish(hipStream_t s, int hidden, const Geom& g, double* partials, void* G1, void* G2);
 hipError_t launch_net_adjoint_w(hipStream_t s, const void* W, void* Wt, int cout, int cin);
-hipError_t launch_net_make_gz(hipStream_t s, const void* diff, void* gz, long n_half, double coef);
 hipError_t launch_gaussian(hipStream_t s, void* out, long n, uint64_t seed, uint64_t stream);  // FP64 complex
 hipError_t launch_adam(hipStream_t s, void* W, const double* G, double* m, double* v, int n, double lr, double b1,
                        double b2, double eps, int step, double gscale);

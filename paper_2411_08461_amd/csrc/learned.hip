@@ -16,9 +16,10 @@ struct qcdw_net {
     PoolBuf W1, W2, Wt;                // FP32 complex weights and the adjoint-layer scratch
     PoolBuf W1bf, W2bf;                // weights rounded to BF16 values (application)
     PoolBuf G1, G2, m1, v1, m2, v2;    // FP64 gradients and Adam moments
-    PoolBuf act0, hid, z, gz, gh;      // activations [parity][channel][Vh][3] complex
+    PoolBuf act0, hid, z, gz, gh;      // activations [parity][channel][Vh][3] complex (gz: even sites)
     PoolBuf hid16;                     // BF16 hidden activations (application)
-    PoolBuf diff, tmp64, partials, res;
+    PoolBuf diff, tmp64, partials;
+    PoolBuf train, norms;              // training: partial gradient sums, norms of a batch
     int adam_step = 0;
     bool bf_dirty = true;
     int mfma = 0;  // BF16 application layers on the matrix cores: bit 0 the first, bit 1 the second (timed)
@@ -35,15 +36,14 @@ qcdw_status net_ensure(qcdw_net* net)
     const int h = net->hidden;
     HIPCHK(ctx, net->act0.alloc(2L * 4 * Vh * 3 * 8));
     HIPCHK(ctx, net->z.alloc(2L * 4 * Vh * 3 * 8));
-    HIPCHK(ctx, net->gz.alloc(2L * 4 * Vh * 3 * 8));
-    HIPCHK(ctx, net->hid.alloc(2L * h * Vh * 3 * 8));
+    HIPCHK(ctx, net->gz.alloc(4L * Vh * 3 * 8));
     HIPCHK(ctx, net->gh.alloc(2L * h * Vh * 3 * 8));
+    HIPCHK(ctx, net->hid.alloc(2L * h * Vh * 3 * 8));
     HIPCHK(ctx, net->hid16.alloc(2L * h * Vh * 3 * 4));
     HIPCHK(ctx, net->diff.alloc(12L * Vh * 16));
     HIPCHK(ctx, net->tmp64.alloc(12L * Vh * 16));
-    const long nb = (2L * Vh + 255) / 256;
-    HIPCHK(ctx, net->partials.alloc((size_t)std::max<long>(nb * 2 * 4 * h, 3 * 4096) * sizeof(double)));
-    HIPCHK(ctx, net->res.alloc(64 * sizeof(double)));
+    HIPCHK(ctx, net->partials.alloc(MAX_PARTIALS * sizeof(double)));
+    HIPCHK(ctx, net->train.alloc(train_partials(net->op->g, h) * sizeof(double)));
     return QCDW_OK;
 }
 
@@ -134,41 +134,36 @@ qcdw_status net_tune_layers(qcdw_net* net)
     return QCDW_OK;
 }
 
-// one training pair: loss_k = ||P(r) - e||^2 / ||e||^2, gradients accumulated into G1, G2
-qcdw_status net_pair_grad(qcdw_net* net, const void* r_e, const void* e_e, double& loss)
+// sums over n pairs: loss = sum_k ||P(r_k) - e_k||^2 / ||e_k||^2, gradients into G1 and G2.  The host
+// waits once, for the norms; pair(k): the pointers (r_e, e_e) of pair k
+template <class Pair>
+qcdw_status net_batch_grad(qcdw_net* net, int n, Pair&& pair, double& loss)
 {
     qcdw_ctx* ctx = net->ctx;
     hipStream_t s = ctx->stream;
     const Geom& g = net->op->g;
-    const long n = 12L * g.Vh;
-    const int h = net->hidden;
-    double* part = (double*)net->partials.p;
-    double* res = (double*)net->res.p;
-    // forward in FP32, the input embedded on even sites
-    HIPCHK(ctx, launch_pack_spinor(s, F32, g, r_e, 0, net->act0.p, 1.0));
-    HIPCHK(ctx, hipMemsetAsync((char*)net->act0.p + n * 8, 0, n * 8, s));
-    HIPCHK(ctx, launch_net_layer(s, F32, F32, 4, h, net->act0.p, net->hid.p, net->gauge32.p, net->W1.p, g));
-    HIPCHK(ctx, launch_net_layer(s, F32, F32, h, 4, net->hid.p, net->z.p, net->gauge32.p, net->W2.p, g));
-    // diff = P(r) - e on even sites
-    HIPCHK(ctx, launch_pack_spinor(s, F64, g, e_e, 0, net->tmp64.p, 1.0));
-    HIPCHK(ctx, launch_norm2(s, F64, net->tmp64.p, n, part, res));
-    HIPCHK(ctx, launch_xmy_norm2(s, F32, F64, net->z.p, net->tmp64.p, net->diff.p, n, part, res + 1));
-    HIPCHK(ctx, hipMemcpyAsync(ctx->host_d, res, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+    const long len = 12L * g.Vh;
+    HIPCHK(ctx, net->norms.alloc(2UL * n * sizeof(double)));
+    double* norms = (double*)net->norms.p;  // (||e||^2, ||P(r) - e||^2) per pair
+    HIPCHK(ctx, launch_net_adjoint_w(s, net->W2.p, net->Wt.p, 4, net->hidden));
+    const TrainFields f{net->gauge32.p, net->act0.p, net->gz.p, net->hid.p,
+                        net->gh.p,      net->W1.p,   net->W2.p, net->Wt.p, (double*)net->train.p};
+    for (int k = 0; k < n; k++) {
+        const void *r_e, *e_e;
+        pair(k, r_e, e_e);
+        HIPCHK(ctx, launch_pack_spinor(s, F32, g, r_e, 0, net->act0.p, 1.0));
+        HIPCHK(ctx, launch_norm2(s, F64, e_e, len, (double*)net->partials.p, norms + 2 * k));
+        HIPCHK(ctx, launch_train_pair(s, net->hidden, g, f, e_e, norms + 2 * k, norms + 2 * k + 1, k == 0));
+    }
+    HIPCHK(ctx, launch_train_finish(s, net->hidden, g, (double*)net->train.p, net->G1.p, net->G2.p));
+    std::vector<double> h(2 * n);
+    HIPCHK(ctx, hipMemcpyAsync(h.data(), norms, h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
-    const double en = ctx->host_d[0], dn = ctx->host_d[1];
-    if (!(en > 0.0)) return fail(ctx, QCDW_EINVAL, "training pair with a zero error field");
-    loss = dn / en;
-    // gz = 2 (P(r) - e) / ||e||^2 on even sites, 0 on odd sites
-    HIPCHK(ctx, launch_net_make_gz(s, net->diff.p, net->gz.p, n, 2.0 / en));
-    for (int a = 0; a < 9; a++)
-        HIPCHK(ctx, launch_net_wgrad(s, h, 4, net->hid.p, net->gz.p, net->gauge32.p, g, a, part,
-                                     (double*)net->G2.p + (long)a * 2 * 4 * h, 1));
-    // gh = adjoint of layer 2 applied to gz
-    HIPCHK(ctx, launch_net_adjoint_w(s, net->W2.p, net->Wt.p, 4, h));
-    HIPCHK(ctx, launch_net_layer(s, F32, F32, 4, h, net->gz.p, net->gh.p, net->gauge32.p, net->Wt.p, g));
-    for (int a = 0; a < 9; a++)
-        HIPCHK(ctx, launch_net_wgrad(s, 4, h, net->act0.p, net->gh.p, net->gauge32.p, g, a, part,
-                                     (double*)net->G1.p + (long)a * 2 * 4 * h, 1));
+    loss = 0;
+    for (int k = 0; k < n; k++) {
+        if (!(h[2 * k] > 0.0)) return fail(ctx, QCDW_EINVAL, "training pair with a zero error field");
+        loss += h[2 * k + 1] / h[2 * k];
+    }
     return QCDW_OK;
 }
 
@@ -313,14 +308,14 @@ extern "C" qcdw_status qcdw_net_loss_grad(qcdw_net* net, int npairs, const void*
         CHK(check_dev(ctx, e_e[k], "e_e"));
     }
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, hipMemsetAsync(net->G1.p, 0, net->nw1 * 16, s));
-    HIPCHK(ctx, hipMemsetAsync(net->G2.p, 0, net->nw2 * 16, s));
     double L = 0;
-    for (int k = 0; k < npairs; k++) {
-        double lk;
-        CHK(net_pair_grad(net, r_e[k], e_e[k], lk));
-        L += lk;
-    }
+    CHK(net_batch_grad(
+        net, npairs,
+        [&](int k, const void*& r, const void*& e) {
+            r = r_e[k];
+            e = e_e[k];
+        },
+        L));
     HIPCHK(ctx, hipStreamSynchronize(s));
     HIPCHK(ctx, hipMemcpy(g1, net->G1.p, net->nw1 * 16, hipMemcpyDeviceToHost));
     HIPCHK(ctx, hipMemcpy(g2, net->G2.p, net->nw2 * 16, hipMemcpyDeviceToHost));
@@ -347,19 +342,19 @@ extern "C" qcdw_status qcdw_net_train(qcdw_net* net, int npairs, const void* con
     std::shuffle(order.begin(), order.end(), rng);
     int pos = 0;
     for (int step = 0; step < steps; step++) {
-        HIPCHK(ctx, hipMemsetAsync(net->G1.p, 0, net->nw1 * 16, s));
-        HIPCHK(ctx, hipMemsetAsync(net->G2.p, 0, net->nw2 * 16, s));
         double L = 0;
-        for (int b = 0; b < batch; b++) {
-            if (pos == npairs) {
-                std::shuffle(order.begin(), order.end(), rng);
-                pos = 0;
-            }
-            const int k = order[pos++];
-            double lk;
-            CHK(net_pair_grad(net, r_e[k], e_e[k], lk));
-            L += lk;
-        }
+        CHK(net_batch_grad(
+            net, batch,
+            [&](int, const void*& r, const void*& e) {
+                if (pos == npairs) {
+                    std::shuffle(order.begin(), order.end(), rng);
+                    pos = 0;
+                }
+                const int k = order[pos++];
+                r = r_e[k];
+                e = e_e[k];
+            },
+            L));
         net->adam_step++;
         HIPCHK(ctx, launch_adam(s, net->W1.p, (const double*)net->G1.p, (double*)net->m1.p, (double*)net->v1.p,
                                 (int)(2 * net->nw1), lr, 0.9, 0.999, 1e-8, net->adam_step, 1.0 / batch));
