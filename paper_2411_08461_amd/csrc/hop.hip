@@ -66,13 +66,21 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
 
     cx<T> outv[3];
     cx<T> yv[3];
-    if constexpr (EPI == EPI_CLOV_XPAY || EPI == EPI_XPAY_CLOVY || RED == RED_TS) {
+    constexpr bool XPAY = EPI == EPI_CLOV_XPAY || EPI == EPI_CLOV_XPAY_G5CLOV;
+    if constexpr (XPAY || EPI == EPI_XPAY_CLOVY || EPI == EPI_XPAY_G5_SHIFT || RED == RED_TS) {
 #pragma unroll
         for (int c = 0; c < 3; c++) yv[c] = valid ? P::ld(a.y, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
     }
     if constexpr (EPI == EPI_NONE) {
 #pragma unroll
         for (int c = 0; c < 3; c++) outv[c] = res[c];
+    } else if constexpr (EPI == EPI_XPAY_G5_SHIFT) {
+        const T aa = q < 2 ? (T)a.a : -(T)a.a, sh = (T)a.shift;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const cx<T> wv = valid ? P::ld(a.w, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
+            outv[c] = (yv[c] - aa * res[c]) + sh * wv;
+        }
     } else {
         T win[27];
         if constexpr (QCDW_WIN_SHARE != 0) {
@@ -102,6 +110,17 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
             } else {
 #pragma unroll
                 for (int c = 0; c < 3; c++) outv[c] = yv[c] - aa * br[c];
+            }
+            if constexpr (EPI == EPI_CLOV_XPAY_G5CLOV) {
+                cx<T> oo[3], b2[3];
+#pragma unroll
+                for (int c = 0; c < 3; c++) oo[c] = quad_dpp_cx<QUAD_XOR1>(outv[c]);
+                herm_rows<QCDW_CLOV_FMA != 0>(win, q & 1, outv, oo, b2);
+                if (valid) {
+                    const T sg = q < 2 ? T(1) : T(-1);
+#pragma unroll
+                    for (int c = 0; c < 3; c++) P::st(a.out2, sp_idx(q, site, c, Vh), sg * b2[c]);
+                }
             }
         }
     }
@@ -383,6 +402,10 @@ static hipError_t launch_hop_nt(hipStream_t s, int epi, int red, const HopArgs& 
     QCDW_HOP_CASE(EPI_CLOV_XPAY, RED_WDOT)
     QCDW_HOP_CASE(EPI_CLOV_XPAY, RED_TS)
     QCDW_HOP_CASE(EPI_XPAY_CLOVY, RED_NONE)
+    if constexpr (P::cbytes == 16) {
+        QCDW_HOP_CASE(EPI_CLOV_XPAY_G5CLOV, RED_NONE)
+        QCDW_HOP_CASE(EPI_XPAY_G5_SHIFT, RED_WDOT)
+    }
 #undef QCDW_HOP_CASE
 #undef QCDW_TKERNEL
 #undef QCDW_HOP_KERNEL

@@ -20,7 +20,10 @@ enum Epi {
     EPI_NONE = 0,       // out = H psi
     EPI_CLOV = 1,       // out = B (H psi)
     EPI_CLOV_XPAY = 2,  // out = y - a B (H psi)
-    EPI_XPAY_CLOVY = 3  // out = B y - a (H psi)
+    EPI_XPAY_CLOVY = 3,  // out = B y - a (H psi)
+    // the normal operator's (FP64): M_hat with g5 A^-1 of its result, and the adjoint's last hop
+    EPI_CLOV_XPAY_G5CLOV = 4,  // out = y - a B (H psi), out2 = g5 B out
+    EPI_XPAY_G5_SHIFT = 5      // out = y - a g5 (H psi) + shift w
 };
 // hop fused reductions (per-block partials)
 enum Red {
@@ -37,6 +40,8 @@ struct HopArgs {
     const void* y;      // xpay / dot operand on the output parity
     const void* w;      // dot operand on the output parity
     double a;           // xpay coefficient
+    void* out2;         // second output (EPI_CLOV_XPAY_G5CLOV)
+    double shift;       // coefficient of w (EPI_XPAY_G5_SHIFT)
     double* partials;   // [nblocks][3]
     Geom g;
     int parity;

@@ -3,18 +3,23 @@
 // Sec. IV uses RHMC; the multi-shift solver is the part of it that reuses the hot path).
 // Shifted CG as in Jegerlehner (1996): the residuals of all shifted systems are collinear with the
 // base residual, r_i = zeta_i r, and the zeta_i follow a scalar recurrence; every shift costs one
-// axpy pair per iteration, the operator is applied once.  M_hat^+ needs no kernel of its own: with
-// M^+ = g5 M g5 on the full lattice and A commuting with g5, the Schur complement S = A_ee M_hat
-// satisfies S^+ = g5 S g5, so M_hat^+ psi = g5 A_ee M_hat (g5 A_ee^-1 psi).  FP64 throughout; the
-// scalars live on the device (two one-block step kernels per iteration), shifts that have converged
-// drop out of the vector updates, and the host synchronises only to read the done flag.
+// axpy pair per iteration, the operator is applied once.  With M^+ = g5 M g5 on the full lattice and A
+// commuting with g5, M_hat^+ = 1 - kappa^2 g5 H_eo A_oo^-1 H_oe g5 A_ee^-1, so the normal operator is four
+// hops: the second also leaves g5 A_ee^-1 of its result (the clover block is in registers there), the last
+// adds the shift term and forms (p, N p).  Applying A_ee, A_ee^-1, g5, the shift and the dot product as kernels
+// of their own took 43 us of 228 us per iteration at 16^3x32.  FP64 throughout; the scalars live on the device
+// (two one-block step kernels per iteration), shifts that have converged drop out of the vector updates, and
+// the host synchronises only to read the done flag.  The shifted vectors are updated once for the iterations
+// between two reads of the flag, whose residuals are kept, in the order of single updates: 8 shifts at 16^3x32 take
+// 70 us per four iterations instead of 4 x 48.  8 shifts, 132 iterations: 29.6 -> 20.2 ms.
 #include <cstddef>
 
 #include "host.h"
 
 namespace {
 
-constexpr int MS_MAX = 64;  // shifts per solve
+constexpr int MS_MAX = 64;   // shifts per solve
+constexpr int MS_CHECK = 4;  // iterations between two reads of the done flag (and two shifted updates)
 
 // Solver state on the device; wave 0 of the two step kernels owns it, every other kernel reads it.
 struct MsState {
@@ -25,14 +30,18 @@ struct MsState {
     int it, done, status, pad;  // status: 1 breakdown, 2 non-finite residual
     double z[MS_MAX], z_old[MS_MAX], z_new[MS_MAX], d[MS_MAX], res2[MS_MAX];
     int act[MS_MAX];            // shift still iterating
-    double c[4 * MS_MAX + 1];   // per shift [alpha_i, zeta_i', beta_i, active], then beta
+    // per iteration since the last shifted update and shift [alpha_i, zeta_i', beta_i, active]; beta
+    double c[MS_CHECK][4 * MS_MAX];
+    double beta;
 };
 
-// Sum the per-block partials of a dot product over a 256-thread block; every thread gets the sum.
+// Sum the per-block partials of a dot product (STRIDE doubles apart) over a 256-thread block; every thread gets
+// the sum.
+template <int STRIDE = 1>
 __device__ double sum_partials(const double* partials, int nb)
 {
     double v[1] = {0.0};
-    for (int b = threadIdx.x; b < nb; b += 256) v[0] += partials[b];
+    for (int b = threadIdx.x; b < nb; b += 256) v[0] += partials[(long)b * STRIDE];
     __shared__ double tot[1];
     block_sum_store<1>(v, tot);
     __syncthreads();
@@ -56,25 +65,9 @@ __global__ __launch_bounds__(256) void k_ms_total(const double* partials, int nb
     if (threadIdx.x == 0) *out = v;
 }
 
-// w = g5 w + s0 p (g5 negates the elements from `half` on: spins 2 and 3) and the partials of (p, w)
-__global__ __launch_bounds__(256) void k_ms_w_dot(double2* w, const double2* p, long n, long half, double s0,
-                                                  double* partials)
-{
-    double acc[1] = {0.0};
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
-        const double2 pv = p[e];
-        double2 v = w[e];
-        const double sg = e < half ? 1.0 : -1.0;
-        v.x = sg * v.x + s0 * pv.x;
-        v.y = sg * v.y + s0 * pv.y;
-        w[e] = v;
-        acc[0] += pv.x * v.x + pv.y * v.y;
-    }
-    block_sum_store<1>(acc, partials + blockIdx.x);
-}
-
-// r -= alpha w and the partials of (r, r)
-__global__ __launch_bounds__(256) void k_ms_axpy_norm(double2* r, const double2* w, const MsState* st, long n,
+// rn = r - alpha w and the partials of (rn, rn)
+__global__ __launch_bounds__(256) void k_ms_axpy_norm(const double2* __restrict__ r, double2* __restrict__ rn,
+                                                      const double2* __restrict__ w, const MsState* st, long n,
                                                       double* partials)
 {
     const double a = st->a;
@@ -84,7 +77,7 @@ __global__ __launch_bounds__(256) void k_ms_axpy_norm(double2* r, const double2*
         double2 rv = r[e];
         rv.x -= a * wv.x;
         rv.y -= a * wv.y;
-        r[e] = rv;
+        rn[e] = rv;
         acc[0] += rv.x * rv.x + rv.y * rv.y;
     }
     block_sum_store<1>(acc, partials + blockIdx.x);
@@ -94,7 +87,7 @@ __global__ __launch_bounds__(256) void k_ms_axpy_norm(double2* r, const double2*
 // shift relative to the base shift, d_i = sigma_i - sigma_0)
 __global__ __launch_bounds__(256) void k_ms_alpha(MsState* st, const double* partials, int nb, int nshift)
 {
-    const double pw = sum_partials(partials, nb);
+    const double pw = sum_partials<3>(partials, nb);  // the hop's (p, N p)
     const int t = threadIdx.x;
     if (t >= 64) return;
     const int done = st->done;
@@ -122,15 +115,15 @@ __global__ __launch_bounds__(256) void k_ms_alpha(MsState* st, const double* par
 
 // beta = (r', r') / (r, r), the update coefficients of every shift, the shifted residuals |zeta_i'| |r'|;
 // a shift whose residual reaches the stopping value takes this last update and then stays put
-__global__ __launch_bounds__(256) void k_ms_beta(MsState* st, const double* partials, int nb, int nshift)
+__global__ __launch_bounds__(256) void k_ms_beta(MsState* st, const double* partials, int nb, int nshift, int slot)
 {
     const double rn = sum_partials(partials, nb);
     const int t = threadIdx.x;
     if (t >= 64) return;
-    double* c = st->c + 4 * t;
+    double* c = st->c[slot] + 4 * t;
     if (st->done) {
         if (t < nshift) c[0] = c[1] = c[2] = c[3] = 0.0;
-        if (t == 0) st->c[4 * nshift] = 0.0;
+        if (t == 0) st->beta = 0.0;
         return;
     }
     const double a = st->a;
@@ -165,7 +158,7 @@ __global__ __launch_bounds__(256) void k_ms_beta(MsState* st, const double* part
     }
     const unsigned long long any_live = __ballot(live), any_bad = __ballot(bad);
     if (t == 0) {
-        st->c[4 * nshift] = beta;
+        st->beta = beta;
         if (any_bad) {
             st->status = 2;
             st->done = 1;
@@ -179,35 +172,46 @@ __global__ __launch_bounds__(256) void k_ms_beta(MsState* st, const double* part
     }
 }
 
-// All shifted updates of one iteration in one pass, reading each old p_i once:
-//   x_i += alpha_i p_i,  p_i = zeta_i' r + beta_i p_i  (live shifts only),  p = r + beta p.
-// c = [alpha_i, zeta_i', beta_i, active] per shift, then beta; vectors X_i, P_i at stride n (complex).
-__global__ __launch_bounds__(256) void k_shift_update(double2* X, double2* P, double2* p, const double2* r, long n,
-                                                      int nshift, const double* c)
+// p = r + beta p: the base search direction of the next iteration
+__global__ __launch_bounds__(256) void k_ms_p(double2* p, const double2* __restrict__ r, const MsState* st, long n)
 {
-    const double beta = c[4 * nshift];
+    const double beta = st->beta;
     for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
-        const double2 rv = r[e];
-        for (int i = 0; i < nshift; i++) {
-            if (c[4 * i + 3] == 0.0) continue;
-            const double a = c[4 * i], z = c[4 * i + 1], b = c[4 * i + 2];
-            const double2 pv = P[(long)i * n + e];
-            double2 xv = X[(long)i * n + e];
-            xv.x += a * pv.x;
-            xv.y += a * pv.y;
-            X[(long)i * n + e] = xv;
-            P[(long)i * n + e] = make_double2(z * rv.x + b * pv.x, z * rv.y + b * pv.y);
-        }
-        const double2 pb = p[e];
+        const double2 rv = r[e], pb = p[e];
         p[e] = make_double2(rv.x + beta * pb.x, rv.y + beta * pb.y);
     }
 }
 
-// g5 in the internal layout [4 spin][Vh][3]: negate spins 2 and 3 (the second half)
-hipError_t apply_g5(hipStream_t s, void* v, const Geom& g)
+struct MsResiduals {
+    const double2* r[MS_CHECK];  // after each iteration of the group
+};
+
+// The shifted updates of the m iterations of a group in one pass over X_i and P_i (stride n), blockIdx.y = shift i:
+//   x_i += alpha_i p_i,  p_i = zeta_i' r + beta_i p_i  per iteration in which the shift was live.
+__global__ __launch_bounds__(256) void k_shift_update(double2* X, double2* P, MsResiduals R, long n, int m,
+                                                      const MsState* st)
 {
-    void* hi = (char*)v + 6L * g.Vh * 16;
-    return launch_convert(s, F64, F64, hi, hi, 6L * g.Vh, -1.0, nullptr);
+    const int i = blockIdx.y;
+    double c[MS_CHECK][4];
+#pragma unroll
+    for (int k = 0; k < MS_CHECK; k++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) c[k][j] = k < m ? st->c[k][4 * i + j] : 0.0;
+    if (c[0][3] == 0.0) return;  // a shift that was live later in the group was live at its start
+    double2 *x = X + (long)i * n, *p = P + (long)i * n;
+    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
+        double2 xv = x[e], pv = p[e];
+#pragma unroll
+        for (int k = 0; k < MS_CHECK; k++) {
+            if (c[k][3] == 0.0) break;
+            const double2 rv = R.r[k][e];
+            xv.x += c[k][0] * pv.x;
+            xv.y += c[k][0] * pv.y;
+            pv = make_double2(c[k][1] * rv.x + c[k][2] * pv.x, c[k][1] * rv.y + c[k][2] * pv.y);
+        }
+        x[e] = xv;
+        p[e] = pv;
+    }
 }
 
 // r = b - w and the partials of (r, r): the true residual of a shifted system
@@ -242,32 +246,55 @@ struct DrainOnExit {
     ~DrainOnExit() { (void)hipStreamSynchronize(s); }
 };
 
-// Device buffers of one solve (internal layout, n complex each) and the per-block dot partials.
+// Device buffers of one solve (internal layout, n complex each) and the per-block dot partials (3 doubles per hop
+// block: hop partials, or one per vector block).  r[0] is the source and the true residual.
 struct MsBufs {
-    void *r, *p, *w, *t1, *t2, *tmpo;
+    void* r[MS_CHECK + 1];
+    void *p, *w, *t1, *t2, *tmpo;
     double* part;
-    int nb;
+    int nb, nb_hop;
     MsState* st;
 };
 
-// w = (M_hat^+ M_hat + sigma) x with M_hat^+ = g5 A_ee M_hat g5 A_ee^-1; the partials of (x, w) land in
-// B.part.  Uses t1, t2 and tmpo.
+// w = (M_hat^+ M_hat + sigma) x; the partials of (x, w) land in B.part (nb_hop times 3).  Uses t1, t2 and tmpo.
 hipError_t apply_normal(hipStream_t s, const qcdw_op* op, const PrecView& v, const MsBufs& B, const void* x, void* w,
-                        long n, double sigma)
+                        double sigma)
 {
-    const Geom& g = op->g;
-    hipError_t e = matpc(s, op, v, x, B.t1, B.tmpo, RED_NONE, nullptr, nullptr, nullptr);
-    if (e == hipSuccess) e = launch_clov_apply_internal(s, F64, g, op->Ainv64[0].p, B.t1, B.t2);
-    if (e == hipSuccess) e = apply_g5(s, B.t2, g);
-    if (e == hipSuccess) e = matpc(s, op, v, B.t2, B.t1, B.tmpo, RED_NONE, nullptr, nullptr, nullptr);
-    if (e == hipSuccess) e = launch_clov_apply_internal(s, F64, g, op->A64[0].p, B.t1, w);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ms_w_dot, dim3(B.nb), dim3(256), 0, s, (double2*)w, (const double2*)x, n, 6L * g.Vh, sigma,
-                       B.part);
-    return hipGetLastError();
+    HopArgs o = hop_args(op->g, 1);  // into odd sites: A_oo^-1 H_oe
+    o.nt = op->hop_nt[F64];
+    o.cgroup = op->hop_cg[F64];
+    o.fma = op->hop_fma[F64];
+    o.gauge = v.gauge;
+    o.clov = v.Ainv[1];
+    o.out = B.tmpo;
+    HopArgs e = o;  // into even sites
+    e.parity = 0;
+    e.clov = v.Ainv[0];
+    e.psi = B.tmpo;
+    e.a = op->kappa * op->kappa;
+    // t1 = M_hat x, t2 = g5 A_ee^-1 t1
+    o.psi = x;
+    hipError_t r = launch_hop(s, F64, v.recon, EPI_CLOV, RED_NONE, o);
+    if (r != hipSuccess) return r;
+    HopArgs m = e;
+    m.y = x;
+    m.out = B.t1;
+    m.out2 = B.t2;
+    r = launch_hop(s, F64, v.recon, EPI_CLOV_XPAY_G5CLOV, RED_NONE, m);
+    if (r != hipSuccess) return r;
+    // w = t1 - kappa^2 g5 H_eo A_oo^-1 H_oe t2 + sigma x
+    o.psi = B.t2;
+    r = launch_hop(s, F64, v.recon, EPI_CLOV, RED_NONE, o);
+    if (r != hipSuccess) return r;
+    e.y = B.t1;
+    e.w = x;
+    e.shift = sigma;
+    e.out = w;
+    e.partials = B.part;
+    return launch_hop(s, F64, v.recon, EPI_XPAY_G5_SHIFT, RED_WDOT, e);
 }
 
-// Shifted CG from x_i = 0 on the source held in B.r (overwritten), for ns shifts, solutions into X
+// Shifted CG from x_i = 0 on the source held in B.r[0] (overwritten), for ns shifts, solutions into X
 // (ns fields at stride n) with search directions in P.  Runs until every shifted residual tracked by
 // the recurrence is <= sqrt(stop2), or maxiter iterations; h returns the final state.
 qcdw_status ms_cg(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B, void* X, void* P, long n, int ns,
@@ -277,13 +304,13 @@ qcdw_status ms_cg(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B
     const size_t vb = (size_t)n * 16;
     double s0 = shifts[0];
     for (int i = 1; i < ns; i++) s0 = std::min(s0, shifts[i]);
-    HIPCHK(ctx, launch_convert(s, F64, F64, B.r, B.p, n, 1.0, nullptr));
+    HIPCHK(ctx, launch_convert(s, F64, F64, B.r[0], B.p, n, 1.0, nullptr));
     for (int i = 0; i < ns; i++) {
-        HIPCHK(ctx, launch_convert(s, F64, F64, B.r, (char*)P + i * vb, n, 1.0, nullptr));
+        HIPCHK(ctx, launch_convert(s, F64, F64, B.r[0], (char*)P + i * vb, n, 1.0, nullptr));
         HIPCHK(ctx, hipMemsetAsync((char*)X + i * vb, 0, vb, s));
     }
     double* hd = ctx->host_d;  // pinned
-    hipLaunchKernelGGL(k_ms_norm, dim3(B.nb), dim3(256), 0, s, (const double2*)B.r, n, B.part);
+    hipLaunchKernelGGL(k_ms_norm, dim3(B.nb), dim3(256), 0, s, (const double2*)B.r[0], n, B.part);
     hipLaunchKernelGGL(k_ms_total, dim3(1), dim3(256), 0, s, (const double*)B.part, B.nb, (double*)B.t1);
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipMemcpyAsync(hd, B.t1, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -304,23 +331,31 @@ qcdw_status ms_cg(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B
     MsState* st = B.st;
     HIPCHK(ctx, hipMemcpyAsync(st, &h, sizeof(MsState), hipMemcpyHostToDevice, s));
     // The scalars stay on the device: the host enqueues iterations and reads the done flag every
-    // CHECK iterations; iterations enqueued after convergence change nothing (alpha = 0, no live shift).
-    constexpr int CHECK = 4;
+    // MS_CHECK iterations; iterations enqueued after convergence change nothing (alpha = 0, no live shift).
     const size_t flags_off = offsetof(MsState, it);
-    for (int k = 0; k < maxiter && !h.done; k++) {
-        HIPCHK(ctx, apply_normal(s, op, v, B, B.p, B.w, n, s0));
-        hipLaunchKernelGGL(k_ms_alpha, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb, ns);
-        hipLaunchKernelGGL(k_ms_axpy_norm, dim3(B.nb), dim3(256), 0, s, (double2*)B.r, (const double2*)B.w,
-                           (const MsState*)st, n, B.part);
-        hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb, ns);
-        hipLaunchKernelGGL(k_shift_update, dim3(B.nb), dim3(256), 0, s, (double2*)X, (double2*)P, (double2*)B.p,
-                           (const double2*)B.r, n, ns, (const double*)st->c);
-        HIPCHK(ctx, hipGetLastError());
-        if ((k + 1) % CHECK == 0 || k + 1 == maxiter) {
-            HIPCHK(ctx, hipMemcpyAsync(hd, (char*)st + flags_off, 4 * sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(ctx, hipStreamSynchronize(s));
-            std::memcpy(&h.it, hd, 4 * sizeof(int));
+    int at = 0;  // the buffer of the current residual
+    for (int k = 0; k < maxiter && !h.done;) {
+        const int m = std::min(MS_CHECK, maxiter - k);
+        MsResiduals R{};
+        for (int j = 0; j < m; j++) {
+            HIPCHK(ctx, apply_normal(s, op, v, B, B.p, B.w, s0));
+            hipLaunchKernelGGL(k_ms_alpha, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb_hop, ns);
+            const int next = (at + 1) % (MS_CHECK + 1);
+            hipLaunchKernelGGL(k_ms_axpy_norm, dim3(B.nb), dim3(256), 0, s, (const double2*)B.r[at],
+                               (double2*)B.r[next], (const double2*)B.w, (const MsState*)st, n, B.part);
+            at = next;
+            R.r[j] = (const double2*)B.r[at];
+            hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb, ns, j);
+            hipLaunchKernelGGL(k_ms_p, dim3(B.nb), dim3(256), 0, s, (double2*)B.p, (const double2*)B.r[at],
+                               (const MsState*)st, n);
         }
+        hipLaunchKernelGGL(k_shift_update, dim3(B.nb, ns), dim3(256), 0, s, (double2*)X, (double2*)P, R, n, m,
+                           (const MsState*)st);
+        HIPCHK(ctx, hipGetLastError());
+        HIPCHK(ctx, hipMemcpyAsync(hd, (char*)st + flags_off, 4 * sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(ctx, hipStreamSynchronize(s));
+        std::memcpy(&h.it, hd, 4 * sizeof(int));
+        k += m;
     }
     HIPCHK(ctx, hipMemcpyAsync(&h, st, sizeof(MsState), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
@@ -329,13 +364,13 @@ qcdw_status ms_cg(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B
     return QCDW_OK;
 }
 
-// ||b - (N + sigma) x||^2 on the GPU in FP64 (b, x internal layout); the residual itself is left in B.r.
+// ||b - (N + sigma) x||^2 on the GPU in FP64 (b, x internal layout); the residual itself is left in B.r[0].
 qcdw_status true_res2(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B, const void* bint, const void* x,
                       long n, double sigma, double& r2)
 {
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, apply_normal(s, op, v, B, x, B.w, n, sigma));
-    hipLaunchKernelGGL(k_ms_resid, dim3(B.nb), dim3(256), 0, s, (double2*)B.r, (const double2*)bint,
+    HIPCHK(ctx, apply_normal(s, op, v, B, x, B.w, sigma));
+    hipLaunchKernelGGL(k_ms_resid, dim3(B.nb), dim3(256), 0, s, (double2*)B.r[0], (const double2*)bint,
                        (const double2*)B.w, n, B.part);
     hipLaunchKernelGGL(k_ms_total, dim3(1), dim3(256), 0, s, (const double*)B.part, B.nb, (double*)B.t1);
     HIPCHK(ctx, hipGetLastError());
@@ -370,22 +405,34 @@ extern "C" qcdw_status qcdw_invert_multishift(qcdw_op* op, const void* b_e, void
     const PrecView v = view(op, F64);
     hipStream_t s = ctx->stream;
     const int nb = blas_blocks(n);
-    // r, p, w, t1, t2, tmp_o, the packed b, a refinement's correction and direction, then X_i, P_i;
-    // the partials of one dot product; the solver state
+    // the residuals of a group, p, w, t1, t2, tmp_o, the packed b, a refinement's correction and direction, then
+    // X_i, P_i; the partials of one dot product; the solver state
+    constexpr int NR = MS_CHECK + 1, FIXED = NR + 8;
+    const int nb_hop = hop_blocks_nt(g, op->hop_nt[F64], op->hop_cg[F64]);
     PoolBuf buf, part, state;
-    HIPCHK(ctx, buf.alloc(vb * (9 + 2 * (size_t)n_shifts)));
-    HIPCHK(ctx, part.alloc((size_t)nb * sizeof(double)));
+    HIPCHK(ctx, buf.alloc(vb * (FIXED + 2 * (size_t)n_shifts)));
+    HIPCHK(ctx, part.alloc((size_t)std::max(nb, 3 * nb_hop) * sizeof(double)));
     HIPCHK(ctx, state.alloc(sizeof(MsState)));
     DrainOnExit drain{s};
     char* base = (char*)buf.p;
-    MsBufs B{base, base + vb, base + 2 * vb, base + 3 * vb, base + 4 * vb, base + 5 * vb, (double*)part.p, nb,
-             (MsState*)state.p};
-    void *bint = base + 6 * vb, *xc = base + 7 * vb, *pc = base + 8 * vb;
-    auto X = [&](int i) { return (void*)(base + (9 + i) * vb); };
-    auto P = [&](int i) { return (void*)(base + (9 + n_shifts + i) * vb); };
+    auto field = [&](int i) { return (void*)(base + i * vb); };
+    MsBufs B{};
+    for (int i = 0; i < NR; i++) B.r[i] = field(i);
+    B.p = field(NR);
+    B.w = field(NR + 1);
+    B.t1 = field(NR + 2);
+    B.t2 = field(NR + 3);
+    B.tmpo = field(NR + 4);
+    B.part = (double*)part.p;
+    B.nb = nb;
+    B.nb_hop = nb_hop;
+    B.st = (MsState*)state.p;
+    void *bint = field(NR + 5), *xc = field(NR + 6), *pc = field(NR + 7);
+    auto X = [&](int i) { return field(FIXED + i); };
+    auto P = [&](int i) { return field(FIXED + n_shifts + i); };
 
     HIPCHK(ctx, launch_pack_spinor(s, F64, g, b_e, 0, bint, 1.0));
-    HIPCHK(ctx, launch_convert(s, F64, F64, bint, B.r, n, 1.0, nullptr));
+    HIPCHK(ctx, launch_convert(s, F64, F64, bint, B.r[0], n, 1.0, nullptr));
     // The recurrence runs to half the tolerance, so that the true residuals (which drift from the
     // recurrence's by rounding) normally pass without refinement.
     MsState h;
