@@ -492,7 +492,15 @@ qcdw_status qcdw_host::fgmres_run(qcdw_op* op, const Precond* precond, const voi
     hipStream_t s = ctx->stream;
     const PrecView v64 = view(op, F64);
 
-    DevBuf be, bo, yo, ye, bhat, xe, xo, r, w, tmp, tmpo, V, Z, part, coef, dres;
+    // from the block cache (sixteen allocations and their releases each solve), except bases that are too
+    // large to be held after the solve; the stream is drained before the blocks go back
+    PoolBuf be, bo, yo, ye, bhat, xe, xo, r, w, tmp, tmpo, part, coef, dres;
+    DevBuf V, Z;
+    V.pooled = Z.pooled = vb * (m + 1) <= (size_t)4 << 30;
+    struct Drain {
+        hipStream_t s;
+        ~Drain() { (void)hipStreamSynchronize(s); }
+    } drain{s};
     HIPCHK(ctx, be.alloc(vb));
     HIPCHK(ctx, bo.alloc(vb));
     HIPCHK(ctx, yo.alloc(vb));

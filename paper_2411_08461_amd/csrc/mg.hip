@@ -26,6 +26,17 @@
 
 namespace qcdw {
 
+// Storage of the coarse stencil in the preconditioner's coarse solve (QCDW_MG_YPREC: 0 FP32, 1 BF16,
+// 2 FP16) and the smoother's precision (QCDW_MG_SMOOTH_F64 = 1: FP64, else the operator's inner one).
+#ifndef QCDW_MG_YPREC
+#define QCDW_MG_YPREC 1
+#endif
+#ifndef QCDW_MG_SMOOTH_F64
+#define QCDW_MG_SMOOTH_F64 0
+#endif
+using MG_YP = std::conditional_t<QCDW_MG_YPREC == 0, P32, std::conditional_t<QCDW_MG_YPREC == 1, PBF16, PF16>>;
+constexpr int MG_YPREC = QCDW_MG_YPREC == 0 ? F32 : QCDW_MG_YPREC == 1 ? BF16 : F16;
+
 struct MgDev {
     Geom g;
     int Lc[4], b[4];
@@ -378,9 +389,10 @@ __global__ __launch_bounds__(256) void k_mg_restrict(MgDev m, const void* W, con
 
 // f_p = scale * sum_k W_k e[chi][k] on the sites of parity p < np (scale = sqrt(*norm2) when norm2 is
 // given, else 1); one block per coarse site, the block's coarse vector staged in LDS
-template <class PW, class PE, class PF>
+// lo: a copy of the even sites in storage precision PL (nullptr: none)
+template <class PW, class PE, class PF, class PL>
 __global__ __launch_bounds__(256) void k_mg_prolong(MgDev m, const void* W, const void* e, const double* norm2,
-                                                     void* f0, void* f1, int np)
+                                                     void* f0, void* f1, int np, void* lo)
 {
     __shared__ cx<double> ec[2 * MG_MAX_N];
     const int cs = blockIdx.x;
@@ -402,22 +414,19 @@ __global__ __launch_bounds__(256) void k_mg_prolong(MgDev m, const void* W, cons
             acc = acc + cx<double>{(double)wk.re, (double)wk.im} * ec[chi * m.N + k];
         }
         const int site = m.blk_sites[((long)cs * 2 + p) * m.hb + j];
-        PF::st(p == 0 ? f0 : f1, sp_idx(sc / 3, site, sc % 3, m.g.Vh), cx<T>{(T)acc.re, (T)acc.im});
+        const long at = sp_idx(sc / 3, site, sc % 3, m.g.Vh);
+        PF::st(p == 0 ? f0 : f1, at, cx<T>{(T)acc.re, (T)acc.im});
+        using TL = typename PL::real;
+        if (lo && p == 0) PL::st(lo, at, cx<TL>{(TL)acc.re, (TL)acc.im});
     }
 }
 
-// out = D_c in, one block per coarse site: thread items (stencil entry d, row) form the partial sums over the
+// out = D_c in, FP64, one block per coarse site: thread items (stencil entry d, row) form the partial sums over the
 // columns of entry d (consecutive threads read consecutive rows of a column), which are then summed over d in
-// a fixed order; red = RED_WDOT: partials of (w, out); RED_TS: partials of (out, y) and ||out||^2 (one
-// partial per coarse site); nothing when *stop != 0 (the solve has finished)
-// (PY: storage of the stencil, P: of the vectors)
-template <class PY, class P, int RED>
-__global__ __launch_bounds__(256) void k_mg_coarse_apply(MgDev m, const void* Yt, const void* in, void* out,
-                                                          const void* y, double* partials, const int* stop)
+// a fixed order
+__global__ __launch_bounds__(256) void k_mg_coarse_apply(MgDev m, const void* Yt, const void* in, void* out)
 {
-    if (stop && *stop) return;
-    using T = typename P::real;
-    __shared__ cx<T> part[9][2 * MG_MAX_N];
+    __shared__ cx<double> part[9][2 * MG_MAX_N];
     const int nc = m.nc, cs = blockIdx.x;
     const long ne = (long)nc * nc;
     for (int it = threadIdx.x; it < 9 * nc; it += 256) {
@@ -425,40 +434,17 @@ __global__ __launch_bounds__(256) void k_mg_coarse_apply(MgDev m, const void* Yt
         const int nb = d == 0 ? cs : m.cnbr[(long)cs * 8 + (d - 1)];
         const long yb = ((long)cs * 9 + d) * ne + row;
         const long ib = (long)nb * nc;
-        cx<T> acc = {T(0), T(0)};
-        for (int col = 0; col < nc; col++) {
-            const auto yv = PY::ld(Yt, yb + (long)col * nc);
-            cmac(acc, cx<T>{(T)yv.re, (T)yv.im}, P::ld(in, ib + col));
-        }
+        cx<double> acc = {0.0, 0.0};
+        for (int col = 0; col < nc; col++) cmac(acc, P64::ld(Yt, yb + (long)col * nc), P64::ld(in, ib + col));
         part[d][row] = acc;
     }
     __syncthreads();
     const int row = threadIdx.x;
-    const bool valid = row < nc;
-    const long tid = (long)cs * nc + row;
-    cx<T> acc = {T(0), T(0)};
-    if (valid) {
-        acc = part[0][row];
+    if (row < nc) {
+        cx<double> acc = part[0][row];
 #pragma unroll
         for (int d = 1; d < 9; d++) acc = acc + part[d][row];
-        P::st(out, tid, acc);
-    }
-    if constexpr (RED != RED_NONE) {
-        double v[3] = {0.0, 0.0, 0.0};
-        if (valid) {
-            const cx<T> o = P::rt(acc);
-            if constexpr (RED == RED_WDOT) {
-                const cx<T> w = P::ld(y, tid);
-                v[0] = (double)w.re * o.re + (double)w.im * o.im;
-                v[1] = (double)w.re * o.im - (double)w.im * o.re;
-            } else {
-                const cx<T> yv = P::ld(y, tid);
-                v[0] = (double)o.re * yv.re + (double)o.im * yv.im;
-                v[1] = (double)o.re * yv.im - (double)o.im * yv.re;
-                v[2] = (double)o.re * o.re + (double)o.im * o.im;
-            }
-        }
-        block_sum_store<3>(v, partials + 3L * blockIdx.x);
+        P64::st(out, (long)cs * nc + row, acc);
     }
 }
 
@@ -473,39 +459,319 @@ __global__ void k_mg_transpose(const double2* __restrict__ in, double2* out, lon
     out[blk * ne + (long)c * nc + r] = in[e];
 }
 
-// coarse solve set-up: scale = 1 / ||r_c|| (0 for a zero right-hand side), BiCGStab stops below tol^2
-__global__ void k_mg_coarse_init(Scal* S, const double* norm2, double tol2, double* scale)
-{
-    const double n2 = *norm2;
-    const bool zero = !(n2 > 0.0);
-    *scale = zero ? 0.0 : 1.0 / sqrt(n2);
-    S->stop_rr = zero ? 1.0 : tol2;
-    S->iter = 0;
-    S->flags = 0;
-    S->fault_iter = 0;
-    S->hist_len = 0;
-    S->hist_norm = 1.0;
-}
+// ---------------------------------------------------------------------------
+// coarse solve: BiCGStab (van der Vorst 1992) on D_c e = r_c / ||r_c|| with FP32 vectors, FP64 scalars, two
+// launches per iteration.
+//
+//   A(i): omega, beta and the residual norm from B(i-1)'s sums; x += alpha p + omega s, r = s - omega t,
+//         p' = r + beta (p - omega v), v' = D_c p'; sums of (r0, v')
+//   B(i): alpha; s = r - alpha v, t = D_c s; sums of (t, s), ||t||^2, ||s||^2, (r0, s), (r0, t)
+//
+// A block takes one coarse site.  It forms the input of its product (p' or s) for the site and its eight
+// neighbours itself, from the vectors of the last launch, so no launch waits for a vector that another has to
+// finish; each vector is written by its own site's block, p and v in two copies in turn because the neighbours
+// read the old ones.  (r0, r) and ||r||^2 of the new residual follow from B's sums: (r0, s) - omega (r0, t) and
+// ||s||^2 - |(t, s)|^2 / ||t||^2.  Every block sums the partials of the launch before in the same order; with
+// many coarse sites (MG_FUSE) a single-block launch does it instead.  The scalars of an iteration have a slot
+// of their own, written in one launch and read in later ones.
+// At 12 288 unknowns (16^3x32, 4^4 blocks, N = 12) an iteration was eight launches (the two products, three scalar
+// kernels and three vector updates) of 1.5-3 us each, issued one by one at 5 us; it is two of 3.5 us from one graph.
+// Loading the stencil row and the vectors ahead of the sums was slower (4.7 us: more registers per wave, and the
+// launches after the solve's end, which return at once, then load too).
+// ---------------------------------------------------------------------------
+struct CoarseSlot {
+    double rho[2], alpha[2], omega[2], beta[2];
+    double rr;
+    int stop_a, stop_b;  // the solve has ended before B(i) / after it without an update
+};
+struct CoarseSolve {
+    MgDev m;
+    const void* Yt;
+    const double2* rc;           // right-hand side, FP64
+    const double* norm2;         // ||rc||^2
+    float2 *x, *r, *r0, *s, *t, *p[2], *v[2];
+    CoarseSlot* slot;            // one per iteration
+    double *pa, *pb;             // partials of A (3 of 8) and B, 8 per coarse site; their totals after the last site's
+    double tol2;
+};
 
-// minimal-residual step: partials of (w, r) and ||w||^2 (vectors in storage precision P)
-template <class P>
-__global__ __launch_bounds__(256) void k_mg_mr_dots(const void* w, const void* r, long n, double* partials)
+__device__ __forceinline__ cx<float> ldf(const float2* p, long k) { return {p[k].x, p[k].y}; }
+__device__ __forceinline__ void stf(float2* p, long k, cx<float> v) { p[k] = make_float2(v.re, v.im); }
+
+// Sums of 8 values per coarse site (A writes 3 of them), in every thread: thread t adds up value t % 8 of every 32nd
+// site, then the block's 32 threads of a value are summed in a fixed order.  !FUSED: already added up by a launch
+// of its own.
+template <bool FUSED>
+__device__ __forceinline__ void coarse_sum(const double* partials, int n, double (&v)[8])
 {
-    double v[3] = {0.0, 0.0, 0.0};
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
-        const auto a = P::ld(w, e), b = P::ld(r, e);
-        v[0] += (double)a.re * b.re + (double)a.im * b.im;
-        v[1] += (double)a.re * b.im - (double)a.im * b.re;
-        v[2] += (double)a.re * a.re + (double)a.im * a.im;
+    if constexpr (FUSED) {
+        __shared__ double red[4][8];
+        double part = 0.0;
+#pragma unroll 4
+        for (int b = threadIdx.x >> 3; b < n; b += 32) part += partials[8L * b + (threadIdx.x & 7)];
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) part += __shfl_xor(part, off, 64);
+        if ((threadIdx.x & 63) < 8) red[threadIdx.x >> 6][threadIdx.x & 7] = part;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = partials[8L * n + k];
     }
-    block_sum_store<3>(v, partials + 3L * blockIdx.x);
 }
 
-// alpha = (w, r) / (w, w) from nb partials (every block sums them in the same order), z += alpha r (z in
-// PZ), r -= alpha w (r, w in P)
-template <class P, class PZ>
-__global__ __launch_bounds__(256) void k_mg_mr_update(void* z, void* r, const void* w, long n, const double* partials,
-                                                      int nb)
+__global__ __launch_bounds__(256) void k_mg_coarse_total(double* partials, int n)
+{
+    double v[8];
+    coarse_sum<true>(partials, n, v);
+    if (threadIdx.x < 8) partials[8L * n + threadIdx.x] = v[threadIdx.x];
+}
+
+// K values of the threads below nc (<= 64, one wave) summed into out
+template <int K>
+__device__ __forceinline__ void coarse_sum_store(double (&v)[K], double* out)
+{
+    if (threadIdx.x >= 64) return;
+#pragma unroll
+    for (int k = 0; k < K; k++) v[k] = wave_sum(v[k]);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < K; k++) out[k] = v[k];
+    }
+}
+
+// r = r0 = p = rc / ||rc|| (zero for a zero right-hand side), x = 0
+__global__ __launch_bounds__(256) void k_mg_coarse_start(CoarseSolve c, long n)
+{
+    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= n) return;
+    const double n2 = *c.norm2, sc = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+    const float2 v = make_float2((float)(sc * c.rc[e].x), (float)(sc * c.rc[e].y));
+    c.r[e] = c.r0[e] = c.p[0][e] = v;
+    c.x[e] = make_float2(0.f, 0.f);
+}
+
+// rows of D_c times the vector in LDS (in[0]: this site, in[1 + d]: its neighbours); thread `row` < nc gets its row
+__device__ __forceinline__ cx<float> coarse_rows(const MgDev& m, const void* Yt, int cs,
+                                                 const cx<float> (&in)[9][2 * MG_MAX_N],
+                                                 cx<float> (&part)[9][2 * MG_MAX_N])
+{
+    const int nc = m.nc;
+    const long ne = (long)nc * nc;
+    for (int it = threadIdx.x; it < 9 * nc; it += 256) {
+        const int d = it / nc, row = it - d * nc;
+        const long yb = ((long)cs * 9 + d) * ne + row;
+        cx<float> acc = {0.f, 0.f};
+#pragma unroll 8
+        for (int col = 0; col < nc; col++) cmac(acc, MG_YP::ld(Yt, yb + (long)col * nc), in[d][col]);
+        part[d][row] = acc;
+    }
+    __syncthreads();
+    cx<float> acc = {0.f, 0.f};
+    if ((int)threadIdx.x < nc) {
+        acc = part[0][threadIdx.x];
+#pragma unroll
+        for (int d = 1; d < 9; d++) acc = acc + part[d][threadIdx.x];
+    }
+    return acc;
+}
+
+__device__ __forceinline__ cx<double> cdiv(cx<double> a, cx<double> b)
+{
+    const double d = b.re * b.re + b.im * b.im;
+    return {(a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d};
+}
+__device__ __forceinline__ double cabs2(cx<double> a) { return a.re * a.re + a.im * a.im; }
+
+// What follows B(it-1): omega, the new rho and ||r||^2, beta.  upd: x and r take their update; stop: the solve ends
+// (converged, broken down or not finite).
+struct CoarseStep {
+    cx<double> omega, rho, beta;
+    double rr;
+    bool upd, stop;
+};
+__device__ __forceinline__ CoarseStep coarse_step(const CoarseSlot& q, const double (&v)[8], double tol2, double n2)
+{
+    CoarseStep o{};
+    const double tt = v[2];
+    o.stop = true;
+    bool fin = true;
+#pragma unroll
+    for (int k = 0; k < 8; k++) fin = fin && isfinite(v[k]);
+    if (!fin) return o;
+    o.upd = true;
+    if (tt != 0.0) o.omega = {v[0] / tt, v[1] / tt};
+    o.rho = cx<double>{v[4], v[5]} - o.omega * cx<double>{v[6], v[7]};
+    const double rr = v[3] - (v[0] * v[0] + v[1] * v[1]) / (tt != 0.0 ? tt : 1.0);
+    o.rr = rr > 0.0 ? rr : 0.0;
+    if (o.rr <= (n2 > 0.0 ? tol2 : 1.0)) return o;
+    if (cabs2(o.omega) == 0.0 || sqrt(cabs2(o.rho)) <= 1e-30 * sqrt(o.rr)) return o;
+    o.beta = cdiv(o.rho, {q.rho[0], q.rho[1]}) * cdiv({q.alpha[0], q.alpha[1]}, o.omega);
+    o.stop = false;
+    return o;
+}
+
+template <bool FUSED>
+__global__ __launch_bounds__(256) void k_mg_coarse_a(CoarseSolve c, int it)
+{
+    __shared__ cx<float> in[9][2 * MG_MAX_N], part[9][2 * MG_MAX_N];
+    const MgDev& m = c.m;
+    const int nc = m.nc, cs = blockIdx.x;
+    const float2 *p = c.p[(it + 1) & 1], *v = c.v[(it + 1) & 1];  // of iteration it - 1
+    float2 *pn = c.p[it & 1], *vn = c.v[it & 1];
+    CoarseStep st{};
+    if (it > 0) {
+        const CoarseSlot q = c.slot[it - 1];
+        const bool ended = q.stop_a || q.stop_b;
+        if (!ended) {
+            double sums[8];
+            coarse_sum<FUSED>(c.pb, m.Vc, sums);
+            st = coarse_step(q, sums, c.tol2, *c.norm2);
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            CoarseSlot o{};
+            o.rho[0] = st.rho.re;
+            o.rho[1] = st.rho.im;
+            o.omega[0] = st.omega.re;
+            o.omega[1] = st.omega.im;
+            o.rr = st.rr;
+            o.stop_a = ended || st.stop;
+            c.slot[it] = o;
+        }
+        if (ended) return;
+        const cx<float> om = {(float)st.omega.re, (float)st.omega.im}, al = {(float)q.alpha[0], (float)q.alpha[1]},
+                        be = {(float)st.beta.re, (float)st.beta.im};
+        if (st.upd && (int)threadIdx.x < nc) {
+            const long e = (long)cs * nc + threadIdx.x;
+            const cx<float> sv = ldf(c.s, e);
+            stf(c.x, e, ldf(c.x, e) + al * ldf(p, e) + om * sv);
+            stf(c.r, e, sv - om * ldf(c.t, e));
+        }
+        if (st.stop) return;
+        for (int k = threadIdx.x; k < 9 * nc; k += 256) {
+            const int d = k / nc, i = k - d * nc;
+            const long e = (long)(d == 0 ? cs : m.cnbr[(long)cs * 8 + (d - 1)]) * nc + i;
+            const cx<float> pv = (ldf(c.s, e) - om * ldf(c.t, e)) + be * (ldf(p, e) - om * ldf(v, e));
+            in[d][i] = pv;
+            if (d == 0) stf(pn, e, pv);
+        }
+    } else {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            CoarseSlot o{};
+            o.stop_a = !(*c.norm2 > 0.0);
+            c.slot[0] = o;
+        }
+        for (int k = threadIdx.x; k < 9 * nc; k += 256) {
+            const int d = k / nc, i = k - d * nc;
+            in[d][i] = ldf(pn, (long)(d == 0 ? cs : m.cnbr[(long)cs * 8 + (d - 1)]) * nc + i);
+        }
+    }
+    __syncthreads();
+    const cx<float> o = coarse_rows(m, c.Yt, cs, in, part);
+    double sum[3] = {0.0, 0.0, 0.0};
+    if ((int)threadIdx.x < nc) {
+        const long e = (long)cs * nc + threadIdx.x;
+        stf(vn, e, o);
+        const cx<float> w = ldf(c.r0, e);
+        sum[0] = (double)w.re * o.re + (double)w.im * o.im;
+        sum[1] = (double)w.re * o.im - (double)w.im * o.re;
+        sum[2] = (double)w.re * w.re + (double)w.im * w.im;  // rho of the first iteration
+    }
+    coarse_sum_store<3>(sum, c.pa + 8L * cs);
+}
+
+template <bool FUSED>
+__global__ __launch_bounds__(256) void k_mg_coarse_b(CoarseSolve c, int it)
+{
+    __shared__ cx<float> in[9][2 * MG_MAX_N], part[9][2 * MG_MAX_N];
+    const MgDev& m = c.m;
+    const int nc = m.nc, cs = blockIdx.x;
+    CoarseSlot* slot = c.slot + it;
+    if (slot->stop_a) return;
+    double a[8];
+    coarse_sum<FUSED>(c.pa, m.Vc, a);
+    const cx<double> rv = {a[0], a[1]};
+    // rho and ||r||^2: recorded by A(it), or those of r0 in the first iteration
+    const cx<double> rho = it == 0 ? cx<double>{a[2], 0.0} : cx<double>{slot->rho[0], slot->rho[1]};
+    const double rr = it == 0 ? a[2] : slot->rr, arv = sqrt(cabs2(rv));
+    const bool bad = !isfinite(arv) || arv <= 1e-30 * sqrt(a[2] * rr);
+    const cx<double> alpha = bad ? cx<double>{0.0, 0.0} : cdiv(rho, rv);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {  // fields that no block reads in this launch (it > 0: rho is left)
+        slot->alpha[0] = alpha.re;
+        slot->alpha[1] = alpha.im;
+        if (it == 0) {
+            slot->rho[0] = rho.re;
+            slot->rho[1] = 0.0;
+        }
+        slot->stop_b = bad;
+    }
+    if (bad) return;
+    const cx<float> al = {(float)alpha.re, (float)alpha.im};
+    const float2* v = c.v[it & 1];
+    for (int k = threadIdx.x; k < 9 * nc; k += 256) {
+        const int d = k / nc, i = k - d * nc;
+        const long e = (long)(d == 0 ? cs : m.cnbr[(long)cs * 8 + (d - 1)]) * nc + i;
+        const cx<float> sv = ldf(c.r, e) - al * ldf(v, e);
+        in[d][i] = sv;
+        if (d == 0) stf(c.s, e, sv);
+    }
+    __syncthreads();
+    const cx<float> o = coarse_rows(m, c.Yt, cs, in, part);
+    double sum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if ((int)threadIdx.x < nc) {
+        const long e = (long)cs * nc + threadIdx.x;
+        stf(c.t, e, o);
+        const cx<float> y = in[0][threadIdx.x], w = ldf(c.r0, e);
+        sum[0] = (double)o.re * y.re + (double)o.im * y.im;
+        sum[1] = (double)o.re * y.im - (double)o.im * y.re;
+        sum[2] = (double)o.re * o.re + (double)o.im * o.im;
+        sum[3] = (double)y.re * y.re + (double)y.im * y.im;
+        sum[4] = (double)w.re * y.re + (double)w.im * y.im;
+        sum[5] = (double)w.re * y.im - (double)w.im * y.re;
+        sum[6] = (double)w.re * o.re + (double)w.im * o.im;
+        sum[7] = (double)w.re * o.im - (double)w.im * o.re;
+    }
+    coarse_sum_store<8>(sum, c.pb + 8L * cs);
+}
+
+// the update of x that the last iteration n - 1 still owes
+template <bool FUSED>
+__global__ __launch_bounds__(256) void k_mg_coarse_end(CoarseSolve c, int n)
+{
+    const CoarseSlot q = c.slot[n - 1];
+    if (q.stop_a || q.stop_b) return;
+    double sums[8];
+    coarse_sum<FUSED>(c.pb, c.m.Vc, sums);
+    const CoarseStep st = coarse_step(q, sums, c.tol2, *c.norm2);
+    if (!st.upd) return;
+    const cx<float> om = {(float)st.omega.re, (float)st.omega.im}, al = {(float)q.alpha[0], (float)q.alpha[1]};
+    const float2* p = c.p[(n - 1) & 1];
+    if ((int)threadIdx.x < c.m.nc) {
+        const long e = (long)blockIdx.x * c.m.nc + threadIdx.x;
+        stf(c.x, e, ldf(c.x, e) + al * ldf(p, e) + om * ldf(c.s, e));
+    }
+}
+
+// r = v - w in storage precision P (v FP64, w in P)
+template <class P>
+__global__ __launch_bounds__(256) void k_mg_residual(const double2* __restrict__ v, const void* __restrict__ w, void* r,
+                                                     long n)
+{
+    using T = typename P::real;
+    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
+        const double2 vv = v[e];
+        const auto wv = P::ld(w, e);
+        P::st(r, e, cx<T>{(T)(vv.x - (double)wv.re), (T)(vv.y - (double)wv.im)});
+    }
+}
+
+// Minimal-residual step: alpha = (w, r) / (w, w) from nb partials of the hop that formed w (every block sums them
+// in the same order), z_s += alpha r (FP32; zero before the first step), r -= alpha w (r, w in P).  The last step
+// adds z_s to the FP64 z instead of storing it, and leaves r.
+template <class P>
+__global__ __launch_bounds__(256) void k_mg_mr_update(float2* zs, void* r, const void* w, long n,
+                                                      const double* partials, int nb, int first, int last, double2* z)
 {
     __shared__ double tot[3];
     double v[3] = {0.0, 0.0, 0.0};
@@ -516,14 +782,21 @@ __global__ __launch_bounds__(256) void k_mg_mr_update(void* z, void* r, const vo
     const double ww = tot[2];
     const double ar = ww > 0.0 ? tot[0] / ww : 0.0, ai = ww > 0.0 ? tot[1] / ww : 0.0;
     using T = typename P::real;
-    using TZ = typename PZ::real;
     const cx<T> al = {(T)ar, (T)ai};
-    const cx<TZ> alz = {(TZ)ar, (TZ)ai};
+    const cx<float> alz = {(float)ar, (float)ai};
     for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
-        const auto rv = P::ld(r, e), wv = P::ld(w, e);
-        const auto zv = PZ::ld(z, e);
-        PZ::st(z, e, zv + alz * cx<TZ>{(TZ)rv.re, (TZ)rv.im});
-        P::st(r, e, rv - al * wv);
+        const auto rv = P::ld(r, e);
+        cx<float> zv = alz * cx<float>{(float)rv.re, (float)rv.im};
+        if (!first) zv = cx<float>{zs[e].x, zs[e].y} + zv;
+        if (last) {
+            double2 o = z[e];
+            o.x += (double)zv.re;
+            o.y += (double)zv.im;
+            z[e] = o;
+        } else {
+            zs[e] = make_float2(zv.re, zv.im);
+            P::st(r, e, rv - al * P::ld(w, e));
+        }
     }
 }
 
@@ -532,19 +805,6 @@ __global__ __launch_bounds__(256) void k_mg_mr_update(void* z, void* r, const vo
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// Storage of the coarse stencil in the preconditioner's coarse solve (QCDW_MG_YPREC: 0 FP32, 1 BF16,
-// 2 FP16) and the smoother's precision (QCDW_MG_SMOOTH_F64 = 1: FP64, else the operator's inner one).
-#ifndef QCDW_MG_YPREC
-#define QCDW_MG_YPREC 1
-#endif
-#ifndef QCDW_MG_SMOOTH_F64
-#define QCDW_MG_SMOOTH_F64 0
-#endif
-namespace qcdw {
-using MG_YP = std::conditional_t<QCDW_MG_YPREC == 0, P32, std::conditional_t<QCDW_MG_YPREC == 1, PBF16, PF16>>;
-constexpr int MG_YPREC = QCDW_MG_YPREC == 0 ? F32 : QCDW_MG_YPREC == 1 ? BF16 : F16;
-}  // namespace qcdw
-
 struct qcdw_mg {
     qcdw_op* op = nullptr;  // operator the set-up and the coarse operator were made with
     qcdw_ctx* ctx = nullptr;
@@ -553,13 +813,21 @@ struct qcdw_mg {
     PoolBuf blk_sites, fine_loc, cnbr;
     PoolBuf W64, W32;        // block vectors
     PoolBuf Yt64, Ylo;       // coarse stencil, column-major blocks: FP64 (API), MG_YP (the preconditioner's solve)
-    PoolBuf rc, ec, ec64;    // coarse right-hand side (FP64), solution (FP32), FP64 scratch
-    PoolBuf ck[6];           // coarse BiCGStab vectors r, r0, p, v, s, t (FP32)
-    PoolBuf scal, dpart, dpart2, dnorm, dscale;
-    PoolBuf t64, r64, w64, tmpo;  // fine even-site FP64 scratch of the preconditioner
-    PoolBuf rlo, wlo, zlo, tmplo;  // smoother vectors in the operator's inner precision (z accumulated in FP32)
+    PoolBuf rc, ec;          // coarse right-hand side (FP64), solution (FP32)
+    PoolBuf ck[8];           // coarse BiCGStab vectors r, r0, s, t, p and v twice (FP32)
+    PoolBuf slots, dpart, dpart2, dnorm;
+    PoolBuf t64;                   // fine even-site FP64 scratch of the preconditioner
+    PoolBuf rlo, wlo, zlo, tmplo, zs;  // smoother vectors in the operator's inner precision, its correction in FP32
     long n_c = 0;                  // complex entries of a coarse vector
-    int nb_apply = 0, nb_blas = 0, nb_fine = 0;
+    int nb_fine = 0;
+    // the coarse solve's launches, all on this object's buffers (captured at the first use)
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    ~qcdw_mg()
+    {
+        if (exec) (void)hipGraphExecDestroy(exec);
+        if (graph) (void)hipGraphDestroy(graph);
+    }
 };
 
 namespace {
@@ -638,13 +906,94 @@ qcdw_status mg_build_coarse(qcdw_mg* mg, qcdw_op* op)
     return QCDW_OK;
 }
 
-template <class PY, class P, int RED>
-hipError_t coarse_apply(hipStream_t s, const qcdw_mg* mg, const void* Yt, const void* in, void* out, const void* y,
-                        double* partials, const int* stop)
+// Coarse sites up to which every block sums the partials of the launch before itself (each reads Vc x 8 doubles)
+constexpr int MG_FUSE = 1024;
+// iterations up to which the coarse solve is captured as one graph
+constexpr int MG_GRAPH_ITERS = 128;
+
+// e ~ D_c^-1 rc / ||rc||: normalisation, coarse_iters iterations with early exit, as launches on stream s
+template <bool FUSED>
+hipError_t coarse_launches(hipStream_t s, qcdw_mg* mg)
 {
-    hipLaunchKernelGGL((k_mg_coarse_apply<PY, P, RED>), dim3(mg->nb_apply), dim3(256), 0, s, mg->md, Yt, in, out, y,
-                       partials, stop);
+    CoarseSolve c{};
+    c.m = mg->md;
+    c.Yt = mg->Ylo.p;
+    c.rc = (const double2*)mg->rc.p;
+    c.norm2 = (const double*)mg->dnorm.p;
+    c.x = (float2*)mg->ec.p;
+    float2** v[8] = {&c.r, &c.r0, &c.s, &c.t, &c.p[0], &c.p[1], &c.v[0], &c.v[1]};
+    for (int k = 0; k < 8; k++) *v[k] = (float2*)mg->ck[k].p;
+    c.slot = (CoarseSlot*)mg->slots.p;
+    c.pa = (double*)mg->dpart.p;
+    c.pb = c.pa + 8L * (mg->md.Vc + 1);
+    c.tol2 = mg->prm.coarse_tol * mg->prm.coarse_tol;
+    const int n = mg->prm.coarse_iters;
+    const dim3 grid(mg->md.Vc), block(256);
+    hipError_t e = launch_norm2(s, F64, mg->rc.p, mg->n_c, (double*)mg->dpart2.p, (double*)mg->dnorm.p);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mg_coarse_start, g256(mg->n_c), block, 0, s, c, mg->n_c);
+    for (int it = 0; it < n; it++) {
+        hipLaunchKernelGGL(k_mg_coarse_a<FUSED>, grid, block, 0, s, c, it);
+        if (!FUSED) hipLaunchKernelGGL(k_mg_coarse_total, dim3(1), block, 0, s, c.pa, mg->md.Vc);
+        hipLaunchKernelGGL(k_mg_coarse_b<FUSED>, grid, block, 0, s, c, it);
+        if (!FUSED) hipLaunchKernelGGL(k_mg_coarse_total, dim3(1), block, 0, s, c.pb, mg->md.Vc);
+    }
+    if (n > 0) hipLaunchKernelGGL(k_mg_coarse_end<FUSED>, grid, block, 0, s, c, n);
     return hipGetLastError();
+}
+
+qcdw_status coarse_solve(qcdw_mg* mg)
+{
+    qcdw_ctx* ctx = mg->ctx;
+    const bool fused = mg->md.Vc <= MG_FUSE;
+    const auto launch = [&](hipStream_t s) {
+        return fused ? coarse_launches<true>(s, mg) : coarse_launches<false>(s, mg);
+    };
+    if (mg->prm.coarse_iters > MG_GRAPH_ITERS) {
+        HIPCHK(ctx, launch(ctx->stream));
+        return QCDW_OK;
+    }
+    if (!mg->exec) {
+        hipStream_t cs = ctx->cap_stream;
+        HIPCHK(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+        const hipError_t e = launch(cs);
+        hipGraph_t g = nullptr;
+        const hipError_t e2 = hipStreamEndCapture(cs, &g);
+        if (mg->graph) (void)hipGraphDestroy(mg->graph);
+        mg->graph = g;
+        HIPCHK(ctx, e);
+        HIPCHK(ctx, e2);
+        HIPCHK(ctx, hipGraphInstantiate(&mg->exec, g, nullptr, nullptr, 0));
+    }
+    HIPCHK(ctx, hipGraphLaunch(mg->exec, ctx->stream));
+    return QCDW_OK;
+}
+
+// z = P e (even sites), undoing the normalisation, and minimal-residual smoothing on M_hat in storage precision P:
+// r = v - M_hat z, then z_s += alpha r, r -= alpha w with w = M_hat r (alpha = (w, r) / (w, w)), and z += z_s
+template <class P>
+qcdw_status prolong_and_smooth(qcdw_mg* mg, qcdw_op* op, const PrecView& vl, const void* v, void* z)
+{
+    qcdw_ctx* ctx = mg->ctx;
+    hipStream_t s = ctx->stream;
+    const MgDev& m = mg->md;
+    const long n = 12L * m.g.Vh;
+    const int iters = mg->prm.smooth_iters;
+    hipLaunchKernelGGL((k_mg_prolong<P32, P32, P64, P>), dim3(m.Vc), dim3(256), 0, s, m, mg->W32.p, mg->ec.p,
+                       (const double*)mg->dnorm.p, z, nullptr, 1, iters > 0 ? mg->zlo.p : nullptr);
+    HIPCHK(ctx, hipGetLastError());
+    if (iters == 0) return QCDW_OK;
+    HIPCHK(ctx, matpc(s, op, vl, mg->zlo.p, mg->wlo.p, mg->tmplo.p, RED_NONE, nullptr, nullptr, nullptr));
+    hipLaunchKernelGGL(k_mg_residual<P>, dim3(mg->nb_fine), dim3(256), 0, s, (const double2*)v, mg->wlo.p, mg->rlo.p, n);
+    double* part = (double*)mg->dpart2.p;
+    const int nb = hop_blocks_nt(op->g, op->hop_nt[vl.prec], op->hop_cg[vl.prec]);
+    for (int it = 0; it < iters; it++) {
+        HIPCHK(ctx, matpc(s, op, vl, mg->rlo.p, mg->wlo.p, mg->tmplo.p, RED_TS, nullptr, part, nullptr));
+        hipLaunchKernelGGL(k_mg_mr_update<P>, dim3(mg->nb_fine), dim3(256), 0, s, (float2*)mg->zs.p, mg->rlo.p,
+                           mg->wlo.p, n, (const double*)part, nb, it == 0, it + 1 == iters, (double2*)z);
+        HIPCHK(ctx, hipGetLastError());
+    }
+    return QCDW_OK;
 }
 
 // Preconditioner of M_hat on FP64 even-site internal fields: z = K(v)
@@ -653,72 +1002,21 @@ qcdw_status mg_precondition(qcdw_mg* mg, qcdw_op* op, const void* v, void* z)
     qcdw_ctx* ctx = mg->ctx;
     hipStream_t s = ctx->stream;
     const MgDev& m = mg->md;
-    const long n = 12L * m.g.Vh;
     // coarse right-hand side P^+ (A_ee v) on the even sites
     HIPCHK(ctx, launch_clov_apply_internal(s, F64, m.g, op->A64[0].p, v, mg->t64.p));
     hipLaunchKernelGGL((k_mg_restrict<P32, P64>), dim3(m.Vc * ((m.N + 3) / 4)), dim3(256), 0, s, m, mg->W32.p,
-                       mg->t64.p, nullptr, 1,
-                       (double2*)mg->rc.p);
+                       mg->t64.p, nullptr, 1, (double2*)mg->rc.p);
     HIPCHK(ctx, hipGetLastError());
-    // coarse BiCGStab on the normalised right-hand side, FP32 vectors, scalars on the device
-    Scal* S = (Scal*)mg->scal.p;
-    double* dn2 = (double*)mg->dnorm.p;
-    HIPCHK(ctx, launch_norm2(s, F64, mg->rc.p, mg->n_c, (double*)mg->dpart2.p, dn2));
-    hipLaunchKernelGGL(k_mg_coarse_init, dim3(1), dim3(1), 0, s, S, dn2, mg->prm.coarse_tol * mg->prm.coarse_tol,
-                       (double*)mg->dscale.p);
-    void *r = mg->ck[0].p, *r0 = mg->ck[1].p, *p = mg->ck[2].p, *vv = mg->ck[3].p, *sv = mg->ck[4].p,
-         *t = mg->ck[5].p;
-    double* dpart = (double*)mg->dpart.p;
-    double* dpart2 = (double*)mg->dpart2.p;
-    HIPCHK(ctx, launch_cycle_start(s, F32, mg->rc.p, r, r0, p, mg->ec.p, mg->n_c, (const double*)mg->dscale.p, S,
-                                   dpart2, 1, nullptr, 0, false));
-    for (int it = 0; it < mg->prm.coarse_iters; it++) {
-        HIPCHK(ctx, (coarse_apply<MG_YP, P32, RED_WDOT>(s, mg, mg->Ylo.p, p, vv, r0, dpart, &S->flags)));
-        HIPCHK(ctx, launch_fin_alpha(s, S, dpart, mg->nb_apply, 1, nullptr));
-        HIPCHK(ctx, launch_bicg_s(s, F32, sv, r, vv, mg->n_c, S, 1, nullptr, 0, nullptr, 0, nullptr));
-        HIPCHK(ctx, (coarse_apply<MG_YP, P32, RED_TS>(s, mg, mg->Ylo.p, sv, t, sv, dpart, &S->flags)));
-        HIPCHK(ctx, launch_fin_omega(s, S, dpart, mg->nb_apply, 1, nullptr));
-        HIPCHK(ctx, launch_bicg_xr(s, F32, F32, mg->ec.p, p, sv, r, t, r0, mg->n_c, S, dpart2, 1, nullptr, 0, nullptr,
-                                   0, nullptr));
-        HIPCHK(ctx, launch_fin_beta(s, S, dpart2, mg->nb_blas, nullptr, 1));
-        HIPCHK(ctx, launch_bicg_p(s, F32, p, r, vv, mg->n_c, S, 1, nullptr, 0, nullptr, 0, nullptr));
+    CHK(coarse_solve(mg));
+    const int lp = QCDW_MG_SMOOTH_F64 ? (int)F64 : op->inner;
+    const PrecView vl = view(op, lp);
+    switch (lp) {
+    case F64: return prolong_and_smooth<P64>(mg, op, vl, v, z);
+    case F32: return prolong_and_smooth<P32>(mg, op, vl, v, z);
+    case BF16: return prolong_and_smooth<PBF16>(mg, op, vl, v, z);
+    case F16: return prolong_and_smooth<PF16>(mg, op, vl, v, z);
     }
-    // z = P e (even sites), undoing the normalisation
-    hipLaunchKernelGGL((k_mg_prolong<P32, P32, P64>), dim3(m.Vc), dim3(256), 0, s, m, mg->W32.p, mg->ec.p, dn2, z,
-                       nullptr, 1);
-    HIPCHK(ctx, hipGetLastError());
-    // minimal-residual smoothing on M_hat in the operator's inner precision: r = v - M_hat z, then
-    // z_s += alpha r, r -= alpha w with w = M_hat r (alpha = (w, r) / (w, w)), and finally z += z_s
-    if (mg->prm.smooth_iters > 0) {
-        const int lp = QCDW_MG_SMOOTH_F64 ? (int)F64 : op->inner;
-        const PrecView vl = view(op, lp);
-        HIPCHK(ctx, launch_convert(s, F64, lp, z, mg->zlo.p, n, 1.0));          // z in the inner precision
-        HIPCHK(ctx, matpc(s, op, vl, mg->zlo.p, mg->wlo.p, mg->tmplo.p, RED_NONE, nullptr, nullptr, nullptr));
-        HIPCHK(ctx, launch_convert(s, F64, lp, v, mg->rlo.p, n, 1.0));
-        HIPCHK(ctx, launch_convert(s, lp, F64, mg->wlo.p, mg->w64.p, n, 1.0));
-        HIPCHK(ctx, launch_xmy_norm2(s, F64, F64, v, mg->w64.p, mg->r64.p, n, dpart2, dn2));
-        HIPCHK(ctx, launch_convert(s, F64, lp, mg->r64.p, mg->rlo.p, n, 1.0));  // r = v - M_hat z
-        HIPCHK(ctx, launch_convert(s, F64, F32, mg->r64.p, mg->zlo.p, n, 0.0));  // z_s = 0 (FP32)
-        for (int it = 0; it < mg->prm.smooth_iters; it++) {
-            HIPCHK(ctx, matpc(s, op, vl, mg->rlo.p, mg->wlo.p, mg->tmplo.p, RED_NONE, nullptr, nullptr, nullptr));
-            switch (lp) {
-#define QCDW_MR_CASE(PREC, P)                                                                                      \
-    case PREC:                                                                                                     \
-        hipLaunchKernelGGL(k_mg_mr_dots<P>, dim3(mg->nb_fine), dim3(256), 0, s, mg->wlo.p, mg->rlo.p, n, dpart2);   \
-        hipLaunchKernelGGL((k_mg_mr_update<P, P32>), dim3(mg->nb_fine), dim3(256), 0, s, mg->zlo.p, mg->rlo.p,       \
-                           mg->wlo.p, n, (const double*)dpart2, mg->nb_fine);                                      \
-        break;
-                QCDW_MR_CASE(F64, P64)
-                QCDW_MR_CASE(F32, P32)
-                QCDW_MR_CASE(BF16, PBF16)
-                QCDW_MR_CASE(F16, PF16)
-#undef QCDW_MR_CASE
-            }
-            HIPCHK(ctx, hipGetLastError());
-        }
-        HIPCHK(ctx, launch_axpy_hi(s, F32, 1.0, nullptr, mg->zlo.p, z, n));  // z += z_s
-    }
-    return QCDW_OK;
+    return fail(ctx, QCDW_EINVAL, "bad inner precision %d", lp);
 }
 
 }  // namespace
@@ -842,27 +1140,22 @@ extern "C" qcdw_status qcdw_mg_create(qcdw_op* op, const qcdw_mg_params* params,
     CHK(mg_build_coarse(mg.get(), op));
     // solve workspace
     mg->n_c = (long)m.Vc * m.nc;
-    mg->nb_apply = m.Vc;  // one block (and one reduction partial) per coarse site
-    mg->nb_blas = blas_blocks(mg->n_c);
     const long nfe = 12L * g.Vh;
     mg->nb_fine = blas_blocks(nfe);
     HIPCHK(ctx, mg->rc.alloc(mg->n_c * 16));
-    HIPCHK(ctx, mg->ec64.alloc(mg->n_c * 16));
     HIPCHK(ctx, mg->ec.alloc(mg->n_c * 8));
     for (auto& b : mg->ck) HIPCHK(ctx, b.alloc(mg->n_c * 8));
-    HIPCHK(ctx, mg->scal.alloc(sizeof(Scal)));
-    HIPCHK(ctx, mg->dpart.alloc(3L * std::max(mg->nb_apply, 1) * sizeof(double)));
-    HIPCHK(ctx, mg->dpart2.alloc(3L * std::max<long>(std::max(mg->nb_blas, mg->nb_fine), 4096) * sizeof(double)));
+    HIPCHK(ctx, mg->slots.alloc(std::max(1, prm.coarse_iters) * sizeof(CoarseSlot)));
+    HIPCHK(ctx, mg->dpart.alloc(16L * (m.Vc + 1) * sizeof(double)));
+    const int nb_hop = std::max(hop_blocks(g.Vh), hop_ctiles(g) * g.Lt);  // most blocks of any hop form
+    HIPCHK(ctx, mg->dpart2.alloc(3L * std::max<long>(nb_hop, MAX_PARTIALS) * sizeof(double)));
     HIPCHK(ctx, mg->dnorm.alloc(64));
-    HIPCHK(ctx, mg->dscale.alloc(64));
     HIPCHK(ctx, mg->t64.alloc(nfe * 16));
-    HIPCHK(ctx, mg->r64.alloc(nfe * 16));
-    HIPCHK(ctx, mg->w64.alloc(nfe * 16));
-    HIPCHK(ctx, mg->tmpo.alloc(nfe * 16));
     HIPCHK(ctx, mg->rlo.alloc(nfe * 16));
     HIPCHK(ctx, mg->wlo.alloc(nfe * 16));
     HIPCHK(ctx, mg->zlo.alloc(nfe * 16));
     HIPCHK(ctx, mg->tmplo.alloc(nfe * 16));
+    HIPCHK(ctx, mg->zs.alloc(nfe * 8));
     HIPCHK(ctx, hipStreamSynchronize(s));
     *out = mg.release();
     return QCDW_OK;
@@ -923,8 +1216,8 @@ extern "C" qcdw_status qcdw_mg_prolong(qcdw_mg* mg, const void* coarse, void* fi
     const long vb = 12L * m.g.Vh * 16;
     PoolBuf f;
     HIPCHK(ctx, f.alloc(2 * vb));
-    hipLaunchKernelGGL((k_mg_prolong<P64, P64, P64>), dim3(m.Vc), dim3(256), 0, s, m, mg->W64.p, coarse, nullptr,
-                       f.p, (char*)f.p + vb, 2);
+    hipLaunchKernelGGL((k_mg_prolong<P64, P64, P64, P64>), dim3(m.Vc), dim3(256), 0, s, m, mg->W64.p, coarse,
+                       nullptr, f.p, (char*)f.p + vb, 2, nullptr);
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, launch_unpack_spinor(s, F64, m.g, f.p, 0, fine, 1.0));
     HIPCHK(ctx, launch_unpack_spinor(s, F64, m.g, (const char*)f.p + vb, 1, fine, 1.0));
@@ -940,7 +1233,8 @@ extern "C" qcdw_status qcdw_mg_coarse_apply(qcdw_mg* mg, const void* in, void* o
     CHK(check_dev(ctx, in, "in"));
     CHK(check_dev(ctx, out, "out"));
     if (in == out) return fail(ctx, QCDW_EINVAL, "out must not alias in");
-    HIPCHK(ctx, (coarse_apply<P64, P64, RED_NONE>(ctx->stream, mg, mg->Yt64.p, in, out, nullptr, nullptr, nullptr)));
+    hipLaunchKernelGGL(k_mg_coarse_apply, dim3(mg->md.Vc), dim3(256), 0, ctx->stream, mg->md, mg->Yt64.p, in, out);
+    HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return QCDW_OK;
 }
