@@ -261,11 +261,29 @@ __device__ __forceinline__ int xcd_tile(int b, int nblk)
 // ---------------------------------------------------------------------------
 // deterministic reductions (fixed lane/wave order)
 // ---------------------------------------------------------------------------
+// Sum over the 64 lanes, in every lane; every lane must be active.  The lanes' values move by DPP (operand
+// modifiers of vector moves: prefix steps of 1, 2, 4, 8 within a row of 16, then the last lane of a row to the next
+// row and of the lower half to the upper), not through the LDS crossbar, whose round trips were a tenth of the
+// hops that end in a dot product.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_moved(double v)
+{
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, make_uint2((unsigned)lo, (unsigned)hi));
+}
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_moved<0x111, 0xf>(v);  // row_shr:1
+    v += dpp_moved<0x112, 0xf>(v);  // row_shr:2
+    v += dpp_moved<0x114, 0xf>(v);  // row_shr:4
+    v += dpp_moved<0x118, 0xf>(v);  // row_shr:8
+    v += dpp_moved<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_moved<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    return __builtin_bit_cast(double, make_uint2((unsigned)__builtin_amdgcn_readlane((int)u.x, 63),
+                                                 (unsigned)__builtin_amdgcn_readlane((int)u.y, 63)));
 }
 
 // Sum K values over a 256-thread block; thread 0 writes them to out[0..K).

@@ -37,25 +37,34 @@ __device__ __forceinline__ void load_link(const void* gauge, long off, long stri
 //   half 0 reads entries 0..26, half 1 reads entries 9..35.
 // FMA: every complex multiply-add as four real multiply-adds (fewer instructions; used by the
 // multi-RHS hop, whose loop is bound by vector ALU issue); else the plain complex products.
-template <bool FMA, typename T>
-__device__ __forceinline__ void herm_rows(const T (&win)[27], int h, const cx<T> (&vo)[3], const cx<T> (&vx)[3],
-                                          cx<T> (&out)[3])
+// The 27 reals of half h's rows in the order that herm_apply uses: diagonal (3), own off-diagonal entries (1,0),
+// (2,0), (2,1), then the cross block (rows of this half, columns of the other half)
+template <typename T>
+__device__ __forceinline__ void herm_coef(const T (&win)[27], int h, T (&m)[27])
 {
-    T d[3], lo[6], Xr[9], Xi[9];
 #pragma unroll
-    for (int i = 0; i < 3; i++) d[i] = h ? win[18 + i] : win[i];
+    for (int i = 0; i < 3; i++) m[i] = h ? win[18 + i] : win[i];
 #pragma unroll
-    for (int i = 0; i < 6; i++) lo[i] = h ? win[21 + i] : win[3 + i];
+    for (int i = 0; i < 6; i++) m[3 + i] = h ? win[21 + i] : win[3 + i];
 #pragma unroll
-    for (int m = 0; m < 9; m++) {
-        Xr[m] = h ? win[2 * m] : win[9 + 2 * m];
-        Xi[m] = h ? win[2 * m + 1] : win[10 + 2 * m];
-    }
-    const cx<T> l10 = {lo[0], lo[1]}, l20 = {lo[2], lo[3]}, l21 = {lo[4], lo[5]};
+    for (int a = 0; a < 3; a++)
+#pragma unroll
+        for (int b = 0; b < 3; b++) {
+            const int x = 2 * (3 * a + b), y = 9 + 2 * (3 * b + a);
+            m[9 + x] = h ? win[x] : win[y];
+            m[10 + x] = h ? win[x + 1] : -win[y + 1];
+        }
+}
+
+template <bool FMA, typename T>
+__device__ __forceinline__ void herm_apply(const T (&m)[27], const cx<T> (&vo)[3], const cx<T> (&vx)[3],
+                                           cx<T> (&out)[3])
+{
+    const cx<T> l10 = {m[3], m[4]}, l20 = {m[5], m[6]}, l21 = {m[7], m[8]};
     cx<T> own[3][3];
-    own[0][0] = {d[0], T(0)};
-    own[1][1] = {d[1], T(0)};
-    own[2][2] = {d[2], T(0)};
+    own[0][0] = {m[0], T(0)};
+    own[1][1] = {m[1], T(0)};
+    own[2][2] = {m[2], T(0)};
     own[1][0] = l10;
     own[2][0] = l20;
     own[2][1] = l21;
@@ -78,8 +87,7 @@ __device__ __forceinline__ void herm_rows(const T (&win)[27], int h, const cx<T>
         }
 #pragma unroll
         for (int b = 0; b < 3; b++) {
-            // cross block: rows of this half, columns of the other half
-            cx<T> cb = h ? cx<T>{Xr[3 * a + b], Xi[3 * a + b]} : cx<T>{Xr[3 * b + a], -Xi[3 * b + a]};
+            const cx<T> cb = {m[9 + 2 * (3 * a + b)], m[10 + 2 * (3 * a + b)]};
             if constexpr (FMA)
                 cmac(s, cb, vx[b]);
             else
@@ -87,6 +95,15 @@ __device__ __forceinline__ void herm_rows(const T (&win)[27], int h, const cx<T>
         }
         out[a] = s;
     }
+}
+
+template <bool FMA, typename T>
+__device__ __forceinline__ void herm_rows(const T (&win)[27], int h, const cx<T> (&vo)[3], const cx<T> (&vx)[3],
+                                          cx<T> (&out)[3])
+{
+    T m[27];
+    herm_coef(win, h, m);
+    herm_apply<FMA>(m, vo, vx, out);
 }
 
 // lane q's 27-entry window: chirality q >> 1, entries 9 (q & 1) .. 9 (q & 1) + 26

@@ -1,48 +1,113 @@
 // Multi-right-hand-side parity hop (a propagator is 12 solves, paper Sec. III.B;
-// the paper names a multi-source solve as the next step).  Same four-lane site
-// decomposition as hop.hip, but each lane loads its four reconstruct-12 links
-// and its clover window once and applies them to every right-hand side in a
-// register-resident loop, so link and clover bytes are paid once per site for
-// all RHS.  RHS k of a field lives at offset k * 12 * Vh complex (a stack of
-// single-RHS fields), and RHS whose solver flag is set are skipped.  With
-// cgroup > 0 the tiles follow the slice-group order of the single-RHS hop.
+// the paper names a multi-source solve as the next step).  Four lanes per site as
+// in hop.hip, but each lane loads its four reconstruct-12 links and its clover
+// window once and applies them to every right-hand side in a register-resident
+// loop, so link and clover bytes are paid once per site for all RHS.  RHS k of a
+// field lives at offset k * 12 * Vh complex (a stack of single-RHS fields), and RHS
+// whose solver flag is set are skipped.  With cgroup > 0 the tiles follow the
+// slice-group order of the single-RHS hop.
+//
+// The lanes of a wave are ordered spin by spin, 16 sites each: a load of one spin's
+// three colours then reads a run of consecutive sites in neighbouring lanes, and the
+// first cache counts 2.5 times fewer accesses.  With the four spins of a site in
+// neighbouring lanes (the order of hop.hip) the loop ran at the rate of one access
+// per lane and load: 0.31 ms for 12 BF16 right-hand sides at 24^3x64, all active.
+// The two exchanges between a site's lanes go through ds_bpermute.
 #include <hip/hip_ext.h>
+
+#include <type_traits>
 
 #include "hop_common.h"
 
-// right-hand sides processed together per loop step (their neighbour loads in flight together); two
-// per step were measured 1.5x slower at 24^3x64 (the doubled accumulators push the kernel to 256 VGPRs)
-#ifndef QCDW_MRHS_STEP
-#define QCDW_MRHS_STEP 1
-#endif
-
 namespace qcdw {
 
-template <class P, int EPI, int RED>
-__global__ __launch_bounds__(256) void hop_mrhs_kernel(HopArgs a, const Scal* S)
+// whether every right-hand side is finished (uniform; the launches enqueued after the end of a cycle return here,
+// before they load links: 47 us each at 24^3x64)
+__device__ __forceinline__ bool all_finished(const Scal* S, int nrhs)
 {
+    if (!S) return false;
+    for (int r = 0; r < nrhs; r++)
+        if (!S[r].flags) return false;
+    return true;
+}
+
+// Reduction partials of a block, right-hand side by right-hand side: each wave leaves its sums in LDS, and the block
+// adds the four waves' once at the end (a barrier pair per right-hand side held the loop's loads up).
+constexpr int MRHS_MAX = 16;
+struct MrhsSums {
+    double v[MRHS_MAX][4][3];
+};
+__device__ __forceinline__ void mrhs_sum_wave(MrhsSums& m, int r, double (&v)[3], int n)
+{
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        if (k >= n) break;
+        const double s = wave_sum(v[k]);
+        if ((threadIdx.x & 63) == 0) m.v[r][threadIdx.x >> 6][k] = s;
+    }
+}
+// partials [r][nblk][3] of this block; finished right-hand sides keep theirs
+__device__ __forceinline__ void mrhs_sum_store(const MrhsSums& m, const Scal* S, int nrhs, int n, double* partials,
+                                               int tile, int nblk)
+{
+    __syncthreads();
+    const int r = threadIdx.x >> 2, k = threadIdx.x & 3;
+    if (r < nrhs && k < 3 && !(S && S[r].flags))
+        partials[3 * ((long)r * nblk + tile) + k] =
+            k < n ? ((m.v[r][0][k] + m.v[r][1][k]) + m.v[r][2][k]) + m.v[r][3][k] : 0.0;
+}
+
+// v of the lane at byte address `at` (ds_bpermute: the exchange between rows of 16 lanes, on the idle LDS pipe)
+__device__ __forceinline__ float lane_val(float v, int at)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(at, __builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double lane_val(double v, int at)
+{
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    return __builtin_bit_cast(double, make_uint2((unsigned)__builtin_amdgcn_ds_bpermute(at, (int)u.x),
+                                                 (unsigned)__builtin_amdgcn_ds_bpermute(at, (int)u.y)));
+}
+template <typename T>
+__device__ __forceinline__ cx<T> lane_cx(cx<T> v, int at)
+{
+    return {lane_val(v.re, at), lane_val(v.im, at)};
+}
+
+template <class P, int EPI, int RED>
+__global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(HopArgs a, const Scal* S)
+{
+    if (all_finished(S, a.nrhs)) return;
+    __shared__ MrhsSums sums;
+    constexpr int NSUM = RED == RED_WDOT ? 2 : 3;
     using T = typename P::real;
     const Geom g = a.g;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int nblk = gridDim.x;
-    const int q = threadIdx.x & 3;
+    const int q = (threadIdx.x >> 4) & 3, ts = (threadIdx.x >> 6) * 16 + (threadIdx.x & 15);
+    // lanes (byte addresses) of this site's partner half and of the chirality block's other spin
+    const int at_partner = 4 * ((threadIdx.x & 15) + 16 * (q < 2 ? q + 2 : 3 - q)),
+              at_xor1 = 4 * ((threadIdx.x & 63) ^ 16);
     int site;
     bool valid;
     if (a.cgroup > 0) {  // slice-group order, as in the single-RHS hop_kernel
         const int G = a.cgroup, St = g.Lxh * g.Ly * g.Lz;
         const int grp = tile / (G * g.Lt), rr = tile - grp * G * g.Lt;
         const int t = rr / G, ct = grp * G + (rr - t * G);
-        const int c = ct * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+        const int c = ct * HOP_SITES_PER_BLOCK + ts;
         site = t * St + c;
         valid = c < St;
     } else {
-        site = tile * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+        site = tile * HOP_SITES_PER_BLOCK + ts;
         valid = site < g.Vh;
     }
-    const int gq = q >> 1, k = q & 1;
+    const int gq = q >> 1;
     const long Vh = g.Vh;
     const long field = 12L * Vh;  // complex per RHS
-    const int su = k, sl = gq == 0 ? 3 - k : 2 + k;
+    // this lane's own spin and the one that its directions couple to it: row q of (1 -/+ gamma) psi, so that the sum
+    // for spin q collects in acc_u in every lane (for z and t that is the row l of hop_common.h, with the
+    // conjugate coefficient)
+    const int su = q, sl = gq == 0 ? 3 - q : q - 2;
 
     // per-lane hop geometry, links (row 2 rebuilt once) and clover window, shared by all RHS
     LaneHops<T, 6> L;
@@ -59,69 +124,116 @@ __global__ __launch_bounds__(256) void hop_mrhs_kernel(HopArgs a, const Scal* S)
     }
 #pragma unroll
     for (int e = 0; e < 27; e++) win[e] = T(0);
-    if (valid) {
-        lane_hops<T, 6, link_soa_for(P::cbytes)>(g, site, a.parity, q, L);
+    if (valid) lane_hops<T, 6, link_soa_for(P::cbytes)>(g, site, a.parity, q, L);
+    if (gq == 1) L.cs[0] = -L.cs[0], L.cs[1] = -L.cs[1];
+    // Right-hand sides in flight ahead of the one that is computed: two in BF16 (a hop's words are replaced as soon
+    // as they are read; 24 registers each, 30 with the epilogue's operands), one in FP16 (whose conversions take the
+    // registers) and, without the epilogue's operands, in FP32; none in FP64.  The links leave room for two waves per
+    // SIMD, which do not cover the loads' latency.  24^3x64, 12 BF16 right-hand sides, a solve's mean per launch (first
+    // hop / r0 dot / t dot; the launches enqueued past the end of a cycle count): a site's lanes side by side
+    // 207 / 426 / 296 us; this order, three waves, none ahead 170 / 385 / 351; one 189 / 220 / 213; two 165 / 213 / 209.
+    constexpr int AHEAD = std::is_same_v<P, PBF16> ? 2 : P::cbytes <= 8 ? 1 : 0;
+    constexpr bool OWN_AHEAD = P::cbytes == 4;
+    constexpr bool HAS_Y = EPI == EPI_CLOV_XPAY || RED == RED_TS, HAS_W = RED == RED_WDOT;
+    // byte offsets within a right-hand side: 32-bit beside a scalar base in 16-bit storage
+    using Off = std::conditional_t<P::cbytes == 4, uint32_t, long>;
+    const long own = sp_idx(q, valid ? site : 0, 0, Vh);
+    const Off own_at = (Off)(own * P::cbytes);
+    Off at_u[4], at_l[4];
 #pragma unroll
-        for (int h = 0; h < 4; h++) load_link<P, 6>(a.gauge, L.loff[h], L.lstr, ur[h]);
-        if constexpr (EPI != EPI_NONE) load_window<P>(a.clov, Vh, site, q, win);
+    for (int h = 0; h < 4; h++) {
+        at_u[h] = (Off)(sp_idx(su, L.nbh[h], 0, Vh) * P::cbytes);
+        at_l[h] = (Off)(sp_idx(sl, L.nbh[h], 0, Vh) * P::cbytes);
     }
-
-    // right-hand sides in groups of QCDW_MRHS_STEP, so that their neighbour loads are in flight together
-    constexpr int RS = QCDW_MRHS_STEP;
-    for (int r0 = 0; r0 < a.nrhs; r0 += RS) {
-        bool act[RS];
+    struct Raw {
+        uint32_t u[3 * P::cbytes / 4];
+    };
+    auto fetch = [&](const void* base, int r, Off at) {
+        Raw v;
+        uint64_t b = (uint64_t)base + __builtin_amdgcn_readfirstlane(r) * field * P::cbytes;
+        asm volatile("" : "+s"(b));  // kept scalar: an address takes one 32-bit register, not a 64-bit pair
+        const auto* src = (const __attribute__((address_space(1))) uint32_t*)(
+            (const __attribute__((address_space(1))) char*)b + at);
 #pragma unroll
-        for (int j = 0; j < RS; j++)  // uniform: every thread reads the same flags
-            act[j] = r0 + j < a.nrhs && !(S && S[r0 + j].flags);
-        bool any = false;
+        for (int e = 0; e < 3 * P::cbytes / 4; e++) v.u[e] = src[e];
+        return v;
+    };
+    auto next_rhs = [&](int r) {  // uniform: every thread reads the same flags
+        while (r < a.nrhs && S && S[r].flags) r++;
+        return r;
+    };
+    struct Flight {
+        Raw u[4], l[4], y, w;
+    } fl[AHEAD == 2 ? 2 : 1];
+    auto fetch_hop = [&](Flight& f, int h, int r) {
+        f.u[h] = fetch(a.psi, r, at_u[h]);
+        f.l[h] = fetch(a.psi, r, at_l[h]);
+    };
+    auto fetch_own = [&](Flight& f, int r) {
+        if constexpr (HAS_Y) f.y = fetch(a.y, r, own_at);
+        if constexpr (HAS_W) f.w = fetch(a.w, r, own_at);
+    };
+    auto fetch_all = [&](Flight& f, int r) {
 #pragma unroll
-        for (int j = 0; j < RS; j++) any = any || act[j];
-        if (!any) continue;
-        cx<T> acc2_u[RS][3], acc2_l[RS][3];
-#pragma unroll
-        for (int j = 0; j < RS; j++)
-#pragma unroll
-            for (int c = 0; c < 3; c++) acc2_u[j][c] = acc2_l[j][c] = {T(0), T(0)};
-        // lanes past the last site run too (their neighbour offsets point at site 0 and their links are
-        // zero) and store nothing: no divergent branch around the loads
+        for (int h = 0; h < 4; h++) fetch_hop(f, h, r);
+        if constexpr (OWN_AHEAD) fetch_own(f, r);
+    };
+    // the first right-hand side's loads go out before the links'
+    int r = next_rhs(0), r1 = next_rhs(r + 1);
+    if constexpr (AHEAD > 0)
+        if (r < a.nrhs) fetch_all(fl[0], r);
+    if constexpr (AHEAD > 1)
+        if (r1 < a.nrhs) fetch_all(fl[1], r1);
+    if (valid) {
 #pragma unroll
         for (int h = 0; h < 4; h++) {
-            cx<T> hv[RS][3];
+            load_link<P, 6>(a.gauge, L.loff[h], L.lstr, ur[h]);
 #pragma unroll
-            for (int j = 0; j < RS; j++) {
-                cx<T> pu[3], pl[3];
-                if (act[j]) {
-                    load_pair<P>((const char*)a.psi + (long)(r0 + j) * field * P::cbytes, Vh, su, sl, L.nbh[h], pu,
-                                 pl);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 3; c++) pu[c] = pl[c] = {T(0), T(0)};
-                }
-                project<true>(pu, pl, L.cs[h], h < 2, hv[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < RS; j++)
-                hop_rows<true>(ur[h], h & 1, h < 2, L.fsg[h], L.cs[h], hv[j], acc2_u[j], acc2_l[j]);
+            for (int e = 0; e < 9; e++) ur[h][e] = L.fsg[h] * ur[h][e];
         }
+        if constexpr (EPI != EPI_NONE) {
+            T raw[27];
+            load_window<P>(a.clov, Vh, site, q, raw);
+            herm_coef(raw, q & 1, win);
+        }
+    }
+    auto clov_row = [&](const T (&m)[27], int i, T (&row)[11]) {
+        // own entries (1,0), (2,0), (2,1) at 3, 5, 7; (i, j) and (j, i) are conjugates
+        const int f0 = i == 2 ? 5 : 3, f1 = i == 0 ? 5 : 7;
+        const T s0 = i == 0 ? T(-1) : T(1), s1 = i == 2 ? T(1) : T(-1);
+        row[0] = m[i];
+        row[1] = m[f0];
+        row[2] = s0 * m[f0 + 1];
+        row[3] = m[f1];
+        row[4] = s1 * m[f1 + 1];
 #pragma unroll
-        for (int j = 0; j < RS; j++) {
-        if (!act[j]) continue;
-        const int r = r0 + j;
-        const long off = (long)r * field;
-        const cx<T>(&acc_u)[3] = acc2_u[j];
-        const cx<T>(&acc_l)[3] = acc2_l[j];
-        cx<T> res[3];
+        for (int e = 0; e < 6; e++) row[5 + e] = m[9 + 6 * i + e];
+    };
+    auto one_rhs = [&](Flight& f, int r, int rn, auto more) {
+        constexpr bool MORE = decltype(more)::value;
+        if constexpr (AHEAD == 0) fetch_all(f, r);
+        if constexpr (!OWN_AHEAD) fetch_own(f, r);
+        cx<T> acc_u[3], acc_l[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) acc_u[c] = acc_l[c] = {T(0), T(0)};
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            cx<T> pu[3], pl[3], hv[3];
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                pu[c] = P::ld(f.u[h].u, c);
+                pl[c] = P::ld(f.l[h].u, c);
+            }
+            project<true>(pu, pl, L.cs[h], h < 2, hv);
+            if constexpr (MORE) fetch_hop(f, h, rn);
+            hop_rows<true>(ur[h], h & 1, h < 2, T(1), L.cs[h], hv, acc_u, acc_l);
+        }
+        cx<T> res[3], outv[3], yv[3], wv[3];
 #pragma unroll
         for (int c = 0; c < 3; c++) {
-            const cx<T> mine = gq == 0 ? acc_u[c] : acc_l[c];
-            const cx<T> theirs = gq == 0 ? acc_l[c] : acc_u[c];
-            res[c] = mine + quad_dpp_cx<QUAD_PARTNER>(theirs);
-        }
-        cx<T> outv[3], yv[3];
-        if constexpr (EPI == EPI_CLOV_XPAY || RED == RED_TS) {
-#pragma unroll
-            for (int c = 0; c < 3; c++)
-                yv[c] = valid ? P::ld(a.y, off + sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
+            res[c] = acc_u[c] + lane_cx(acc_l[c], at_partner);
+            if constexpr (HAS_Y) yv[c] = P::ld(f.y.u, c);
+            if constexpr (HAS_W) wv[c] = P::ld(f.w.u, c);
         }
         if constexpr (EPI == EPI_NONE) {
 #pragma unroll
@@ -129,17 +241,29 @@ __global__ __launch_bounds__(256) void hop_mrhs_kernel(HopArgs a, const Scal* S)
         } else {
             cx<T> ox[3], br[3];
 #pragma unroll
-            for (int c = 0; c < 3; c++) ox[c] = quad_dpp_cx<QUAD_XOR1>(res[c]);
-            herm_rows<true>(win, q & 1, res, ox, br);
+            for (int c = 0; c < 3; c++) ox[c] = lane_cx(res[c], at_xor1);
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
+                T m[11];
+                clov_row(win, i, m);
+                const int j0 = i == 0 ? 1 : 0, j1 = i == 2 ? 1 : 2;
+                cx<T> s = {m[0] * res[i].re, m[0] * res[i].im};
+                cmac(s, cx<T>{m[1], m[2]}, res[j0]);
+                cmac(s, cx<T>{m[3], m[4]}, res[j1]);
+#pragma unroll
+                for (int b = 0; b < 3; b++) cmac(s, cx<T>{m[5 + 2 * b], m[6 + 2 * b]}, ox[b]);
+                br[i] = s;
+            }
             const T aa = (T)a.a;
 #pragma unroll
             for (int c = 0; c < 3; c++) outv[c] = (EPI == EPI_CLOV) ? br[c] : yv[c] - aa * br[c];
         }
+        if constexpr (MORE && OWN_AHEAD) fetch_own(f, rn);
 #pragma unroll
         for (int c = 0; c < 3; c++) outv[c] = P::rt(outv[c]);
         if (valid) {
 #pragma unroll
-            for (int c = 0; c < 3; c++) P::st(a.out, off + sp_idx(q, site, c, Vh), outv[c]);
+            for (int c = 0; c < 3; c++) P::st(a.out, r * field + own + c, outv[c]);
         }
         if constexpr (RED != RED_NONE) {
             double v[3] = {0.0, 0.0, 0.0};
@@ -148,9 +272,8 @@ __global__ __launch_bounds__(256) void hop_mrhs_kernel(HopArgs a, const Scal* S)
                 for (int c = 0; c < 3; c++) {
                     const cx<T> o = outv[c];
                     if constexpr (RED == RED_WDOT) {
-                        const cx<T> wv = P::ld(a.w, off + sp_idx(q, site, c, Vh));
-                        v[0] += (double)wv.re * o.re + (double)wv.im * o.im;
-                        v[1] += (double)wv.re * o.im - (double)wv.im * o.re;
+                        v[0] += (double)wv[c].re * o.re + (double)wv[c].im * o.im;
+                        v[1] += (double)wv[c].re * o.im - (double)wv[c].im * o.re;
                     } else {
                         v[0] += (double)o.re * yv[c].re + (double)o.im * yv[c].im;
                         v[1] += (double)o.re * yv[c].im - (double)o.im * yv[c].re;
@@ -158,11 +281,31 @@ __global__ __launch_bounds__(256) void hop_mrhs_kernel(HopArgs a, const Scal* S)
                     }
                 }
             }
-            block_sum_store<3>(v, a.partials + 3 * ((long)r * nblk + tile));
-            __syncthreads();  // the block reduction's shared buffer is reused for the next RHS
+            mrhs_sum_wave(sums, r, v, NSUM);
         }
+    };
+    if constexpr (AHEAD == 2) {
+        while (r1 < a.nrhs) {
+            const int r2 = next_rhs(r1 + 1), r3 = next_rhs(r2 + 1);
+            if (r3 >= a.nrhs) {  // two or three left
+                one_rhs(fl[0], r, r2 < a.nrhs ? r2 : r, std::true_type{});
+                one_rhs(fl[1], r1, r1, std::false_type{});
+                r = r2;
+                break;
+            }
+            one_rhs(fl[0], r, r2, std::true_type{});
+            one_rhs(fl[1], r1, r3, std::true_type{});
+            r = r2;
+            r1 = r3;
         }
+        if (r < a.nrhs) one_rhs(fl[0], r, r, std::false_type{});
+    } else if constexpr (AHEAD == 1) {
+        for (; r1 < a.nrhs; r = r1, r1 = next_rhs(r + 1)) one_rhs(fl[0], r, r1, std::true_type{});
+        if (r < a.nrhs) one_rhs(fl[0], r, r, std::false_type{});
+    } else {
+        for (; r < a.nrhs; r = next_rhs(r + 1)) one_rhs(fl[0], r, r, std::false_type{});
     }
+    if constexpr (RED != RED_NONE) mrhs_sum_store(sums, S, a.nrhs, NSUM, a.partials, tile, nblk);
 }
 
 template <class P>
@@ -190,6 +333,7 @@ hipError_t launch_hop_mrhs(hipStream_t s, int prec, int epi, int red, const HopA
                            hipEvent_t e0, hipEvent_t e1)
 {
     if (a.g.Vh <= 0 || a.nrhs <= 0) return hipSuccess;
+    if (a.nrhs > MRHS_MAX) return hipErrorInvalidValue;
     switch (prec) {
     case F64: return launch_mrhs_p<P64>(s, epi, red, a, S, e0, e1);
     case F32: return launch_mrhs_p<P32>(s, epi, red, a, S, e0, e1);
@@ -212,10 +356,10 @@ hipError_t launch_hop_mrhs(hipStream_t s, int prec, int epi, int red, const HopA
 // is rebuilt in FP32 and rounded to 16 bits once per site (the only rounding the vector form does not have);
 // the products are exact in FP32 and all eight directions accumulate there (the spatial ones first, their sum
 // then scaled by the spatial weight).  Link operands are built once per site and kept in registers for all
-// right-hand sides; the clover epilogue is the vector form's.  Measured at 24^3x64 with 12 RHS (BF16): 370 us
-// against 306 us for the vector register loop, with a third fewer vector instructions: the vector form keeps
-// its SIMDs issuing 74 % of the time and its address unit 86 % busy, while this form waits on its loads with
-// less work in flight.  The multi-RHS tuner times this form beside the others.
+// right-hand sides; the clover epilogue is the vector form's.  Measured at 24^3x64 with 12 RHS (BF16), a solve's
+// mean per launch (first hop / r0 dot / t dot): 232 / 347 / 312 us against 165 / 213 / 209 us for the vector register
+// loop: the quad of a site must be neighbouring lanes here, so its loads cost an access per lane, and it keeps
+// nothing in flight for the next right-hand side.  The multi-RHS tuner times this form beside the others.
 // ---------------------------------------------------------------------------
 typedef float mf4 __attribute__((ext_vector_type(4)));
 typedef short ms4 __attribute__((ext_vector_type(4)));
@@ -252,6 +396,9 @@ template <class P, int EPI, int RED>
 __global__ __launch_bounds__(256) void hop_mrhs_mfma_kernel(HopArgs a, const Scal* S)
 {
     static_assert(QCDW_SPINOR_SOA == 0, "the matrix-core form reads a spin's three colours as one run");
+    if (all_finished(S, a.nrhs)) return;
+    __shared__ MrhsSums sums;
+    constexpr int NSUM = RED == RED_WDOT ? 2 : 3;
     using M = Mfma16<P>;
     constexpr uint32_t SGN = 0x80008000u;
     const Geom g = a.g;
@@ -440,8 +587,7 @@ __global__ __launch_bounds__(256) void hop_mrhs_mfma_kernel(HopArgs a, const Sca
                     }
                 }
             }
-            block_sum_store<3>(v, a.partials + 3 * ((long)r * nblk + tile));
-            __syncthreads();  // the block reduction's shared buffer is reused for the next RHS
+            mrhs_sum_wave(sums, r, v, NSUM);
         }
     };
 
@@ -454,6 +600,7 @@ __global__ __launch_bounds__(256) void hop_mrhs_mfma_kernel(HopArgs a, const Sca
         fetch(r, da);
         compute(r, da);
     }
+    if constexpr (RED != RED_NONE) mrhs_sum_store(sums, S, a.nrhs, NSUM, a.partials, tile, nblk);
 }
 
 template <class P>
@@ -481,7 +628,7 @@ hipError_t launch_hop_mrhs_mfma(hipStream_t s, int prec, int epi, int red, const
                                 hipEvent_t e0, hipEvent_t e1)
 {
     if (a.g.Vh <= 0 || a.nrhs <= 0) return hipSuccess;
-    if (12L * a.g.Vh > 0x7fffffffL) return hipErrorInvalidValue;  // 32-bit neighbour offsets
+    if (a.nrhs > MRHS_MAX || 12L * a.g.Vh > 0x7fffffffL) return hipErrorInvalidValue;  // 32-bit neighbour offsets
     switch (prec) {
     case BF16: return launch_mrhs_mfma_p<PBF16>(s, epi, red, a, S, e0, e1);
     case F16: return launch_mrhs_mfma_p<PF16>(s, epi, red, a, S, e0, e1);
