@@ -622,7 +622,7 @@ struct Solver {
             b.total_tiles = batch->total_tiles;
             b.parity = parity;
             b.nbmax = batch->nbmax;
-            b.use_kappa2 = epi == EPI_CLOV_XPAY;
+            b.kpow = epi == EPI_CLOV_XPAY ? 2 : 0;
             b.psi = psi;
             b.out = out;
             b.y = y;
@@ -822,51 +822,102 @@ struct Solver {
         return QCDW_OK;
     }
 
-    // rhi = bhat - M_hat xhi in FP64 for every problem; rr[k] = ||rhi_k||^2
+    // c-tiles per group of the FP64 multi-RHS hop: the largest divisor of a slice's tiles with tiles x right-hand
+    // sides <= 216, so that neighbours along t (and most along z) are still in the XCD's L2; 24^3x64, 12 of them:
+    // groups of 18 / 9 / 6 / none 2.90 / 2.98 / 3.03 / 3.15 ms for the two hops of M_hat
+    static int rhs64_cgroup(const Geom& g, int nrhs)
+    {
+        const int m = 216 / nrhs, nct = hop_ctiles(g);
+        for (int d = std::min(m, nct - 1); d >= 2; d--)
+            if (nct % d == 0) return d;
+        return 0;
+    }
+
+    // An FP64 hop of the source preparation or a residual for every problem (of `only`, where given: problems
+    // whose flags are set there are skipped), in one launch: a batch over its table, right-hand sides of one
+    // operator with the tile's links and clover entries shared through L2, a single one in the operator's form.
+    // coef is kappa^2 (kpow 2) or c kappa (kpow 1).  Partials (RED_NORM, RED_DIST): [problem][*nb][3].
+    hipError_t hop64(int epi, int red, int parity, const void* psi, void* out, const void* y, const void* w, int kpow,
+                     double c, const Scal* only = nullptr, double* partials = nullptr, int* nb = nullptr)
+    {
+        if (batch) {
+            BatchHopArgs b{};
+            b.tab = (const BatchEntry*)batch->tab64.p;
+            b.nprob = nprob;
+            b.total_tiles = batch->total_tiles;
+            b.parity = parity;
+            b.nbmax = batch->nbmax;
+            b.kpow = kpow;
+            b.a = c;
+            b.psi = psi;
+            b.out = out;
+            b.y = y;
+            b.w = w;
+            b.partials = partials;
+            b.S = only;
+            if (nb) *nb = batch->nbmax;
+            return launch_hop_batch(s, F64, epi, red, b, 0);
+        }
+        const qcdw_op* op = ops[0];
+        const PrecView v = view(op, F64);
+        HopArgs a = hop_args(op->g, parity);
+        a.psi = psi;
+        a.out = out;
+        a.gauge = v.gauge;
+        a.clov = epi == EPI_XPAY_CLOVY ? op->A64[parity].p : v.Ainv[parity];
+        a.y = y;
+        a.w = w;
+        a.a = kpow == 2 ? op->kappa * op->kappa : c * op->kappa;
+        a.partials = partials;
+        a.nrhs = nprob;
+        if (nprob > 1) {
+            a.cgroup = rhs64_cgroup(op->g, nprob);
+            if (nb) *nb = hop_blocks_nt(op->g, 1, a.cgroup);
+            return launch_hop_rhs64(s, v.recon, epi, red, a, only);
+        }
+        a.nt = op->hop_nt[F64];
+        a.cgroup = op->hop_cg[F64];
+        a.fma = op->hop_fma[F64];
+        const int blocks = hop_blocks_nt(op->g, a.nt, a.cgroup);
+        if (red != RED_NONE && blocks > nb_hop_cap) return hipErrorInvalidValue;
+        if (nb) *nb = blocks;
+        return launch_hop(s, F64, v.recon, epi, red, a);
+    }
+
+    // rhi = bhat - M_hat xhi in FP64 for every problem; rr[k] = ||rhi_k||^2 (the difference and its norm are
+    // formed by the second hop)
     qcdw_status true_schur_residual(std::vector<double>& rr)
     {
-        for (int k = 0; k < nprob; k++) {
-            const qcdw_op* op = ops[k];
-            HIPCHK(ctx, matpc(s, op, view(op, F64), at(W.xhi, k), at(W.tmp64, k), W.tmpo64.p, RED_NONE, nullptr,
-                              nullptr, nullptr));
-        }
-        HIPCHK(ctx, launch_xmy_norm2(s, F64, F64, W.bhat.p, W.tmp64.p, W.rhi.p, n0(), (double*)W.partials.p,
-                                     (double*)W.dres.p, nprob, map, nmax));
+        double* part = (double*)W.partials.p;
+        int nb = 0;
+        HIPCHK(ctx, hop64(EPI_CLOV, RED_NONE, 1, W.xhi.p, W.tmp64.p, nullptr, nullptr, 0, 0.0));
+        HIPCHK(ctx, hop64(EPI_CLOV_RESID, RED_NORM, 0, W.tmp64.p, W.rhi.p, W.xhi.p, W.bhat.p, 2, 0.0, nullptr, part,
+                          &nb));
+        HIPCHK(ctx, launch_sum_hop_norms(s, part, nullptr, nb, nb, nbs, (double*)W.dres.p, nprob));
         return read_doubles(rr);
     }
 
-    // x_o = A_oo^-1 b_o + kappa A_oo^-1 H_oe x_e for problem k into tmpo64, then the FP64
-    // full-lattice residual ||b - M x||^2 of that problem
-    qcdw_status full_residual(int k, double& r2)
+    // For the problems in `want`: x_o = A_oo^-1 b_o + kappa A_oo^-1 H_oe x_e into tmp64, and the FP64
+    // full-lattice residual r2[k] = ||b - M x||^2; (M x)_p = A_pp x_p - kappa H x_{1-p} is compared with b in
+    // the hop's registers
+    qcdw_status full_residual(const std::vector<char>& want, std::vector<double>& r2)
     {
-        const qcdw_op* op = ops[k];
-        const PrecView v64 = view(op, F64);
-        const Geom& g = op->g;
-        HopArgs a = hop_args(g, 1);
-        a.psi = at(W.xhi, k);
-        a.out = W.tmpo64.p;
-        a.gauge = v64.gauge;
-        a.clov = v64.Ainv[1];
-        a.y = at(W.yo, k);
-        a.a = -op->kappa;
-        HIPCHK(ctx, launch_hop(s, F64, v64.recon, EPI_CLOV_XPAY, RED_NONE, a));
-        r2 = 0;
-        for (int p = 0; p < 2; p++) {
-            HopArgs m = hop_args(g, p);  // (M x)_p = A_pp x_p - kappa H x_{1-p}
-            m.psi = p == 0 ? W.tmpo64.p : at(W.xhi, k);
-            m.out = W.tmp64.p;
-            m.gauge = v64.gauge;
-            m.clov = op->A64[p].p;
-            m.y = p == 0 ? at(W.xhi, k) : W.tmpo64.p;
-            m.a = op->kappa;
-            HIPCHK(ctx, launch_hop(s, F64, v64.recon, EPI_XPAY_CLOVY, RED_NONE, m));
-            HIPCHK(ctx, launch_xmy_norm2(s, F64, F64, p == 0 ? at(W.be, k) : at(W.bo, k), W.tmp64.p, nullptr, len[k],
-                                         (double*)W.partials.p, (double*)W.dres.p + p));
+        double *p0 = (double*)W.partials.p, *p1 = p0 + 3L * nprob * part_stride();
+        const Scal* only = nullptr;
+        if (std::find(want.begin(), want.end(), 0) != want.end()) {
+            std::vector<Scal> skip(nprob);  // the second half of the scalar buffer
+            for (int k = 0; k < nprob; k++) skip[k].flags = want[k] ? 0 : FLAG_CONV;
+            Scal* d = (Scal*)W.scal.p + MAX_BATCH;
+            HIPCHK(ctx, hipMemcpyAsync(d, skip.data(), nprob * sizeof(Scal), hipMemcpyHostToDevice, s));
+            HIPCHK(ctx, hipStreamSynchronize(s));
+            only = d;
         }
-        HIPCHK(ctx, hipMemcpyAsync(ctx->host_d, W.dres.p, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(ctx, hipStreamSynchronize(s));
-        r2 = ctx->host_d[0] + ctx->host_d[1];
-        return QCDW_OK;
+        int nb = 0;
+        HIPCHK(ctx, hop64(EPI_CLOV_XPAY, RED_NONE, 1, W.xhi.p, W.tmp64.p, W.yo.p, nullptr, 1, -1.0, only));
+        HIPCHK(ctx, hop64(EPI_XPAY_CLOVY, RED_DIST, 0, W.tmp64.p, nullptr, W.xhi.p, W.be.p, 1, 1.0, only, p0, &nb));
+        HIPCHK(ctx, hop64(EPI_XPAY_CLOVY, RED_DIST, 1, W.xhi.p, nullptr, W.tmp64.p, W.bo.p, 1, 1.0, only, p1, &nb));
+        HIPCHK(ctx, launch_sum_hop_norms(s, p0, p1, nb, nb, nbs, (double*)W.dres.p, nprob));
+        return read_doubles(r2);
     }
 
     qcdw_status ensure_workspace(int kprec, int maxiter)
@@ -879,11 +930,10 @@ struct Solver {
         for (DevBuf* b : all) before.push_back(b->p);
         DevBuf* stacked64[] = {&W.be, &W.bo, &W.yo, &W.ye, &W.bhat, &W.xhi, &W.rhi, &W.tmp64};
         for (DevBuf* b : stacked64) HIPCHK(ctx, b->alloc((size_t)total * 16));
-        HIPCHK(ctx, W.tmpo64.alloc((size_t)nmax * 16));
         for (auto& b : W.kr) HIPCHK(ctx, b.alloc((size_t)total * cplx_bytes(kprec)));
         if (kprec != F64) HIPCHK(ctx, W.xlo.alloc((size_t)total * 8));
         HIPCHK(ctx, W.partials.alloc(2 * 3UL * nprob * part_stride() * sizeof(double)));
-        HIPCHK(ctx, W.scal.alloc(MAX_BATCH * sizeof(Scal)));
+        HIPCHK(ctx, W.scal.alloc(2 * MAX_BATCH * sizeof(Scal)));
         HIPCHK(ctx, W.dres.alloc(MAX_BATCH * sizeof(double)));
         HIPCHK(ctx, W.coef.alloc(2 * MAX_BATCH * sizeof(double)));
         HIPCHK(ctx, W.hist.alloc((size_t)nprob * ((size_t)maxiter + 2) * sizeof(double)));
@@ -992,15 +1042,8 @@ qcdw_status solve(Solver& S, const void* const* bs, void* const* xs, const qcdw_
         // y_o = A_oo^-1 b_o ; y_e = A_ee^-1 b_e ; bhat = y_e + kappa A_ee^-1 H_eo y_o
         HIPCHK(ctx, launch_clov_apply_internal(s, F64, g, v64.Ainv[1], S.at(W.bo, k), S.at(W.yo, k)));
         HIPCHK(ctx, launch_clov_apply_internal(s, F64, g, v64.Ainv[0], S.at(W.be, k), S.at(W.ye, k)));
-        HopArgs a = hop_args(g, 0);
-        a.psi = S.at(W.yo, k);
-        a.out = S.at(W.bhat, k);
-        a.gauge = v64.gauge;
-        a.clov = v64.Ainv[0];
-        a.y = S.at(W.ye, k);
-        a.a = -op->kappa;
-        HIPCHK(ctx, launch_hop(s, F64, v64.recon, EPI_CLOV_XPAY, RED_NONE, a));
     }
+    HIPCHK(ctx, S.hop64(EPI_CLOV_XPAY, RED_NONE, 0, W.yo.p, W.bhat.p, W.ye.p, nullptr, 1, -1.0));
     CHK(S.tune(kprec));
 
     // ---- outer loop: Krylov cycles with FP64 residual recomputation -----
@@ -1043,6 +1086,11 @@ qcdw_status solve(Solver& S, const void* const* bs, void* const* xs, const qcdw_
 
     while (true) {
         bool pending = false;
+        std::vector<char> reached(nprob, 0);
+        for (int k = 0; k < nprob; k++)
+            reached[k] = !done[k] && std::isfinite(rr_hi[k]) && std::sqrt(rr_hi[k]) <= target[k];
+        std::vector<double> r2;
+        if (std::find(reached.begin(), reached.end(), 1) != reached.end()) CHK(S.full_residual(reached, r2));
         for (int k = 0; k < nprob; k++) {
             if (done[k]) continue;
             if (!std::isfinite(rr_hi[k])) {
@@ -1050,16 +1098,14 @@ qcdw_status solve(Solver& S, const void* const* bs, void* const* xs, const qcdw_
                 done[k] = 1;
                 continue;
             }
-            if (std::sqrt(rr_hi[k]) <= target[k]) {
-                double r2;
-                CHK(S.full_residual(k, r2));
-                true_res[k] = std::sqrt(r2) / bnorm[k];
+            if (reached[k]) {
+                true_res[k] = std::sqrt(r2[k]) / bnorm[k];
                 if (true_res[k] <= prm.tol) {
                     status[k] = QCDW_OK;
                     done[k] = 1;
                     const Geom& g = S.ops[k]->g;
                     HIPCHK(ctx, launch_unpack_spinor(s, F64, g, S.at(W.xhi, k), 0, xs[k], 1.0));
-                    HIPCHK(ctx, launch_unpack_spinor(s, F64, g, W.tmpo64.p, 1, xs[k], 1.0));
+                    HIPCHK(ctx, launch_unpack_spinor(s, F64, g, S.at(W.tmp64, k), 1, xs[k], 1.0));
                     continue;
                 }
                 target[k] *= 0.5 * prm.tol / true_res[k];  // tighten and keep iterating
@@ -1190,14 +1236,16 @@ qcdw_status solve(Solver& S, const void* const* bs, void* const* xs, const qcdw_
     }
 
     // ---- unfinished problems: best iterate and its true residual ----------
+    std::vector<char> left(nprob);
+    for (int k = 0; k < nprob; k++) left[k] = status[k] != QCDW_OK && status[k] != QCDW_ENAN;
+    std::vector<double> left_r2;
+    if (std::find(left.begin(), left.end(), 1) != left.end()) CHK(S.full_residual(left, left_r2));
     for (int k = 0; k < nprob; k++) {
-        if (status[k] == QCDW_OK || status[k] == QCDW_ENAN) continue;
-        double r2;
-        CHK(S.full_residual(k, r2));
-        true_res[k] = std::sqrt(r2) / bnorm[k];
+        if (!left[k]) continue;
+        true_res[k] = std::sqrt(left_r2[k]) / bnorm[k];
         const Geom& g = S.ops[k]->g;
         HIPCHK(ctx, launch_unpack_spinor(s, F64, g, S.at(W.xhi, k), 0, xs[k], 1.0));
-        HIPCHK(ctx, launch_unpack_spinor(s, F64, g, W.tmpo64.p, 1, xs[k], 1.0));
+        HIPCHK(ctx, launch_unpack_spinor(s, F64, g, S.at(W.tmp64, k), 1, xs[k], 1.0));
     }
     HIPCHK(ctx, hipStreamSynchronize(s));
     // the iterated-residual history of each problem, written by the device at iterations 1..iters
@@ -1306,7 +1354,10 @@ extern "C" qcdw_status qcdw_batch_create(qcdw_ctx* ctx, int n, qcdw_op* const op
             BatchEntry& e = pr == 0 ? t64[k] : tlo[k];
             const PrecView v = view(op, pr == 0 ? F64 : op->inner);
             e.g = op->g;
+            e.kappa = op->kappa;
             e.kappa2 = op->kappa * op->kappa;
+            e.a64[0] = op->A64[0].p;
+            e.a64[1] = op->A64[1].p;
             e.gauge = v.gauge;
             e.clov[0] = v.Ainv[0];
             e.clov[1] = v.Ainv[1];

@@ -65,6 +65,17 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double* partials, in
     block_sum_store<K>(v, out + (long)blockIdx.x * K);
 }
 
+// one block per problem: the first of the three doubles of each hop partial (launch_sum_hop_norms)
+__global__ __launch_bounds__(256) void k_sum_hop_norms(const double* p0, const double* p1, int nb, int stride,
+                                                       const int* nbs, double* out)
+{
+    const long at = 3L * blockIdx.x * stride;
+    const int n = nbs ? nbs[blockIdx.x] : nb;
+    double v[1] = {0.0};
+    for (int b = threadIdx.x; b < n; b += 256) v[0] += p1 ? p0[at + 3L * b] + p1[at + 3L * b] : p0[at + 3L * b];
+    block_sum_store<1>(v, out + blockIdx.x);
+}
+
 // out = scale_y in for RHS y (scales: per-RHS device array, or nullptr for `scale`)
 template <class PI, class PO>
 __global__ __launch_bounds__(256) void k_convert(const void* in, void* out, long n, double scale,
@@ -568,6 +579,13 @@ hipError_t launch_xmy_norm2(hipStream_t s, int prec_b, int prec_y, const void* b
     else return hipErrorInvalidValue;
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_sum_partials<1>, dim3(nrhs), dim3(256), 0, s, partials, nb, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_hop_norms(hipStream_t s, const double* p0, const double* p1, int nb, int stride, const int* nbs,
+                                double* out, int nprob)
+{
+    hipLaunchKernelGGL(k_sum_hop_norms, dim3(nprob), dim3(256), 0, s, p0, p1, nb, stride, nbs, out);
     return hipGetLastError();
 }
 

@@ -47,11 +47,13 @@
 namespace qcdw {
 
 // Gather of the lane partial sums (lane q finishes spin q), epilogue, store, and
-// this site's contribution to the fused reduction (added to v).
-template <class P, int EPI, int RED>
+// this site's contribution to the fused reduction (added to v).  given: the caller's clover window, or
+// nullptr to load it here.
+template <class P, int EPI, int RED, bool GIVEN = false>
 __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool valid, int q,
                                            const cx<typename P::real> (&acc_u)[3],
-                                           const cx<typename P::real> (&acc_l)[3], double (&v)[3])
+                                           const cx<typename P::real> (&acc_l)[3], double (&v)[3],
+                                           const typename P::real* given = nullptr)
 {
     using T = typename P::real;
     const long Vh = a.g.Vh;
@@ -66,10 +68,16 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
 
     cx<T> outv[3];
     cx<T> yv[3];
-    constexpr bool XPAY = EPI == EPI_CLOV_XPAY || EPI == EPI_CLOV_XPAY_G5CLOV;
+    constexpr bool XPAY = EPI == EPI_CLOV_XPAY || EPI == EPI_CLOV_XPAY_G5CLOV || EPI == EPI_CLOV_RESID;
+    constexpr bool DIST = RED == RED_DIST;  // out is compared with w, not stored
     if constexpr (XPAY || EPI == EPI_XPAY_CLOVY || EPI == EPI_XPAY_G5_SHIFT || RED == RED_TS) {
 #pragma unroll
         for (int c = 0; c < 3; c++) yv[c] = valid ? P::ld(a.y, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
+    }
+    cx<T> wv[3];
+    if constexpr (EPI == EPI_XPAY_G5_SHIFT || EPI == EPI_CLOV_RESID || DIST) {
+#pragma unroll
+        for (int c = 0; c < 3; c++) wv[c] = valid ? P::ld(a.w, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
     }
     if constexpr (EPI == EPI_NONE) {
 #pragma unroll
@@ -77,13 +85,13 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
     } else if constexpr (EPI == EPI_XPAY_G5_SHIFT) {
         const T aa = q < 2 ? (T)a.a : -(T)a.a, sh = (T)a.shift;
 #pragma unroll
-        for (int c = 0; c < 3; c++) {
-            const cx<T> wv = valid ? P::ld(a.w, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
-            outv[c] = (yv[c] - aa * res[c]) + sh * wv;
-        }
+        for (int c = 0; c < 3; c++) outv[c] = (yv[c] - aa * res[c]) + sh * wv[c];
     } else {
         T win[27];
-        if constexpr (QCDW_WIN_SHARE != 0) {
+        if constexpr (GIVEN) {
+#pragma unroll
+            for (int e = 0; e < 27; e++) win[e] = given[e];
+        } else if constexpr (QCDW_WIN_SHARE != 0) {
             load_window_shared<P>(a.clov, Vh, site, q, valid, win);
         } else if (valid) {
             load_window<P>(a.clov, Vh, site, q, win);
@@ -111,6 +119,10 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
 #pragma unroll
                 for (int c = 0; c < 3; c++) outv[c] = yv[c] - aa * br[c];
             }
+            if constexpr (EPI == EPI_CLOV_RESID) {
+#pragma unroll
+                for (int c = 0; c < 3; c++) outv[c] = wv[c] - outv[c];
+            }
             if constexpr (EPI == EPI_CLOV_XPAY_G5CLOV) {
                 cx<T> oo[3], b2[3];
 #pragma unroll
@@ -129,7 +141,7 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
     // vectors it reads back
 #pragma unroll
     for (int c = 0; c < 3; c++) outv[c] = P::rt(outv[c]);
-    if (valid) {
+    if (valid && !DIST) {
 #pragma unroll
         for (int c = 0; c < 3; c++) P::st(a.out, sp_idx(q, site, c, Vh), outv[c]);
     }
@@ -140,9 +152,12 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
             for (int c = 0; c < 3; c++) {
                 const cx<T> o = outv[c];
                 if constexpr (RED == RED_WDOT) {
-                    const cx<T> wv = P::ld(a.w, sp_idx(q, site, c, Vh));
-                    v[0] += (double)wv.re * o.re + (double)wv.im * o.im;
-                    v[1] += (double)wv.re * o.im - (double)wv.im * o.re;
+                    const cx<T> wd = P::ld(a.w, sp_idx(q, site, c, Vh));
+                    v[0] += (double)wd.re * o.re + (double)wd.im * o.im;
+                    v[1] += (double)wd.re * o.im - (double)wd.im * o.re;
+                } else if constexpr (RED == RED_NORM || DIST) {
+                    const cx<T> e = DIST ? wv[c] - o : o;
+                    v[0] += (double)e.re * e.re + (double)e.im * e.im;
                 } else {
                     v[0] += (double)o.re * yv[c].re + (double)o.im * yv[c].im;
                     v[1] += (double)o.re * yv[c].im - (double)o.im * yv[c].re;
@@ -345,6 +360,107 @@ __global__ __launch_bounds__(256) void hop_rhs_kernel(HopArgs a, const Scal* S)
     hop_tile<P, 6, EPI, RED>(b, tile, a.partials + 3 * ((long)r * hop_blocks(a.g.Vh) + tile));
 }
 
+// FP64 hop of several right-hand sides of one operator (source preparation and residuals of a multi-RHS solve):
+// a thread group takes RHS64 of them, so that a link and the clover window are loaded once for all of these, and
+// the groups of one tile run back to back on one XCD (links re-read from its L2).  Bound by the address path: the
+// 48-byte spins of a wave's 16 sites cost nearly one cache access per lane and load.  M_hat of 12 right-hand sides
+// at 24^3x64, first hop + second: launches per right-hand side 2.05 + 2.28 ms and 0.6 ms for the residual and its
+// norm; one launch over single ones 1.61 + 1.97 ms (residual included); 2, 3, 4, 6 of them per group in slice order
+// 3.51, 3.16, 3.15, 3.12 ms, and 4 in groups of 18 tiles 2.90 ms (6 there 2.88, with half the waves).
+constexpr int RHS64 = 4;
+template <int R, int EPI, int RED>
+__global__ __launch_bounds__(256, 2) void hop_rhs64_kernel(HopArgs a, const Scal* S)
+{
+    using P = P64;
+    const Geom g = a.g;
+    const int ng = (a.nrhs + RHS64 - 1) / RHS64, nblk = gridDim.x / ng;
+    const int logical = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = logical / ng, r0 = (logical - tile * ng) * RHS64;
+    bool act[RHS64], any = false;  // uniform
+#pragma unroll
+    for (int j = 0; j < RHS64; j++) {
+        act[j] = r0 + j < a.nrhs && !(S && S[r0 + j].flags);
+        any = any || act[j];
+    }
+    if (!any) return;
+    int site = tile * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+    bool valid = site < g.Vh;
+    if (a.cgroup > 0) {  // slice-group order, as in the single-RHS hop_kernel
+        const int G = a.cgroup, St = g.Lxh * g.Ly * g.Lz;
+        const int grp = tile / (G * g.Lt), rr = tile - grp * G * g.Lt;
+        const int t = rr / G, c = (grp * G + (rr - t * G)) * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+        site = t * St + c;
+        valid = c < St;
+    }
+    const int q = threadIdx.x & 3, gq = q >> 1, k = q & 1;
+    const int su = k, sl = gq == 0 ? 3 - k : 2 + k;
+    const long field = 12L * g.Vh;
+    cx<double> acc_u[RHS64][3], acc_l[RHS64][3];
+#pragma unroll
+    for (int j = 0; j < RHS64; j++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) acc_u[j][c] = acc_l[j][c] = {0.0, 0.0};
+    double win[27];
+    if (valid) {
+        LaneHops<double, R> L;
+        lane_hops<double, R, link_soa_for(P::cbytes)>(g, site, a.parity, q, L);
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            cx<double> u[9];
+            load_link<P, R>(a.gauge, L.loff[h], L.lstr, u);
+#pragma unroll
+            for (int j = 0; j < RHS64; j++) {
+                // a skipped right-hand side's place is computed too and dropped (no branch around the loads)
+                const int r = r0 + j < a.nrhs ? r0 + j : a.nrhs - 1;
+                cx<double> pu[3], pl[3], hv[3];
+                load_pair<P>((const char*)a.psi + r * field * P::cbytes, g.Vh, su, sl, L.nbh[h], pu, pl);
+                project<true>(pu, pl, L.cs[h], h < 2, hv);
+                hop_rows<true>(u, h & 1, h < 2, L.fsg[h], L.cs[h], hv, acc_u[j], acc_l[j]);
+            }
+        }
+    }
+    load_window_shared<P>(a.clov, g.Vh, site, q, valid, win);
+#pragma unroll
+    for (int j = 0; j < RHS64; j++) {
+        if (!act[j]) continue;
+        const long off = (r0 + j) * field * P::cbytes;
+        HopArgs b = a;
+        b.out = (char*)a.out + off;
+        if (a.y) b.y = (const char*)a.y + off;
+        if (a.w) b.w = (const char*)a.w + off;
+        double v[3] = {0.0, 0.0, 0.0};
+        hop_finish<P, EPI, RED, true>(b, site, valid, q, acc_u[j], acc_l[j], v, win);
+        if constexpr (RED != RED_NONE) {
+            block_sum_store<3>(v, a.partials + 3 * ((long)(r0 + j) * nblk + tile));
+            __syncthreads();
+        }
+    }
+}
+
+template <int R>
+static hipError_t launch_rhs64(hipStream_t s, int epi, int red, const HopArgs& a, const Scal* S)
+{
+    const dim3 grid(hop_blocks_nt(a.g, 1, a.cgroup) * ((a.nrhs + RHS64 - 1) / RHS64)), block(256);
+#define QCDW_RHS64_CASE(E, D)                                                         \
+    if (epi == E && red == D) {                                                       \
+        hipLaunchKernelGGL((hop_rhs64_kernel<R, E, D>), grid, block, 0, s, a, S);     \
+        return hipGetLastError();                                                     \
+    }
+    QCDW_RHS64_CASE(EPI_CLOV, RED_NONE)
+    QCDW_RHS64_CASE(EPI_CLOV_XPAY, RED_NONE)
+    QCDW_RHS64_CASE(EPI_CLOV_RESID, RED_NORM)
+    QCDW_RHS64_CASE(EPI_XPAY_CLOVY, RED_DIST)
+#undef QCDW_RHS64_CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_hop_rhs64(hipStream_t s, int recon, int epi, int red, const HopArgs& a, const Scal* S)
+{
+    if (a.g.Vh <= 0 || a.nrhs <= 0) return hipSuccess;
+    if (!hop_cgroup_fits(a.g, a.cgroup)) return hipErrorInvalidValue;
+    return recon == 18 ? launch_rhs64<9>(s, epi, red, a, S) : launch_rhs64<6>(s, epi, red, a, S);
+}
+
 // Batched hop: a persistent grid walks the tiles of every problem in a device
 // table (problems of different lattice sizes and kappas).  Tile t belongs to
 // the problem whose [tile0, tile0 + ntiles) contains it; finished problems
@@ -365,12 +481,12 @@ __global__ __launch_bounds__(256) void hop_batch_kernel(BatchHopArgs b)
         a.g = e.g;
         a.parity = b.parity;
         a.gauge = e.gauge;
-        a.clov = e.clov[b.parity];
+        a.clov = EPI == EPI_XPAY_CLOVY ? e.a64[b.parity] : e.clov[b.parity];
         a.psi = (const char*)b.psi + e.off * P::cbytes;
         a.out = (char*)b.out + e.off * P::cbytes;
         a.y = b.y ? (const char*)b.y + e.off * P::cbytes : nullptr;
         a.w = b.w ? (const char*)b.w + e.off * P::cbytes : nullptr;
-        a.a = b.use_kappa2 ? e.kappa2 : b.a;
+        a.a = b.kpow == 2 ? e.kappa2 : b.kpow == 1 ? b.a * e.kappa : b.a;
         a.nrhs = 1;
         const int tile = t - e.tile0;
         hop_tile<P, 6, EPI, RED>(a, tile, b.partials + 3 * ((long)lo * b.nbmax + tile));
@@ -403,6 +519,8 @@ static hipError_t launch_hop_nt(hipStream_t s, int epi, int red, const HopArgs& 
     QCDW_HOP_CASE(EPI_CLOV_XPAY, RED_TS)
     QCDW_HOP_CASE(EPI_XPAY_CLOVY, RED_NONE)
     if constexpr (P::cbytes == 16) {
+        QCDW_HOP_CASE(EPI_CLOV_RESID, RED_NORM)
+        QCDW_HOP_CASE(EPI_XPAY_CLOVY, RED_DIST)
         QCDW_HOP_CASE(EPI_CLOV_XPAY_G5CLOV, RED_NONE)
         QCDW_HOP_CASE(EPI_XPAY_G5_SHIFT, RED_WDOT)
     }
@@ -480,6 +598,11 @@ static hipError_t launch_batch_p(hipStream_t s, int epi, int red, const BatchHop
         else                                                                                             \
             hipLaunchKernelGGL((hop_batch_kernel<P, E, D>), dim3(grid), dim3(256), 0, s, b);             \
         return hipGetLastError();                                                                        \
+    }
+    if constexpr (P::cbytes == 16) {
+        QCDW_BATCH_CASE(EPI_CLOV_XPAY, RED_NONE)
+        QCDW_BATCH_CASE(EPI_CLOV_RESID, RED_NORM)
+        QCDW_BATCH_CASE(EPI_XPAY_CLOVY, RED_DIST)
     }
     QCDW_BATCH_CASE(EPI_CLOV, RED_NONE)
     QCDW_BATCH_CASE(EPI_CLOV_XPAY, RED_WDOT)

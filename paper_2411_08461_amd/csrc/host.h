@@ -244,7 +244,7 @@ using namespace qcdw_host;
 // Solver workspace: stacked/concatenated vectors of all problems of a solve,
 // scalars, partials, and the graphs captured over them.
 struct Workspace {
-    PoolBuf be, bo, yo, ye, bhat, xhi, rhi, tmp64, tmpo64;  // FP64, per problem
+    PoolBuf be, bo, yo, ye, bhat, xhi, rhi, tmp64;  // FP64, per problem (tmp64: odd sites)
     PoolBuf kr[7];  // r, r0, p, v, s, t, tmp_o in the Krylov precision
     PoolBuf xlo;    // FP32 correction (mixed precision)
     PoolBuf partials, scal, dres, hist, coef;

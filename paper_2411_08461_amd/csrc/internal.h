@@ -23,13 +23,17 @@ enum Epi {
     EPI_XPAY_CLOVY = 3,  // out = B y - a (H psi)
     // the normal operator's (FP64): M_hat with g5 A^-1 of its result, and the adjoint's last hop
     EPI_CLOV_XPAY_G5CLOV = 4,  // out = y - a B (H psi), out2 = g5 B out
-    EPI_XPAY_G5_SHIFT = 5      // out = y - a g5 (H psi) + shift w
+    EPI_XPAY_G5_SHIFT = 5,     // out = y - a g5 (H psi) + shift w
+    EPI_CLOV_RESID = 6         // out = w - (y - a C H psi)   (with RED_NORM)
 };
 // hop fused reductions (per-block partials)
 enum Red {
     RED_NONE = 0,
     RED_WDOT = 1,  // (w, out)              -> 2 doubles
-    RED_TS = 2     // (out, y), ||out||^2   -> 3 doubles
+    RED_TS = 2,    // (out, y), ||out||^2   -> 3 doubles
+    // FP64 residuals:
+    RED_NORM = 3,  // ||out||^2             -> 1 double
+    RED_DIST = 4   // ||w - out||^2, out is not stored -> 1 double
 };
 
 struct HopArgs {
@@ -57,7 +61,8 @@ struct HopArgs {
 // one problem of a batched solve (device table entry); reconstruct-12 operators
 struct BatchEntry {
     Geom g;
-    double kappa2;        // kappa^2 of this problem
+    double kappa, kappa2;  // kappa and kappa^2 of this problem
+    const void* a64[2];   // A per parity in FP64
     const void* gauge;    // links in the batch's Krylov precision
     const void* clov[2];  // A^-1 per parity, same precision
     long off;             // element offset (complex) of this problem in the concatenated vectors
@@ -72,7 +77,7 @@ struct BatchHopArgs {
     int total_tiles;
     int parity;
     int nbmax;           // partials stride per problem (tiles)
-    int use_kappa2;      // 1: xpay coefficient = kappa^2 of each problem, else `a`
+    int kpow;            // xpay coefficient: 2 kappa^2 of each problem, 1 `a` kappa, 0 `a`
     double a;
     const void* psi;     // concatenated vectors, problem k at element offset tab[k].off
     void* out;
@@ -168,6 +173,10 @@ inline int blas_blocks(long n)
 // ranges come from the map and nmax is the longest length.
 hipError_t launch_norm2(hipStream_t s, int prec, const void* x, long n, double* partials, double* out, int nrhs = 1,
                         const long2* map = nullptr, long nmax = 0);
+// out[k] = sum over b < nbs[k] (nb if nbs is null) of p0[k][b][0], plus the same of p1 unless null; the hops'
+// one-double partials, [problem][stride][3]
+hipError_t launch_sum_hop_norms(hipStream_t s, const double* p0, const double* p1, int nb, int stride, const int* nbs,
+                                double* out, int nprob);
 hipError_t launch_xmy_norm2(hipStream_t s, int prec_b, int prec_y, const void* b, const void* y, void* r, long n,
                             double* partials, double* out, int nrhs = 1, const long2* map = nullptr,
                             long nmax = 0);  // r = b - y (FP64 r), out = ||r||^2
@@ -221,6 +230,9 @@ hipError_t launch_hop_mrhs_mfma(hipStream_t s, int prec, int epi, int red, const
 // the same operation with one block per (tile, rhs), rhs fastest (links and clover re-read from L2)
 hipError_t launch_hop_rhs(hipStream_t s, int prec, int epi, int red, const HopArgs& a, const Scal* S,
                           hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// the FP64 hop of source preparation and residuals, several RHS per thread group (either reconstruction; EPI_CLOV, EPI_CLOV_XPAY,
+// EPI_CLOV_RESID with RED_NORM, EPI_XPAY_CLOVY with RED_DIST)
+hipError_t launch_hop_rhs64(hipStream_t s, int recon, int epi, int red, const HopArgs& a, const Scal* S);
 
 // learned preconditioner layers (activations [parity][channel][Vh][3], FP32/BF16 storage)
 // mfma: layers with a BF16 end mix channels on the BF16 matrix cores (k_net_layer_mfma)
