@@ -582,6 +582,12 @@ hipError_t launch_xmy_norm2(hipStream_t s, int prec_b, int prec_y, const void* b
     return hipGetLastError();
 }
 
+hipError_t launch_sum_partials(hipStream_t s, const double* partials, int nb, double* out)
+{
+    hipLaunchKernelGGL(k_sum_partials<1>, dim3(1), dim3(256), 0, s, partials, nb, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_sum_hop_norms(hipStream_t s, const double* p0, const double* p1, int nb, int stride, const int* nbs,
                                 double* out, int nprob)
 {

@@ -265,7 +265,12 @@ hipError_t launch_scale_inv_norm(hipStream_t s, const void* w, void* out, long n
 hipError_t launch_multidot(hipStream_t s, const void* V, long stride, int nvec, const void* w, long n,
                            double* partials, double* out);  // out[2i..] = (V_i, w); partials: 16 ceil(nvec/8) blocks
 hipError_t launch_multiaxpy(hipStream_t s, const void* V, long stride, int nvec, const double* c, void* w, long n,
-                            double sign);  // w += sign sum_i c_i V_i
+                            double sign, double* partials = nullptr,
+                            double* nrm2 = nullptr);  // w += sign sum_i c_i V_i [, nrm2 = ||w||^2]
+// w -= sum_i c_i V_i and out[2i..] = (V_i, w) of the result in one pass; at most 64 vectors
+hipError_t launch_multiaxpy_dot(hipStream_t s, const void* V, long stride, int nvec, const double* c, void* w, long n,
+                                double* partials, double* out);
+hipError_t launch_sum_partials(hipStream_t s, const double* partials, int nb, double* out);  // one double per block
 
 // pack / unpack between the paper layouts and the internal ones
 hipError_t launch_pack_spinor(hipStream_t s, int prec, const Geom& g, const void* paper, int parity, void* internal,

@@ -639,10 +639,8 @@ qcdw_status qcdw_host::fgmres_run(qcdw_op* op, const Precond* precond, const voi
             // device (dd[0..], dd[128..]), ||w||^2 lands in dd[256] and v_{j+1} = w / ||w|| is
             // formed on the device, so the step needs one host synchronisation
             HIPCHK(ctx, launch_multidot(s, V.p, n, j + 1, w.p, n, dpart, dd));
-            HIPCHK(ctx, launch_multiaxpy(s, V.p, n, j + 1, dd, w.p, n, -1.0));
-            HIPCHK(ctx, launch_multidot(s, V.p, n, j + 1, w.p, n, dpart, dd + 128));
-            HIPCHK(ctx, launch_multiaxpy(s, V.p, n, j + 1, dd + 128, w.p, n, -1.0));
-            HIPCHK(ctx, launch_norm2(s, F64, w.p, n, dpart, dd + 256));
+            HIPCHK(ctx, launch_multiaxpy_dot(s, V.p, n, j + 1, dd, w.p, n, dpart, dd + 128));
+            HIPCHK(ctx, launch_multiaxpy(s, V.p, n, j + 1, dd + 128, w.p, n, -1.0, dpart, dd + 256));
             HIPCHK(ctx, launch_scale_inv_norm(s, w.p, Vk(j + 1), n, dd + 256));
             CHK(rd(257, ctx->host_d));
             const double* hc = ctx->host_d;
