@@ -172,7 +172,6 @@ struct Geom {
     int Vh;    // sites per parity
     int t_bc;  // +1 / -1
     double xs = 1.0;  // weight of the spatial hops (nu / xi_0 for the anisotropic action, Sec. III.B)
-    uint32_t inv[3] = {0, 0, 0};  // multipliers of Lxh, Ly, Lz: n / d = high 32 bits of n inv (0: divide)
 };
 
 // real index of entry m (reordered packing) of chirality block chi at `site` in an internal
@@ -229,21 +228,15 @@ __host__ __device__ inline long link_base(int mu, int p, long site, long Vh, int
 }
 __host__ __device__ inline long link_stride(long Vh, bool soa) { return soa ? Vh : 1; }
 
-// n / d by the multiplier of d (Geom::inv): a dozen instructions of a runtime division in one
-__device__ __forceinline__ int quotient(int n, int d, uint32_t inv)
-{
-    return inv ? (int)__umulhi((uint32_t)n, inv) : n / d;
-}
-
 // coordinates of checkerboard index i on parity p
 __device__ __forceinline__ void site_coords(const Geom& g, int i, int p, int& x, int& y, int& z, int& t)
 {
-    int r = quotient(i, g.Lxh, g.inv[0]);
-    const int xh = i - r * g.Lxh;
-    int r2 = quotient(r, g.Ly, g.inv[1]);
-    y = r - r2 * g.Ly;
-    t = quotient(r2, g.Lz, g.inv[2]);
-    z = r2 - t * g.Lz;
+    int xh = i % g.Lxh;
+    int r = i / g.Lxh;
+    y = r % g.Ly;
+    r /= g.Ly;
+    z = r % g.Lz;
+    t = r / g.Lz;
     x = 2 * xh + ((p + y + z + t) & 1);
 }
 

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void k_dslash_paper(Geom g, const double2* __r
         }
         return;
     }
-    const int su = q, sl = gq == 0 ? 3 - q : q - 2;
+    const int su = k, sl = gq == 0 ? 3 - k : 2 + k;
     const double2* other = psi + (long)(1 - p) * Vh * 12;
     cx<double> acc_u[3], acc_l[3];
 #pragma unroll
@@ -126,7 +126,9 @@ __global__ __launch_bounds__(256) void k_dslash_paper(Geom g, const double2* __r
     cx<double> res[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) {  // lane q finishes spin q (partner lane: q < 2 ? q + 2 : 3 - q)
-        res[c] = acc_u[c] + quad_dpp_cx<QUAD_PARTNER>(acc_l[c]);
+        const cx<double> mine = gq == 0 ? acc_u[c] : acc_l[c];
+        const cx<double> theirs = gq == 0 ? acc_l[c] : acc_u[c];
+        res[c] = mine + quad_dpp_cx<QUAD_PARTNER>(theirs);
     }
     if constexpr (CLOV) {
         cx<double> y[3], ox[3], by[3];

@@ -46,16 +46,10 @@
 
 namespace qcdw {
 
-// Whether lanes past the last site are branched round.  In FP64 the branch holds the loads of one hop to its place
-// (without it the scheduler brings all of them forward: the 24^3x64 hop 172 -> 190 us, the four right-hand sides of
-// hop_rhs64_kernel spill); in the other types the selects and moves behind it cost 12 % of the instructions.
-template <class P, bool F>
-constexpr bool BRANCHES = P::cbytes == 16 || !F;
-
 // Gather of the lane partial sums (lane q finishes spin q), epilogue, store, and
 // this site's contribution to the fused reduction (added to v).  given: the caller's clover window, or
 // nullptr to load it here.
-template <class P, int EPI, int RED, bool F, bool GIVEN = false>
+template <class P, int EPI, int RED, bool GIVEN = false>
 __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool valid, int q,
                                            const cx<typename P::real> (&acc_u)[3],
                                            const cx<typename P::real> (&acc_l)[3], double (&v)[3],
@@ -63,13 +57,13 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
 {
     using T = typename P::real;
     const long Vh = a.g.Vh;
-    // lanes past the last site store nothing; below FP64 they read site 0, without branches (BRANCHES)
-    const bool in = BRANCHES<P, F> ? valid : true;
-    const int at = in ? (valid ? site : 0) : site;
+    const int gq = q >> 1;
     cx<T> res[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) {  // partner lane: q < 2 ? q + 2 : 3 - q
-        res[c] = acc_u[c] + quad_dpp_cx<QUAD_PARTNER>(acc_l[c]);
+        const cx<T> mine = gq == 0 ? acc_u[c] : acc_l[c];
+        const cx<T> theirs = gq == 0 ? acc_l[c] : acc_u[c];
+        res[c] = mine + quad_dpp_cx<QUAD_PARTNER>(theirs);
     }
 
     cx<T> outv[3];
@@ -78,12 +72,12 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
     constexpr bool DIST = RED == RED_DIST;  // out is compared with w, not stored
     if constexpr (XPAY || EPI == EPI_XPAY_CLOVY || EPI == EPI_XPAY_G5_SHIFT || RED == RED_TS) {
 #pragma unroll
-        for (int c = 0; c < 3; c++) yv[c] = in ? P::ld(a.y, sp_idx(q, at, c, Vh)) : cx<T>{T(0), T(0)};
+        for (int c = 0; c < 3; c++) yv[c] = valid ? P::ld(a.y, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
     }
     cx<T> wv[3];
     if constexpr (EPI == EPI_XPAY_G5_SHIFT || EPI == EPI_CLOV_RESID || DIST) {
 #pragma unroll
-        for (int c = 0; c < 3; c++) wv[c] = in ? P::ld(a.w, sp_idx(q, at, c, Vh)) : cx<T>{T(0), T(0)};
+        for (int c = 0; c < 3; c++) wv[c] = valid ? P::ld(a.w, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
     }
     if constexpr (EPI == EPI_NONE) {
 #pragma unroll
@@ -98,9 +92,9 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
 #pragma unroll
             for (int e = 0; e < 27; e++) win[e] = given[e];
         } else if constexpr (QCDW_WIN_SHARE != 0) {
-            load_window_shared<P>(a.clov, Vh, at, q, in, win);
-        } else if (in) {
-            load_window<P>(a.clov, Vh, at, q, win);
+            load_window_shared<P>(a.clov, Vh, site, q, valid, win);
+        } else if (valid) {
+            load_window<P>(a.clov, Vh, site, q, win);
         } else {
 #pragma unroll
             for (int e = 0; e < 27; e++) win[e] = T(0);
@@ -187,15 +181,15 @@ __device__ __forceinline__ void hop_site(const HopArgs& a, int site, bool valid,
     using T = typename P::real;
     const Geom g = a.g;
     const int q = threadIdx.x & 3;
-    const int gq = q >> 1;
-    const int su = q, sl = gq == 0 ? 3 - q : q - 2;
+    const int gq = q >> 1, k = q & 1;
+    const int su = k, sl = gq == 0 ? 3 - k : 2 + k;
 
     cx<T> acc_u[3], acc_l[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) acc_u[c] = acc_l[c] = {T(0), T(0)};
-    if (!BRANCHES<P, F> || valid) {
+    if (valid) {
         LaneHops<T, R> L;
-        lane_hops<T, R, link_soa_for(P::cbytes)>(g, valid ? site : 0, a.parity, q, L);
+        lane_hops<T, R, link_soa_for(P::cbytes)>(g, site, a.parity, q, L);
 #pragma unroll
         for (int h = 0; h < 4; h++) {
             cx<T> pu[3], pl[3], hv[3];
@@ -215,7 +209,7 @@ __device__ __forceinline__ void hop_site(const HopArgs& a, int site, bool valid,
         }
     }
     double v[3] = {0.0, 0.0, 0.0};
-    hop_finish<P, EPI, RED, F>(a, site, valid, q, acc_u, acc_l, v);
+    hop_finish<P, EPI, RED>(a, site, valid, q, acc_u, acc_l, v);
     if constexpr (RED != RED_NONE) block_sum_store<3>(v, part);
 }
 
@@ -300,8 +294,8 @@ __global__ __launch_bounds__(256) QCDW_TKERNEL_ATTR void hop_tkernel(HopArgs a)
     const int q = threadIdx.x & 3;
     const int c = ct * 64 + (threadIdx.x >> 2);
     const bool valid = c < St;
-    const int gq = q >> 1;
-    const int su = q, sl = gq == 0 ? 3 - q : q - 2;
+    const int gq = q >> 1, k = q & 1;
+    const int su = k, sl = gq == 0 ? 3 - k : 2 + k;
     double v[3] = {0.0, 0.0, 0.0};
     cx<T> carry[3];  // t-lanes: projected backward half-spinor for the next step
 #pragma unroll
@@ -317,9 +311,9 @@ __global__ __launch_bounds__(256) QCDW_TKERNEL_ATTR void hop_tkernel(HopArgs a)
         cx<T> acc_u[3], acc_l[3];
 #pragma unroll
         for (int cc = 0; cc < 3; cc++) acc_u[cc] = acc_l[cc] = {T(0), T(0)};
-        if (!BRANCHES<P, F> || valid) {
+        if (valid) {
             LaneHops<T, R> L;
-            lane_hops<T, R, link_soa_for(P::cbytes)>(g, valid ? site : 0, a.parity, q, L);
+            lane_hops<T, R, link_soa_for(P::cbytes)>(g, site, a.parity, q, L);
             cx<T> next[3];  // this step's forward t-neighbour, projected for the next step
 #pragma unroll
             for (int h = 0; h < 4; h++) {
@@ -341,7 +335,7 @@ __global__ __launch_bounds__(256) QCDW_TKERNEL_ATTR void hop_tkernel(HopArgs a)
                 for (int cc = 0; cc < 3; cc++) carry[cc] = next[cc];
             }
         }
-        hop_finish<P, EPI, RED, F>(a, site, valid, q, acc_u, acc_l, v);
+        hop_finish<P, EPI, RED>(a, site, valid, q, acc_u, acc_l, v);
     }
     if constexpr (RED != RED_NONE) block_sum_store<3>(v, a.partials + 3 * (long)blk);
 }
@@ -398,8 +392,8 @@ __global__ __launch_bounds__(256, 2) void hop_rhs64_kernel(HopArgs a, const Scal
         site = t * St + c;
         valid = c < St;
     }
-    const int q = threadIdx.x & 3, gq = q >> 1;
-    const int su = q, sl = gq == 0 ? 3 - q : q - 2;
+    const int q = threadIdx.x & 3, gq = q >> 1, k = q & 1;
+    const int su = k, sl = gq == 0 ? 3 - k : 2 + k;
     const long field = 12L * g.Vh;
     cx<double> acc_u[RHS64][3], acc_l[RHS64][3];
 #pragma unroll
@@ -435,7 +429,7 @@ __global__ __launch_bounds__(256, 2) void hop_rhs64_kernel(HopArgs a, const Scal
         if (a.y) b.y = (const char*)a.y + off;
         if (a.w) b.w = (const char*)a.w + off;
         double v[3] = {0.0, 0.0, 0.0};
-        hop_finish<P, EPI, RED, true, true>(b, site, valid, q, acc_u[j], acc_l[j], v, win);
+        hop_finish<P, EPI, RED, true>(b, site, valid, q, acc_u[j], acc_l[j], v, win);
         if constexpr (RED != RED_NONE) {
             block_sum_store<3>(v, a.partials + 3 * ((long)(r0 + j) * nblk + tile));
             __syncthreads();

@@ -3,12 +3,11 @@
 // decomposition, the projected hop, and the Hermitian clover rows.
 //
 // Lane q = 2 gq + k of a site handles directions mu = 2 gq and 2 gq + 1
-// (forward and backward) and only row q of the half-spinor that (1 -/+ g_mu)
-// projects onto: in the DeGrand-Rossi basis h_q = psi_q + c psi_l with a unit
-// coefficient c and the spin l that g_mu couples to q, 3 - q (mu = x, y) or
-// q - 2 (mu = z, t); W h_q adds to spin q and conj(c) W h_q to spin l (paper
-// Sec. III.B, Eq. "clover", the Wilson hopping term written out).  Every lane's
-// first accumulator is thus its own spin's, without a select.
+// (forward and backward) and only row k of the half-spinor that (1 -/+ g_mu)
+// projects onto: in the DeGrand-Rossi basis h_k = psi_k + c psi_l with a unit
+// coefficient c and l = 3 - k (mu = x, y) or 2 + k (mu = z, t); W h_k adds to
+// spin k and conj(c) W h_k to spin l (paper Sec. III.B, Eq. "clover", the
+// Wilson hopping term written out).
 #pragma once
 #include "internal.h"
 
@@ -25,21 +24,9 @@ __device__ __forceinline__ void load_link(const void* gauge, long off, long stri
 #pragma unroll
         for (int e = 0; e < 6; e++) u[e] = P::ld(gauge, off + e * stride);
         // third row of an SU(3) matrix: complex conjugate of row0 x row1
-        if constexpr (P::cbytes == 16) {
-            u[6] = conj(u[1] * u[5] - u[2] * u[4]);
-            u[7] = conj(u[2] * u[3] - u[0] * u[5]);
-            u[8] = conj(u[0] * u[4] - u[1] * u[3]);
-        } else {  // eight multiply-adds an entry instead of ten operations (in FP64 their longer chains cost 3 %)
-#pragma unroll
-            for (int c = 0; c < 3; c++) {
-                const cx<typename P::real> a0 = u[(c + 1) % 3], b0 = u[3 + (c + 2) % 3], a1 = u[(c + 2) % 3],
-                                           b1 = u[3 + (c + 1) % 3];
-                cx<typename P::real> w = a0 * b0;
-                w.re -= a1.re * b1.re, w.re += a1.im * b1.im;
-                w.im -= a1.re * b1.im, w.im -= a1.im * b1.re;
-                u[6 + c] = conj(w);
-            }
-        }
+        u[6] = conj(u[1] * u[5] - u[2] * u[4]);
+        u[7] = conj(u[2] * u[3] - u[0] * u[5]);
+        u[8] = conj(u[0] * u[4] - u[1] * u[3]);
     }
 }
 
@@ -186,7 +173,7 @@ __device__ __forceinline__ void lane_hops(const Geom& g, int site, int p, int q,
     L.lstr = link_stride(Vh, SOA);
     int x, y, z, t;
     site_coords(g, site, p, x, y, z, t);
-    const int xh = x >> 1;
+    const int xh = site % g.Lxh;
     const int Sy = g.Lxh, Sz = g.Lxh * g.Ly, St = g.Lxh * g.Ly * g.Lz;
 #pragma unroll
     for (int j = 0; j < 2; j++) {
@@ -205,7 +192,7 @@ __device__ __forceinline__ void lane_hops(const Geom& g, int site, int p, int q,
             } else {  // z
                 fwd = (z + 1 == g.Lz) ? site - (g.Lz - 1) * Sz : site + Sz;
                 bwd = (z == 0) ? site + (g.Lz - 1) * Sz : site - Sz;
-                c_s = k == 0 ? T(1) : T(-1);
+                c_s = k == 0 ? T(-1) : T(1);
             }
         } else {
             if (gq == 0) {  // y

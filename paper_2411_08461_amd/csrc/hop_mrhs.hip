@@ -104,6 +104,9 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
     const int gq = q >> 1;
     const long Vh = g.Vh;
     const long field = 12L * Vh;  // complex per RHS
+    // this lane's own spin and the one that its directions couple to it: row q of (1 -/+ gamma) psi, so that the sum
+    // for spin q collects in acc_u in every lane (for z and t that is the row l of hop_common.h, with the
+    // conjugate coefficient)
     const int su = q, sl = gq == 0 ? 3 - q : q - 2;
 
     // per-lane hop geometry, links (row 2 rebuilt once) and clover window, shared by all RHS
@@ -122,6 +125,7 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
 #pragma unroll
     for (int e = 0; e < 27; e++) win[e] = T(0);
     if (valid) lane_hops<T, 6, link_soa_for(P::cbytes)>(g, site, a.parity, q, L);
+    if (gq == 1) L.cs[0] = -L.cs[0], L.cs[1] = -L.cs[1];
     // Right-hand sides in flight ahead of the one that is computed: two in BF16 (a hop's words are replaced as soon
     // as they are read; 24 registers each, 30 with the epilogue's operands), one in FP16 (whose conversions take the
     // registers) and, without the epilogue's operands, in FP32; none in FP64.  The links leave room for two waves per

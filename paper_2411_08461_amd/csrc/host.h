@@ -213,9 +213,6 @@ inline qcdw_status check_lattice(qcdw_ctx* ctx, const qcdw_lattice* lat, Geom& g
     g.Lxh = g.Lx / 2;
     g.Vh = (int)(V / 2);
     g.t_bc = lat->t_bc;
-    const int dims[3] = {g.Lxh, g.Ly, g.Lz};
-    for (int k = 0; k < 3; k++)  // exact for every site index: (2^32 / d + 1) d exceeds 2^32 by at most d
-        g.inv[k] = dims[k] >= 2 && (uint64_t)g.Vh * dims[k] < (1ull << 32) ? (uint32_t)((1ull << 32) / dims[k]) + 1 : 0;
     return QCDW_OK;
 }
 
