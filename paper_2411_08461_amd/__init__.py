@@ -237,7 +237,62 @@ def _close_live_contexts():
 atexit.register(_close_live_contexts)
 
 
-class Context:
+class _Native:
+    """One native object: its handle and the objects that have to be destroyed before it.
+
+    Owners keep their children's records, and a record knows nothing of the Python object that shows
+    it, so the order of destruction holds however the Python objects die: when the collector takes a
+    cycle, it clears the weak references to the cycle's objects before any of their finalisers runs,
+    and it may finalise a context before its operators."""
+
+    def __init__(self, handle, destroy: str, rank: int = 0, owners=()):
+        self.handle, self.destroy, self.rank = handle, destroy, rank
+        self.children = []
+        self.owners = list(owners)
+        for o in self.owners:
+            o.children.append(self)
+
+    def close(self):
+        if self.handle is None:
+            return
+        # nets and batches reference operators, operators reference the context
+        for c in sorted(self.children, key=lambda c: c.rank):
+            c.close()
+        handle, self.handle = self.handle, None
+        getattr(load_library(), self.destroy)(handle)
+        for o in self.owners:
+            o.children.remove(self)
+        self.owners = []
+
+    def move(self, old, new):
+        """Owner `new` in the place of `old`."""
+        self.owners.remove(old)
+        old.children.remove(self)
+        self.owners.append(new)
+        new.children.append(self)
+
+
+class _Owned:
+    """What every object of the library has: a handle (None once closed) and its end."""
+
+    _native = None
+
+    @property
+    def handle(self):
+        return self._native.handle if self._native is not None else None
+
+    def close(self):
+        if self._native is not None:
+            self._native.close()
+
+    def __del__(self):
+        try:
+            self.close()
+        except Exception:
+            pass
+
+
+class Context(_Owned):
     """qcdw_ctx bound to one device and one HIP stream (torch's current one by default)."""
 
     def __init__(self, device: int = 0, stream=None):
@@ -248,33 +303,12 @@ class Context:
             stream = torch.cuda.current_stream(device)
         self.device = device
         self.stream = stream
-        self._children = weakref.WeakSet()  # objects that must be destroyed before the context
         h = ctypes.c_void_p()
         st = lib.qcdw_ctx_create(ctypes.byref(h), device, ctypes.c_void_p(stream.cuda_stream))
         if st != QCDW_OK:
             raise QcdwError(st, "qcdw_ctx_create failed")
-        self.handle = h
+        self._native = _Native(h, "qcdw_ctx_destroy")
         _live_contexts.add(self)
-
-    def _adopt(self, obj):
-        self._children.add(obj)
-
-    def close(self):
-        if getattr(self, "handle", None):
-            # nets and batches reference operators, operators reference the context
-            kids = list(self._children)
-            for rank in (0, 1, 2):
-                for k in kids:
-                    if getattr(k, "_rank", 2) == rank:
-                        k.close()
-            load_library().qcdw_ctx_destroy(self.handle)
-            self.handle = None
-
-    def __del__(self):
-        try:
-            self.close()
-        except Exception:
-            pass
 
 
 def qcdw_solver_params_default() -> qcdw_solver_params:
@@ -364,7 +398,7 @@ def qcdw_dslash_noalloc(ctx: Context, lat: qcdw_lattice, U, clover, psi, out, ka
     _check(ctx.handle, st)
 
 
-class Operator:
+class Operator(_Owned):
     """qcdw_op: packed links, clover inverse and solver workspace for one (U, kappa, csw)."""
 
     _rank = 2  # destroyed after the nets and batches that use it
@@ -391,22 +425,7 @@ class Operator:
                                                      float(kappa), xi_0, nu, csw_t, csw_r, self.inner, int(recon),
                                                      ctypes.byref(h))
         _check(ctx.handle, st)
-        self.handle = h
-        self._children = weakref.WeakSet()
-        ctx._adopt(self)
-
-    def close(self):
-        if getattr(self, "handle", None):
-            for k in list(self._children):
-                k.close()
-            load_library().qcdw_op_destroy(self.handle)
-            self.handle = None
-
-    def __del__(self):
-        try:
-            self.close()
-        except Exception:
-            pass
+        self._native = _Native(h, "qcdw_op_destroy", self._rank, [ctx._native])
 
 
 def qcdw_op_create(ctx: Context, lat: qcdw_lattice, U, kappa: float, csw: float, inner="f64", recon: int = 12):
@@ -587,7 +606,7 @@ def qcdw_invert_multi(op: Operator, b, x, params: qcdw_solver_params | None = No
     return [SolveInfo(infos[k], hists[k]) for k in range(nrhs)]
 
 
-class Batch:
+class Batch(_Owned):
     """qcdw_batch: operators of different lattices / kappas solved in lockstep."""
 
     _rank = 1
@@ -599,21 +618,8 @@ class Batch:
         h = ctypes.c_void_p()
         st = load_library().qcdw_batch_create(ctx.handle, len(self.ops), arr, ctypes.byref(h))
         _check(ctx.handle, st)
-        self.handle = h
-        ctx._adopt(self)
-        for o in self.ops:
-            o._children.add(self)
-
-    def close(self):
-        if getattr(self, "handle", None):
-            load_library().qcdw_batch_destroy(self.handle)
-            self.handle = None
-
-    def __del__(self):
-        try:
-            self.close()
-        except Exception:
-            pass
+        owners = dict.fromkeys([ctx._native, *(o._native for o in self.ops)])
+        self._native = _Native(h, "qcdw_batch_destroy", self._rank, owners)
 
 
 def qcdw_batch_create(ctx: Context, ops) -> Batch:
@@ -648,7 +654,7 @@ def qcdw_invert_batch(batch: Batch, bs, xs, params: qcdw_solver_params | None = 
     return [SolveInfo(infos[k], hists[k]) for k in range(n)]
 
 
-class Net:
+class Net(_Owned):
     """qcdw_net: the learned gauge-covariant preconditioner of one operator."""
 
     _rank = 0
@@ -659,20 +665,7 @@ class Net:
         h = ctypes.c_void_p()
         st = load_library().qcdw_net_create(op.handle, int(hidden), int(seed), float(init_scale), ctypes.byref(h))
         _check(op.ctx.handle, st)
-        self.handle = h
-        op.ctx._adopt(self)
-        op._children.add(self)
-
-    def close(self):
-        if getattr(self, "handle", None):
-            load_library().qcdw_net_destroy(self.handle)
-            self.handle = None
-
-    def __del__(self):
-        try:
-            self.close()
-        except Exception:
-            pass
+        self._native = _Native(h, "qcdw_net_destroy", self._rank, [op.ctx._native, op._native])
 
 
 def qcdw_net_create(op: Operator, hidden: int = 12, seed: int = 0, init_scale: float = 0.01) -> Net:
@@ -686,9 +679,8 @@ def qcdw_net_destroy(net: Net) -> None:
 def qcdw_net_bind(net: Net, op: Operator) -> None:
     """Move the net to another operator of the same lattice (weights and Adam state kept)."""
     _check(net.op.ctx.handle, load_library().qcdw_net_bind(net.handle, op.handle))
-    net.op._children.discard(net)
+    net._native.move(net.op._native, op._native)
     net.op = op
-    op._children.add(net)
 
 
 def _wshape(net):
@@ -817,7 +809,7 @@ def make_mg_params(**kw) -> qcdw_mg_params:
     return prm
 
 
-class Multigrid:
+class Multigrid(_Owned):
     """qcdw_mg: two-level aggregation multigrid set up on one operator (vecs: None or nvec fermion fields)."""
 
     _rank = 0
@@ -834,20 +826,13 @@ class Multigrid:
                                            _ptr(vecs, torch.complex128, "vecs") if vecs is not None else None,
                                            ctypes.byref(h))
         _check(op.ctx.handle, st)
-        self.handle = h
+        self._native = _Native(h, "qcdw_mg_destroy", self._rank, [op.ctx._native, op._native])
         dims = (ctypes.c_int * 4)()
         nv = ctypes.c_int()
         _check(op.ctx.handle, load_library().qcdw_mg_info(h, dims, ctypes.byref(nv)))
         self.coarse_dims = tuple(dims)
         self.nvec = nv.value
         self.coarse_sites = int(math.prod(self.coarse_dims))
-        op.ctx._adopt(self)
-        op._children.add(self)
-
-    def close(self):
-        if getattr(self, "handle", None):
-            load_library().qcdw_mg_destroy(self.handle)
-            self.handle = None
 
     def coarse_len(self) -> int:
         return self.coarse_sites * 2 * self.nvec
