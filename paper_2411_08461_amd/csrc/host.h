@@ -145,9 +145,9 @@ struct DevBuf {
             }
         }
         hipError_t e = hipMalloc(&p, bytes);
-        if (e == hipErrorOutOfMemory && pooled) {
+        if (e == hipErrorOutOfMemory) {
             (void)hipGetLastError();
-            block_cache().trim(dev);
+            block_cache().trim(dev);  // idle blocks may be what is missing, whoever asks
             e = hipMalloc(&p, bytes);
         }
         if (e == hipSuccess)
