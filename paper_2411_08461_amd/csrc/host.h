@@ -60,51 +60,72 @@ struct qcdw_ctx {
 
 namespace qcdw_host {
 
-// Device blocks of destroyed operators, batches and nets, kept per device and handed to the next
-// allocation of about the same size: creating operators one after another (a new gauge field per
+// Device blocks of destroyed operators, batches and nets and of finished calls, kept per device and handed to the
+// next allocation of about the same size: creating operators one after another (a new gauge field per
 // solve) then costs no hipMalloc, and no hipFree, which also waits for the whole device.  Blocks
 // enter the cache only once their owner's stream has drained (the destroy calls synchronise it).
+// The cache holds at most a quarter of the device's memory; when a block does not fit, the ones that
+// have lain there longest go, so that sizes no longer in use do not shut out those of the running work.
 struct BlockCache {
+    struct Block {
+        void* p;
+        uint64_t age;  // when it came in
+    };
+    struct Device {
+        std::multimap<size_t, Block> free;  // by size
+        size_t held = 0, limit = 0;         // bytes in the cache, and at most
+        uint64_t clock = 0;
+    };
     std::mutex m;
-    std::map<int, std::multimap<size_t, void*>> free;  // device -> (size, block)
-    std::map<int, size_t> held, limit;  // bytes in the cache, and at most a quarter of the device's memory
+    std::map<int, Device> devices;
     // smallest cached block of at least `bytes` and at most a quarter (plus 1 MiB) larger
     void* take(int dev, size_t bytes, size_t& got)
     {
         std::lock_guard<std::mutex> lk(m);
-        auto& f = free[dev];
-        auto it = f.lower_bound(bytes);
-        if (it == f.end() || it->first > bytes + bytes / 4 + (1u << 20)) return nullptr;
-        void* q = it->second;
+        Device& d = devices[dev];
+        auto it = d.free.lower_bound(bytes);
+        if (it == d.free.end() || it->first > bytes + bytes / 4 + (1u << 20)) return nullptr;
+        void* q = it->second.p;
         got = it->first;
-        held[dev] -= got;
-        f.erase(it);
+        d.held -= got;
+        d.free.erase(it);
         return q;
     }
     void give(int dev, void* q, size_t n)
     {
+        std::vector<void*> out;  // released outside the lock
         {
             std::lock_guard<std::mutex> lk(m);
-            size_t& cap = limit[dev];
-            if (cap == 0) {
+            Device& d = devices[dev];
+            if (d.limit == 0) {
                 hipDeviceProp_t prop;
-                cap = hipGetDeviceProperties(&prop, dev) == hipSuccess ? prop.totalGlobalMem / 4 : 1;
+                d.limit = hipGetDeviceProperties(&prop, dev) == hipSuccess ? prop.totalGlobalMem / 4 : 1;
             }
-            if (held[dev] + n <= cap) {
-                free[dev].emplace(n, q);
-                held[dev] += n;
-                return;
+            if (n > d.limit) {
+                out.push_back(q);
+            } else {
+                while (d.held + n > d.limit) {
+                    auto oldest = d.free.begin();
+                    for (auto it = d.free.begin(); it != d.free.end(); ++it)
+                        if (it->second.age < oldest->second.age) oldest = it;
+                    out.push_back(oldest->second.p);
+                    d.held -= oldest->first;
+                    d.free.erase(oldest);
+                }
+                d.free.emplace(n, Block{q, d.clock++});
+                d.held += n;
             }
         }
-        (void)hipFree(q);
+        for (void* p : out) (void)hipFree(p);
     }
     // return every cached block of the device to the runtime (the current device must be dev)
     void trim(int dev)
     {
         std::lock_guard<std::mutex> lk(m);
-        for (auto& kv : free[dev]) (void)hipFree(kv.second);
-        free[dev].clear();
-        held[dev] = 0;
+        Device& d = devices[dev];
+        for (auto& kv : d.free) (void)hipFree(kv.second.p);
+        d.free.clear();
+        d.held = 0;
     }
 };
 inline BlockCache& block_cache()

@@ -71,11 +71,38 @@ static int out_of_memory()
     return 0;
 }
 
+// a cache full of sizes that nobody asks for any more makes room for those in use, oldest first
+static int full_cache()
+{
+    capacity = 100000 * MB;
+    for (int k = 0; k < 2; k++) {
+        use(400 * MB);
+        use(250 * MB);
+        use(310 * MB);
+    }
+    EXPECT(used == 960 * MB && mallocs == 3);
+    use(120 * MB);
+    EXPECT(used <= 1000 * MB);
+    const size_t n = mallocs;
+    for (int k = 0; k < 5; k++) use(120 * MB);
+    EXPECT(mallocs == n);
+    use(310 * MB);  // the last one in before the new size
+    EXPECT(mallocs == n);
+    use(400 * MB);  // the first one in: gone
+    EXPECT(mallocs == n + 1 && used <= 1000 * MB);
+    use(1001 * MB);  // larger than the cache: returned at once, and nothing else with it
+    const size_t held = used;
+    use(1001 * MB);
+    EXPECT(used == held && mallocs == n + 3);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     int bad = 1;
     if (what == "out_of_memory") bad = out_of_memory();
+    if (what == "full_cache") bad = full_cache();
     if (bad == 0) std::puts("ok");
     return bad;
 }
