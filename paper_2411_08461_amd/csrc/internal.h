@@ -267,6 +267,15 @@ hipError_t launch_multidot(hipStream_t s, const void* V, long stride, int nvec, 
 hipError_t launch_multiaxpy(hipStream_t s, const void* V, long stride, int nvec, const double* c, void* w, long n,
                             double sign, double* partials = nullptr,
                             double* nrm2 = nullptr);  // w += sign sum_i c_i V_i [, nrm2 = ||w||^2]
+// Blocks (and groups of partials) of launch_multiaxpy_dot, whose blocks take 64 elements at a time where those of the
+// other vector kernels take 1024: small fields get a block per tile, up to three per CU.  With blas_blocks(n) alone
+// FGMRES(32) at 8^3x16 (48 blocks) took 5.24 ms for its 58 iterations, 4.64 so; 12^3x24 7.40 and 7.07; from 16^3x32 on
+// the count is the same.
+inline int multiaxpy_dot_blocks(long n)
+{
+    const long tiles = (n + 63) / 64, few = tiles < 768 ? tiles : 768, b = blas_blocks(n);
+    return (int)(b > few ? b : few);
+}
 // w -= sum_i c_i V_i and out[2i..] = (V_i, w) of the result in one pass; at most 64 vectors
 hipError_t launch_multiaxpy_dot(hipStream_t s, const void* V, long stride, int nvec, const double* c, void* w, long n,
                                 double* partials, double* out);

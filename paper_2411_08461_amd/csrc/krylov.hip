@@ -148,7 +148,7 @@ hipError_t launch_multiaxpy_dot(hipStream_t s, const void* V, long stride, int n
 {
     if (nvec <= 0 || nvec > 8 * MDOT_GROUP) return hipErrorInvalidValue;
     const int ng = (nvec + MDOT_GROUP - 1) / MDOT_GROUP;
-    const int nb = blas_blocks(n);
+    const int nb = multiaxpy_dot_blocks(n);
     hipLaunchKernelGGL(k_multiaxpy_dot, dim3(nb), dim3(64 * ng), 0, s, (const double2*)V, stride, nvec, c, (double2*)w,
                        n, partials);
     hipLaunchKernelGGL(k_multidot_sum, dim3(2 * MDOT_GROUP, ng), dim3(256), 0, s, partials, nb, nvec, out);

@@ -515,7 +515,7 @@ qcdw_status qcdw_host::fgmres_run(qcdw_op* op, const Precond* precond, const voi
     HIPCHK(ctx, V.alloc(vb * (m + 1)));
     if (precond) HIPCHK(ctx, Z.alloc(vb * m));
     const int ngroups = (m + 1 + 7) / 8;
-    HIPCHK(ctx, part.alloc((size_t)16 * ngroups * blas_blocks(n) * sizeof(double) + 64));
+    HIPCHK(ctx, part.alloc((size_t)16 * ngroups * multiaxpy_dot_blocks(n) * sizeof(double) + 64));
     HIPCHK(ctx, coef.alloc(2 * 65 * sizeof(double)));
     HIPCHK(ctx, dres.alloc(HOST_D_N * sizeof(double)));
     static_assert(HOST_D_N >= 257, "FGMRES stages two Gram-Schmidt columns and a norm");
