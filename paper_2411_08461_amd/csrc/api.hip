@@ -822,17 +822,6 @@ struct Solver {
         return QCDW_OK;
     }
 
-    // c-tiles per group of the FP64 multi-RHS hop: the largest divisor of a slice's tiles with tiles x right-hand
-    // sides <= 216, so that neighbours along t (and most along z) are still in the XCD's L2; 24^3x64, 12 of them:
-    // groups of 18 / 9 / 6 / none 2.90 / 2.98 / 3.03 / 3.15 ms for the two hops of M_hat
-    static int rhs64_cgroup(const Geom& g, int nrhs)
-    {
-        const int m = 216 / nrhs, nct = hop_ctiles(g);
-        for (int d = std::min(m, nct - 1); d >= 2; d--)
-            if (nct % d == 0) return d;
-        return 0;
-    }
-
     // An FP64 hop of the source preparation or a residual for every problem (of `only`, where given: problems
     // whose flags are set there are skipped), in one launch: a batch over its table, right-hand sides of one
     // operator with the tile's links and clover entries shared through L2, a single one in the operator's form.

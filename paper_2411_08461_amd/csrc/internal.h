@@ -233,6 +233,20 @@ hipError_t launch_hop_rhs(hipStream_t s, int prec, int epi, int red, const HopAr
 // the FP64 hop of source preparation and residuals, several RHS per thread group (either reconstruction; EPI_CLOV, EPI_CLOV_XPAY,
 // EPI_CLOV_RESID with RED_NORM, EPI_XPAY_CLOVY with RED_DIST)
 hipError_t launch_hop_rhs64(hipStream_t s, int recon, int epi, int red, const HopArgs& a, const Scal* S);
+// c-tiles per group of that hop: the largest divisor of a slice's tiles with tiles x right-hand sides <= 216, so that
+// neighbours along t (and most along z) are still in the XCD's L2; none where the padding of a slice to whole tiles is
+// more than 1/32 of its sites, which costs more lanes than the order gives.  Source preparation and residual of 12
+// right-hand sides in groups against none: 24^3x32 7.55 and 7.94 ms (two hops of 24^3x64 in groups of 18 / 9 / 6 / none
+// 2.90 / 2.98 / 3.03 / 3.15), 22^3x32 (1 % of padding) 6.08 and 6.33, 16^3x32 2.22 and 2.24; 14^3x32 (2.6 %) 1.79 and
+// 1.76, 14^2x2x64 (31 %) 0.69 and 0.67; four and sixteen of them alike.
+inline int rhs64_cgroup(const Geom& g, int nrhs)
+{
+    const int sites = g.Lxh * g.Ly * g.Lz, nct = hop_ctiles(g), m = 216 / nrhs;
+    if ((64L * nct - sites) * 32 > sites) return 0;
+    for (int d = m < nct - 1 ? m : nct - 1; d >= 2; d--)
+        if (nct % d == 0) return d;
+    return 0;
+}
 
 // learned preconditioner layers (activations [parity][channel][Vh][3], FP32/BF16 storage)
 // mfma: layers with a BF16 end mix channels on the BF16 matrix cores (k_net_layer_mfma)

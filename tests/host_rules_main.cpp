@@ -28,9 +28,36 @@ static int vector_blocks()
     return 0;
 }
 
+static Geom lattice(int x, int y, int z, int t)
+{
+    Geom g{};
+    g.Lx = x, g.Ly = y, g.Lz = z, g.Lt = t, g.Lxh = x / 2, g.Vh = x / 2 * y * z * t, g.t_bc = 1;
+    return g;
+}
+
+// groups of the FP64 hop of several right-hand sides: whole groups, none on slices that are mostly padding, and never
+// many more lanes than sites
+static int rhs64_groups()
+{
+    EXPECT(rhs64_cgroup(lattice(24, 24, 24, 64), 12) == 18);
+    EXPECT(rhs64_cgroup(lattice(14, 14, 2, 32), 12) == 0);  // 196 of 256 lanes
+    EXPECT(rhs64_cgroup(lattice(12, 10, 10, 32), 12) == 0);  // 600 of 640
+    EXPECT(rhs64_cgroup(lattice(14, 6, 6, 4), 9) == 2);      // 252 of 256
+    for (int x = 2; x <= 32; x += 2)
+        for (int y = 2; y <= 32; y += 2)
+            for (int z = 2; z <= 32; z += 2)
+                for (int n = 1; n <= 16; n++) {
+                    const Geom g = lattice(x, y, z, 16);
+                    const int c = rhs64_cgroup(g, n);
+                    EXPECT(hop_cgroup_fits(g, c) && c * n <= 216);
+                    EXPECT(64L * hop_blocks_nt(g, 1, c) <= g.Vh + g.Vh / 32 + 63);
+                }
+    return 0;
+}
+
 int main()
 {
-    if (vector_blocks()) return 1;
+    if (vector_blocks() || rhs64_groups()) return 1;
     std::puts("ok");
     return 0;
 }
