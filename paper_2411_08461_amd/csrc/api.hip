@@ -8,27 +8,6 @@
 
 namespace {
 
-// multi-RHS hop forms (tuning-cache value of "mrhs_hop/..."): bit 0 set: one block per (tile, RHS), links
-// re-read from L2; else the register loop, in slice-group order of (v & 1023) / 2 c-tiles when nonzero, on
-// the matrix cores when MRHS_MFMA is set (16-bit storage)
-constexpr int MRHS_MFMA = 1024;
-
-bool mrhs_variant_fits(const qcdw::Geom& g, int prec, int v)
-{
-    if (v == 1) return true;
-    if ((v & 1) || (v & ~(MRHS_MFMA | 1023))) return false;
-    // the matrix-core form keeps its neighbour offsets (complex index within one RHS) in 32 bits
-    if ((v & MRHS_MFMA) && ((prec != qcdw::BF16 && prec != qcdw::F16) || 12L * g.Vh > 0x7fffffffL)) return false;
-    const int cg = (v & 1023) >> 1;
-    return cg == 0 || hop_cgroup_fits(g, cg);
-}
-
-int mrhs_blocks(const qcdw::Geom& g, int v)
-{
-    const int cg = (v & 1) ? 0 : (v & 1023) >> 1;
-    return cg > 0 ? hop_ctiles(g) * g.Lt : hop_blocks(g.Vh);
-}
-
 hipError_t launch_mrhs_variant(hipStream_t st, int prec, int epi, int red, qcdw::HopArgs a, const qcdw::Scal* S,
                                int v, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
 {
@@ -471,7 +450,7 @@ qcdw_status qcdw_op_matpc_multi(qcdw_op* op, qcdw_prec prec, int nrhs, const voi
         HIPCHK(ctx, launch_pack_spinor(s, prec, g, (const char*)in_e + k * half, 0,
                                        (char*)in.p + (size_t)k * n * cplx_bytes(prec), 1.0));
     // the kernel form cached for this shape by a multi-RHS solve (or a tuning file), else the register loop
-    int form = 0;
+    int form = mrhs_variant_fits(g, prec, 0) ? 0 : 1;
     char key[96];
     snprintf(key, sizeof key, "mrhs_hop/p%d/L%dx%dx%dx%d/n%d", (int)prec, g.Lx, g.Ly, g.Lz, g.Lt, nrhs);
     const auto it = ctx->tune.find(key);
@@ -726,6 +705,8 @@ struct Solver {
                     if ((cand[c] & 1) == 0 && mrhs_variant_fits(g, kprec, MRHS_MFMA | cand[c]))
                         cand.push_back(MRHS_MFMA | cand[c]);
             }
+            cand.erase(std::remove_if(cand.begin(), cand.end(), [&](int v) { return !mrhs_variant_fits(g, kprec, v); }),
+                       cand.end());  // (the form with one block per tile and right-hand side always fits)
         }
         auto choose = [&](int v) {
             variant = v;

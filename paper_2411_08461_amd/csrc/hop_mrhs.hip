@@ -333,7 +333,7 @@ hipError_t launch_hop_mrhs(hipStream_t s, int prec, int epi, int red, const HopA
                            hipEvent_t e0, hipEvent_t e1)
 {
     if (a.g.Vh <= 0 || a.nrhs <= 0) return hipSuccess;
-    if (a.nrhs > MRHS_MAX) return hipErrorInvalidValue;
+    if (a.nrhs > MRHS_MAX || !mrhs_offsets_fit(prec, a.g.Vh)) return hipErrorInvalidValue;
     switch (prec) {
     case F64: return launch_mrhs_p<P64>(s, epi, red, a, S, e0, e1);
     case F32: return launch_mrhs_p<P32>(s, epi, red, a, S, e0, e1);

@@ -219,6 +219,27 @@ hipError_t launch_fin_omega(hipStream_t s, Scal* S, const double* partials, int 
                             const int* nbs = nullptr);
 hipError_t launch_fin_beta(hipStream_t s, Scal* S, const double* partials, int nb, double* hist, int nrhs = 1);
 
+// multi-RHS hop forms (tuning-cache value of "mrhs_hop/..."): bit 0 set: one block per (tile, RHS), links
+// re-read from L2; else the register loop, in slice-group order of (v & 1023) / 2 c-tiles when nonzero, on
+// the matrix cores when MRHS_MFMA is set (16-bit storage)
+constexpr int MRHS_MFMA = 1024;
+// in 16-bit storage the register loop's byte offsets within a right-hand side (12 Vh complex of 4 bytes) are 32-bit
+inline bool mrhs_offsets_fit(int prec, long Vh) { return (prec != BF16 && prec != F16) || 48 * Vh <= 1L << 32; }
+inline bool mrhs_variant_fits(const Geom& g, int prec, int v)
+{
+    if (v == 1) return true;
+    if ((v & 1) || (v & ~(MRHS_MFMA | 1023))) return false;
+    // the matrix-core form keeps its neighbour offsets (complex index within one RHS) in 32 bits
+    if ((v & MRHS_MFMA) && ((prec != BF16 && prec != F16) || 12L * g.Vh > 0x7fffffffL)) return false;
+    if (!(v & MRHS_MFMA) && !mrhs_offsets_fit(prec, g.Vh)) return false;
+    const int cg = (v & 1023) >> 1;
+    return cg == 0 || hop_cgroup_fits(g, cg);
+}
+inline int mrhs_blocks(const Geom& g, int v)
+{
+    const int cg = (v & 1) ? 0 : (v & 1023) >> 1;
+    return cg > 0 ? hop_ctiles(g) * g.Lt : hop_blocks(g.Vh);
+}
 // multi-RHS hop (reconstruct-12): a.nrhs stacked fields; RHS y skipped when S[y].flags != 0;
 // partials [y][hop_blocks][3]
 hipError_t launch_hop_mrhs(hipStream_t s, int prec, int epi, int red, const HopArgs& a, const Scal* S,

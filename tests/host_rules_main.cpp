@@ -55,9 +55,29 @@ static int rhs64_groups()
     return 0;
 }
 
+// forms of the multi-RHS hop on lattices whose right-hand side does not fit the 32-bit byte offsets of 16-bit storage:
+// the forms with wider offsets are left, so that every call still has one
+static int mrhs_forms()
+{
+    const Geom fits = lattice(256, 128, 64, 84), big = lattice(256, 128, 64, 86);
+    EXPECT(48L * fits.Vh <= 1L << 32 && 48L * big.Vh > 1L << 32);
+    for (int prec : {F64, F32, BF16, F16}) {
+        const bool narrow = prec == BF16 || prec == F16;
+        for (int v : {0, 8}) {
+            EXPECT(mrhs_variant_fits(fits, prec, v));
+            EXPECT(mrhs_variant_fits(big, prec, v) == !narrow);
+        }
+        EXPECT(mrhs_offsets_fit(prec, fits.Vh) && mrhs_offsets_fit(prec, big.Vh) == !narrow);
+        EXPECT(mrhs_variant_fits(big, prec, 1));
+        EXPECT(!mrhs_variant_fits(fits, prec, 3) && !mrhs_variant_fits(fits, prec, 2 * 7));
+        EXPECT(mrhs_variant_fits(fits, prec, MRHS_MFMA) == narrow);
+    }
+    return 0;
+}
+
 int main()
 {
-    if (vector_blocks() || rhs64_groups()) return 1;
+    if (vector_blocks() || rhs64_groups() || mrhs_forms()) return 1;
     std::puts("ok");
     return 0;
 }
