@@ -74,6 +74,22 @@ __device__ __forceinline__ cx<T> lane_cx(cx<T> v, int at)
     return {lane_val(v.re, at), lane_val(v.im, at)};
 }
 
+// complex number c of a run of words as they were loaded (a bit copy: the words are no object of P's storage type)
+template <class P>
+__device__ __forceinline__ cx<typename P::real> words_cx(const uint32_t* w, int c)
+{
+    if constexpr (P::cbytes == 16)
+        return {__builtin_bit_cast(double, make_uint2(w[4 * c], w[4 * c + 1])),
+                __builtin_bit_cast(double, make_uint2(w[4 * c + 2], w[4 * c + 3]))};
+    else if constexpr (P::cbytes == 8)
+        return {__builtin_bit_cast(float, w[2 * c]), __builtin_bit_cast(float, w[2 * c + 1])};
+    else if constexpr (std::is_same_v<P, PBF16>)
+        return {bf_bits2f(w[c] & 0xffffu), bf_bits2f(w[c] >> 16)};
+    else
+        return {(float)__builtin_bit_cast(_Float16, (uint16_t)(w[c] & 0xffffu)),
+                (float)__builtin_bit_cast(_Float16, (uint16_t)(w[c] >> 16))};
+}
+
 template <class P, int EPI, int RED>
 __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(HopArgs a, const Scal* S)
 {
@@ -221,8 +237,8 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
             cx<T> pu[3], pl[3], hv[3];
 #pragma unroll
             for (int c = 0; c < 3; c++) {
-                pu[c] = P::ld(f.u[h].u, c);
-                pl[c] = P::ld(f.l[h].u, c);
+                pu[c] = words_cx<P>(f.u[h].u, c);
+                pl[c] = words_cx<P>(f.l[h].u, c);
             }
             project<true>(pu, pl, L.cs[h], h < 2, hv);
             if constexpr (MORE) fetch_hop(f, h, rn);
@@ -232,8 +248,8 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
 #pragma unroll
         for (int c = 0; c < 3; c++) {
             res[c] = acc_u[c] + lane_cx(acc_l[c], at_partner);
-            if constexpr (HAS_Y) yv[c] = P::ld(f.y.u, c);
-            if constexpr (HAS_W) wv[c] = P::ld(f.w.u, c);
+            if constexpr (HAS_Y) yv[c] = words_cx<P>(f.y.u, c);
+            if constexpr (HAS_W) wv[c] = words_cx<P>(f.w.u, c);
         }
         if constexpr (EPI == EPI_NONE) {
 #pragma unroll

@@ -383,6 +383,7 @@ struct TrainArgs {
 
 constexpr int TR_ROW = 18;  // floats per row of R: 16 and a pad that spreads the lanes of a store over the banks
 constexpr int TR_R = 192 * TR_ROW;
+static_assert(TR_ROW % 2 == 0 && TR_R % 4 == 0, "rows are read in pairs of floats, arrays of R stay 16-byte aligned");
 
 // this wave's channel of the two hops (forward, backward) along mu into R; site odd
 __device__ __forceinline__ void train_transport(const Geom& g, const void* gauge, const void* field, int mu, int w,
@@ -456,7 +457,7 @@ __device__ __forceinline__ void train_own(const void* field, long Vh, int w, int
 template <int H>
 __global__ __launch_bounds__(256) void k_train_hidden(TrainArgs n)
 {
-    __shared__ float R[2][TR_R];
+    __shared__ alignas(16) float R[2][TR_R];
     const Geom& g = n.g;
     const int odd = (int)blockIdx.x < n.tiles, tile = odd ? blockIdx.x : blockIdx.x - n.tiles;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -624,15 +625,18 @@ __device__ __forceinline__ void train_product(const float* rows, const float* C,
     }
 }
 
-// the four waves' accumulators of one tile summed into (or added to) a block's partial sums
-__device__ __forceinline__ void train_store(double* red, double* out, int accumulate, const mfma_d4& acc, int w)
+// the four waves' accumulators of one tile summed into (or added to) a block's partial sums; red: the bits of
+// [4][256] doubles, in LDS that held floats
+typedef float bits64 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void train_store(bits64* red, double* out, int accumulate, const mfma_d4& acc, int w)
 {
     const int lane = threadIdx.x & 63, e = threadIdx.x;
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 4; r++) red[w * 256 + 64 * r + lane] = acc[r];
+    for (int r = 0; r < 4; r++) red[w * 256 + 64 * r + lane] = __builtin_bit_cast(bits64, (double)acc[r]);
     __syncthreads();
-    const double s = ((red[e] + red[256 + e]) + red[512 + e]) + red[768 + e];
+    const auto part = [&](int k) { return __builtin_bit_cast(double, red[256 * k + e]); };
+    const double s = ((part(0) + part(1)) + part(2)) + part(3);
     out[e] = accumulate ? out[e] + s : s;
 }
 
@@ -644,8 +648,8 @@ template <int H>
 __global__ __launch_bounds__(256) void k_train_grad(TrainArgs n, int nb)
 {
     constexpr int CT = train_ct<H>(), CROW = 2 * H + 2;
-    __shared__ float R[TR_R];
-    __shared__ float C[192 * CROW + 16];  // columns: C[k][2 H]; the last tile reads up to 16 floats past a row
+    __shared__ alignas(16) float R[TR_R];
+    __shared__ alignas(16) float C[192 * CROW + 16];  // columns: C[k][2 H]; the last tile reads up to 16 floats past a row
     const Geom& g = n.g;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int part = blockIdx.x / nb, b0 = blockIdx.x - part * nb;
@@ -654,7 +658,7 @@ __global__ __launch_bounds__(256) void k_train_grad(TrainArgs n, int nb)
 #pragma unroll
         for (int j = 2 * H; j < CROW; j++) C[threadIdx.x * CROW + j] = 0.f;
     }
-    double* red = reinterpret_cast<double*>(R);  // [4][256]
+    bits64* red = reinterpret_cast<bits64*>(R);  // [4][256]
     static_assert(TR_R * 4 >= 4 * 256 * 8, "the reduction buffer fits in R");
     if (part < 2) {
         const void* rows = part == 0 ? n.gz : n.r;
