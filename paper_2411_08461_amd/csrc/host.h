@@ -171,10 +171,12 @@ struct DevBuf {
             block_cache().trim(dev);  // idle blocks may be what is missing, whoever asks
             e = hipMalloc(&p, bytes);
         }
-        if (e == hipSuccess)
+        if (e == hipSuccess) {
             n = bytes;
-        else
+        } else {
             p = nullptr;
+            (void)hipGetLastError();  // the caller has it; a launch after this one is not at fault
+        }
         return e;
     }
 };

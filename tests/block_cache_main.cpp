@@ -5,6 +5,7 @@
 constexpr size_t MB = 1 << 20;
 static size_t capacity, used, mallocs, frees;
 static std::map<void*, size_t> blocks;
+static hipError_t last_error = hipSuccess;
 static char* next_address = (char*)(1UL << 40);
 
 hipError_t hipGetDevice(int* d)
@@ -20,7 +21,7 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int)
 }
 hipError_t hipMalloc(void** p, size_t n)
 {
-    if (used + n > capacity) return hipErrorOutOfMemory;
+    if (used + n > capacity) return last_error = hipErrorOutOfMemory;
     mallocs++;
     used += n;
     *p = next_address;
@@ -37,7 +38,12 @@ hipError_t hipFree(void* p)
     blocks.erase(it);
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError()
+{
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
 
 #define EXPECT(c)                                                    \
     do {                                                             \
@@ -97,12 +103,26 @@ static int full_cache()
     return 0;
 }
 
+// an allocation that fails is reported once, by the call itself: the next launch's own check finds no error
+static int error_left_behind()
+{
+    capacity = 1000 * MB;
+    for (int pooled = 0; pooled < 2; pooled++) {
+        DevBuf b;
+        b.pooled = pooled;
+        EXPECT(b.alloc(1200 * MB) == hipErrorOutOfMemory);
+        EXPECT(hipGetLastError() == hipSuccess);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     int bad = 1;
     if (what == "out_of_memory") bad = out_of_memory();
     if (what == "full_cache") bad = full_cache();
+    if (what == "error_left_behind") bad = error_left_behind();
     if (bad == 0) std::puts("ok");
     return bad;
 }

@@ -21,7 +21,7 @@ def exe(tmp_path_factory):
     return str(out)
 
 
-@pytest.mark.parametrize("scenario", ["out_of_memory", "full_cache"])
+@pytest.mark.parametrize("scenario", ["out_of_memory", "full_cache", "error_left_behind"])
 def test_block_cache(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stderr
