@@ -151,10 +151,25 @@ __device__ __forceinline__ M3 ld_link(const LinkPlanes& U, int mu, Site s)
     return r;
 }
 
+// the paper's links as they are, for a call that finds no memory for a plane-major copy
+struct LinkRecords {
+    const double2* U;
+    long Vh;
+};
+__device__ __forceinline__ M3 ld_link(const LinkRecords& U, int mu, Site s)
+{
+    M3 r;
+    const double2* p = U.U + ((long)(mu * 2 + s.parity) * U.Vh + s.cb) * 9;
+#pragma unroll
+    for (int e = 0; e < 9; e++) r.m[e] = {p[e].x, p[e].y};
+    return r;
+}
+
 // F_{mu nu}(x): traceless part of (Q - Q^+)/8, Q = sum of the four
 // counter-clockwise plaquettes in the (mu, nu) plane that touch x, times w.  F is
 // anti-Hermitian: out gets the imaginary diagonal and the three entries above it.
-__device__ __forceinline__ void field_strength(const LinkPlanes& U, const Geom& g, const int (&c)[4], int mu, int nu,
+template <class Links>
+__device__ __forceinline__ void field_strength(const Links& U, const Geom& g, const int (&c)[4], int mu, int nu,
                                                double w, double (&out)[8])
 {
     const Site x = site_of(g, c);
@@ -340,8 +355,8 @@ __device__ __forceinline__ void copy_rows(const double* stage, int n, F&& f)
     }
 }
 
-template <class PL, bool OP>
-__global__ __launch_bounds__(128) void k_clover_build(LinkPlanes U, Geom g, double wt, double ws, int G,
+template <class Links, class PL, bool OP>
+__global__ __launch_bounds__(128) void k_clover_build(Links U, Geom g, double wt, double ws, int G,
                                                       CloverOut out)
 {
     __shared__ double sh[6 * 8 * CB_SITES];  // F, then the packed blocks of half of the sites at a time
@@ -475,14 +490,26 @@ __global__ void k_clover_invert(const double* __restrict__ clover, double* __res
 
 static inline dim3 grid_for(long n) { return dim3((unsigned)((n + 255) / 256)); }
 
-hipError_t launch_clover_build(hipStream_t s, const Geom& g, const LinkPlanes& U, void* clover, double wt, double ws)
+template <class Links>
+static hipError_t clover_build(hipStream_t s, const Geom& g, const Links& U, void* clover)
 {
     if (g.Vh == 0) return hipSuccess;
     const int tiles = (g.Vh + CB_SITES - 1) / CB_SITES;
     CloverOut o{};
     o.C = (double*)clover;
-    hipLaunchKernelGGL((k_clover_build<P64, false>), dim3(2 * tiles), dim3(128), 0, s, U, g, wt, ws, grouped_order(g), o);
+    hipLaunchKernelGGL((k_clover_build<Links, P64, false>), dim3(2 * tiles), dim3(128), 0, s, U, g, 1.0, 1.0,
+                       grouped_order(g), o);
     return hipGetLastError();
+}
+
+hipError_t launch_clover_build(hipStream_t s, const Geom& g, const LinkPlanes& U, void* clover)
+{
+    return clover_build(s, g, U, clover);
+}
+
+hipError_t launch_clover_build_records(hipStream_t s, const Geom& g, const void* U, void* clover)
+{
+    return clover_build(s, g, LinkRecords{(const double2*)U, g.Vh}, clover);
 }
 
 hipError_t launch_clover_op(hipStream_t s, const Geom& g, const LinkPlanes& U, double wt, double ws, double kappa,
@@ -499,8 +526,9 @@ hipError_t launch_clover_op(hipStream_t s, const Geom& g, const LinkPlanes& U, d
     }
     o.kc = kappa * csw;
     o.notpd = notpd_count;
-#define QCDW_CLOVER_OP(P) \
-    hipLaunchKernelGGL((k_clover_build<P, true>), dim3(2 * tiles), dim3(128), 0, s, U, g, wt, ws, grouped_order(g), o)
+#define QCDW_CLOVER_OP(P)                                                                                              \
+    hipLaunchKernelGGL((k_clover_build<LinkPlanes, P, true>), dim3(2 * tiles), dim3(128), 0, s, U, g, wt, ws,          \
+                       grouped_order(g), o)
     switch (prec_lo) {
     case F64: QCDW_CLOVER_OP(P64); break;
     case F32: QCDW_CLOVER_OP(P32); break;

@@ -434,10 +434,11 @@ struct CallScratch {
     }
 };
 
-// the clover field of the paper's links; planes: 9 complex per link of scratch (nullptr: out of memory)
+// the clover field of the paper's links; planes: 9 complex per link of scratch, or nullptr where there is no memory
+// for it (slower)
 inline hipError_t clover_from_paper(hipStream_t s, const Geom& g, const void* U, void* clover, void* planes)
 {
-    if (!planes) return hipErrorOutOfMemory;
+    if (!planes) return launch_clover_build_records(s, g, U, clover);
     const hipError_t e = launch_pack_links(s, g, U, 18, planes, nullptr, F64, 18, nullptr);
     return e != hipSuccess ? e : launch_clover_build(s, g, link_planes(planes, 18, nullptr, g.Vh), clover);
 }

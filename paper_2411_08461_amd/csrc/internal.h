@@ -349,11 +349,12 @@ hipError_t launch_meson_2pt(hipStream_t s, const Geom& g, const void* S, const v
 // sequential sources through the sink slice t_f from the propagator S (12 fields into out)
 hipError_t launch_seq_sources(hipStream_t s, const Geom& g, const void* S, int t_f, int g_f, const int mom[3],
                               void* out);
-// C = wt sum_i sigma_i4 F_i4 + ws sum_{i<j} sigma_ij F_ij (wt = ws = 1: the isotropic clover field)
-hipError_t launch_clover_build(hipStream_t s, const Geom& g, const LinkPlanes& U, void* clover, double wt = 1.0,
-                               double ws = 1.0);
-// A = 1 - kappa csw C and its inverse per parity in the internal packing, the inverse also in prec_lo (F64: not);
-// notpd_count is raised by the blocks that are not positive definite
+// the isotropic clover field C = sum_{mu<nu} sigma_{mu nu} F_{mu nu}, from plane-major links or from the paper's
+hipError_t launch_clover_build(hipStream_t s, const Geom& g, const LinkPlanes& U, void* clover);
+hipError_t launch_clover_build_records(hipStream_t s, const Geom& g, const void* U, void* clover);
+// A = 1 - kappa csw C, C = wt sum_i sigma_i4 F_i4 + ws sum_{i<j} sigma_ij F_ij (wt = ws = 1: the isotropic field), and
+// its inverse per parity in the internal packing, the inverse also in prec_lo (F64: not); notpd_count is raised by the
+// blocks that are not positive definite
 hipError_t launch_clover_op(hipStream_t s, const Geom& g, const LinkPlanes& U, double wt, double ws, double kappa,
                             double csw, void* const A[2], void* const inv[2], int prec_lo, void* const lo[2],
                             int* notpd_count);
