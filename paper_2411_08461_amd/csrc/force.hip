@@ -178,7 +178,8 @@ __device__ __forceinline__ Anti gamma_plane(const double2* x, const double2* y)
 
 }  // namespace
 
-// Gam[(8 plane + k) V + e] (6 planes, V sites in eo order) and XY[c V + e]: the 12 components of X, then of Y
+// Gam[(8 plane + k) V + e] (6 planes, V sites in eo order) and, unless it is null, XY[c V + e]: the 12 components of X,
+// then of Y
 __global__ __launch_bounds__(384) void k_force_gamma(int V, const double2* __restrict__ X,
                                                      const double2* __restrict__ Y, double* __restrict__ Gam,
                                                      double2* __restrict__ XY)
@@ -194,7 +195,8 @@ __global__ __launch_bounds__(384) void k_force_gamma(int V, const double2* __res
     const int lane = threadIdx.x & 63, plane = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (lane >= n) return;
     const double2 *x = sx + lane * ROW, *y = sy + lane * ROW;
-    for (int c = plane; c < 24; c += 6) XY[(long)c * V + e0 + lane] = c < 12 ? x[c] : y[c - 12];
+    if (XY)
+        for (int c = plane; c < 24; c += 6) XY[(long)c * V + e0 + lane] = c < 12 ? x[c] : y[c - 12];
     Anti G;
     switch (plane) {
     case 0: G = gamma_plane<0, 1>(x, y); break;
@@ -210,21 +212,46 @@ __global__ __launch_bounds__(384) void k_force_gamma(int V, const double2* __res
 
 namespace {
 
-// what a lane of k_force_link reads
-struct ForceFields {
+// What a lane of k_force_link reads: Gam's planes, and the links and spinors from F, a source of the numbers of one
+// link and of one component of X (0 .. 11) or Y (12 .. 23) at an eo site
+struct PlaneFields {
     LinkPlanes U;
-    const double* Gam;
     const double2* XY;
-    long V;
+    struct Link {
+        const double2 *p, *q;
+        long Vh;
+        __device__ __forceinline__ double2 operator[](int e) const { return e < 6 ? p[e * Vh] : q[(e - 6) * Vh]; }
+    };
+    __device__ __forceinline__ long Vh() const { return U.Vh; }
+    __device__ __forceinline__ Link link(int mu, Site s) const
+    {
+        return {U.top + (long)(mu * 2 + s.parity) * U.top_rec * U.Vh + s.cb,
+                U.low + (long)(mu * 2 + s.parity) * U.low_rec * U.Vh + s.cb, U.Vh};
+    }
+    __device__ __forceinline__ double2 spinor(int c, long e) const { return XY[c * 2 * U.Vh + e]; }
+};
+// the caller's records, for a call that finds no memory for copies
+struct RecordFields {
+    const double2 *U, *X, *Y;
+    long nVh;
+    __device__ __forceinline__ long Vh() const { return nVh; }
+    __device__ __forceinline__ const double2* link(int mu, Site s) const
+    {
+        return U + ((long)(mu * 2 + s.parity) * nVh + s.cb) * 9;
+    }
+    __device__ __forceinline__ double2 spinor(int c, long e) const { return c < 12 ? X[e * 12 + c] : Y[e * 12 + c - 12]; }
+};
+template <class F>
+struct ForceFields : F {
+    const double* Gam;
     // link (mu, site), adjoint if DAG
     template <bool DAG>
     __device__ __forceinline__ void link(int mu, Site s, c3& m) const
     {
-        const double2* p = U.top + (long)(mu * 2 + s.parity) * U.top_rec * U.Vh + s.cb;
-        const double2* q = U.low + (long)(mu * 2 + s.parity) * U.low_rec * U.Vh + s.cb;
+        const auto u = F::link(mu, s);
 #pragma unroll
         for (int e = 0; e < 9; e++) {
-            const double2 v = e < 6 ? p[e * U.Vh] : q[(e - 6) * U.Vh];
+            const double2 v = u[e];
             if (DAG)
                 m[e % 3][e / 3] = {v.x, -v.y};
             else
@@ -235,18 +262,18 @@ struct ForceFields {
     {
         Anti G;
 #pragma unroll
-        for (int k = 0; k < 8; k++) G.r[k] = Gam[(long)(8 * p + k) * V + s.parity * U.Vh + s.cb];
+        for (int k = 0; k < 8; k++) G.r[k] = Gam[(long)(8 * p + k) * 2 * F::Vh() + s.parity * F::Vh() + s.cb];
         return G;
     }
     // row k of the half-spinor (1 + sg gamma_mu) projects a spinor on (X: first = 0, Y: first = 12), see hop_common.h
     __device__ __forceinline__ void half(int first, Site s, int mu, int k, double sg, cx<double> (&h)[3]) const
     {
-        const long e = s.parity * U.Vh + s.cb;
+        const long e = s.parity * F::Vh() + s.cb;
         const int l = gperm(mu, k);
         const cx<double> c = gph(mu, k);
 #pragma unroll
         for (int i = 0; i < 3; i++) {
-            const double2 a = XY[(first + 3 * k + i) * V + e], b = XY[(first + 3 * l + i) * V + e];
+            const double2 a = F::spinor(first + 3 * k + i, e), b = F::spinor(first + 3 * l + i, e);
             const cx<double> w = c * cx<double>{b.x, b.y};
             h[i] = {a.x + sg * w.re, a.y + sg * w.im};
         }
@@ -254,24 +281,24 @@ struct ForceFields {
 };
 
 // acc += sgn T for the plaquette of (rho, sig) on side D = +-1 (file header)
-template <int D>
-__device__ __forceinline__ void add_plaquette(const ForceFields& f, const Geom& g, const int (&c)[4], int rho, int sig,
+template <int D, class F>
+__device__ __forceinline__ void add_plaquette(const ForceFields<F>& f, const Geom& g, const int (&c)[4], int rho, int sig,
                                               int p, double sgn, Site y, Site yr, c3& acc)
 {
     const Site yd = step(g, c, sig, D, sig, 0), yrd = step(g, c, rho, 1, sig, D);
     c3 S, t, u;
-    f.link<(D > 0)>(sig, D > 0 ? y : yd, S);  // U4: from x+d to x
+    f.template link<(D > 0)>(sig, D > 0 ? y : yd, S);  // U4: from x+d to x
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
         for (int j = 0; j < 3; j++) t[i][j] = {0.0, 0.0};
     add_gm(t, f.gam(p, yd), S);
     add_mg(t, S, f.gam(p, y));
-    f.link<true>(rho, yd, u);  // U3: from x+rho+d to x+d
+    f.template link<true>(rho, yd, u);  // U3: from x+rho+d to x+d
     left_mul(u, t);
     left_mul(u, S);
     add_gm(t, f.gam(p, yrd), S);
-    f.link<(D < 0)>(sig, D > 0 ? yr : yrd, u);  // U2: from x+rho to x+rho+d
+    f.template link<(D < 0)>(sig, D > 0 ? yr : yrd, u);  // U2: from x+rho to x+rho+d
     left_mul(u, t);
     left_mul(u, S);
     add_gm(t, f.gam(p, yr), S);
@@ -287,8 +314,9 @@ __device__ __forceinline__ void add_plaquette(const ForceFields& f, const Geom& 
 }  // namespace
 
 // H (paper gauge layout [4][2][Vh][3][3]): a block takes 64 sites of one parity, wave rho their links rho
-__global__ __launch_bounds__(256, 2) void k_force_link(Geom g, ForceFields f, double kappa, double csw,
-                                                    double2* __restrict__ H, int G)
+template <class F>
+__global__ __launch_bounds__(256, 2) void k_force_link(Geom g, ForceFields<F> f, double kappa, double csw,
+                                                       double2* __restrict__ H, int G)
 {
     __shared__ double2 stage[4][FS * 9];
     const int blk = xcd_tile(blockIdx.x, gridDim.x);
@@ -334,7 +362,7 @@ __global__ __launch_bounds__(256, 2) void k_force_link(Geom g, ForceFields f, do
     }
     // H = the traceless Hermitian part (B - B^+) / (2i) of B = U acc
     c3 u;
-    f.link<false>(rho, y, u);
+    f.template link<false>(rho, y, u);
     left_mul(u, acc);
     double2* o = stage[rho] + lane * 9;
     const double tr = (acc[0][0].im + acc[1][1].im + acc[2][2].im) / 3.0;
@@ -351,21 +379,33 @@ __global__ __launch_bounds__(256, 2) void k_force_link(Geom g, ForceFields f, do
     for (int e = lane; e < n; e += 64) h[e] = stage[rho][e];
 }
 
+template <class F>
+static hipError_t force_links(hipStream_t s, const Geom& g, const F& fields, const double* Gam, double kappa, double csw,
+                              void* H)
+{
+    const ForceFields<F> f{fields, Gam};
+    hipLaunchKernelGGL(k_force_link<F>, dim3(2 * ((g.Vh + FS - 1) / FS)), dim3(256), 0, s, g, f, kappa, csw, (double2*)H,
+                       grouped_order(g));
+    return hipGetLastError();
+}
+
 hipError_t launch_clover_force(hipStream_t s, const Geom& g, const void* U, const void* X, const void* Y,
-                               double kappa, double csw, void* scratch, void* H)
+                               double kappa, double csw, void* scratch, bool copies, void* H)
 {
     const long V = 2L * g.Vh;
     double2* planes = (double2*)scratch;  // links [4][2][9][Vh], X and Y [24][V], Gam [48][V] reals
-    double2* XY = planes + 36 * V;
-    double* Gam = (double*)(XY + 24 * V);
-    hipError_t e = launch_pack_links(s, g, U, 18, planes, nullptr, F64, 18, nullptr);
-    if (e != hipSuccess) return e;
+    double2* XY = copies ? planes + 36 * V : nullptr;
+    double* Gam = copies ? (double*)(XY + 24 * V) : (double*)scratch;
+    if (copies) {
+        const hipError_t e = launch_pack_links(s, g, U, 18, planes, nullptr, F64, 18, nullptr);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_force_gamma, dim3((unsigned)((V + FS - 1) / FS)), dim3(384), 0, s, (int)V, (const double2*)X,
                        (const double2*)Y, Gam, XY);
-    const ForceFields f{link_planes(planes, 18, nullptr, g.Vh), Gam, XY, V};
-    hipLaunchKernelGGL(k_force_link, dim3(2 * ((g.Vh + FS - 1) / FS)), dim3(256), 0, s, g, f, kappa, csw, (double2*)H,
-                       grouped_order(g));
-    return hipGetLastError();
+    if (copies)
+        return force_links(s, g, PlaneFields{link_planes(planes, 18, nullptr, g.Vh), XY}, Gam, kappa, csw, H);
+    return force_links(s, g, RecordFields{(const double2*)U, (const double2*)X, (const double2*)Y, g.Vh}, Gam, kappa, csw,
+                       H);
 }
 
 }  // namespace qcdw
@@ -385,8 +425,10 @@ extern "C" qcdw_status qcdw_clover_force(qcdw_ctx* ctx, const qcdw_lattice* lat,
     if (!std::isfinite(kappa) || !std::isfinite(csw)) return fail(ctx, QCDW_EINVAL, "kappa and csw must be finite");
     CallScratch scratch(ctx->stream);
     void* work = scratch(2UL * g.Vh * FORCE_SITE_BYTES);
+    const bool copies = work != nullptr;
+    if (!work) work = scratch(2UL * g.Vh * FORCE_GAMMA_BYTES);
     if (!work) return fail(ctx, QCDW_ENOMEM, "out of device memory for the force's workspace");
-    HIPCHK(ctx, launch_clover_force(ctx->stream, g, U, X, Y, kappa, csw, work, H));
+    HIPCHK(ctx, launch_clover_force(ctx->stream, g, U, X, Y, kappa, csw, work, copies, H));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return QCDW_OK;
 }

@@ -362,9 +362,10 @@ hipError_t launch_clover_apply(hipStream_t s, const Geom& g, const void* clover,
                                double kappa, double csw);
 hipError_t launch_clover_invert(hipStream_t s, const Geom& g, const void* clover, double kappa, double csw,
                                 void* inv, int* notpd_count);
-// clover fermion force of the bilinear 2 Re(Y^+ M X) (force.hip); scratch: FORCE_SITE_BYTES per site
-constexpr size_t FORCE_SITE_BYTES = (36 + 24) * 16 + 48 * 8;
+// clover fermion force of the bilinear 2 Re(Y^+ M X) (force.hip); scratch: FORCE_SITE_BYTES per site for plane-major
+// copies of the fields and Gam (copies), or FORCE_GAMMA_BYTES for Gam alone (slower)
+constexpr size_t FORCE_GAMMA_BYTES = 48 * 8, FORCE_SITE_BYTES = (36 + 24) * 16 + FORCE_GAMMA_BYTES;
 hipError_t launch_clover_force(hipStream_t s, const Geom& g, const void* U, const void* X, const void* Y,
-                               double kappa, double csw, void* scratch, void* H);
+                               double kappa, double csw, void* scratch, bool copies, void* H);
 
 }  // namespace qcdw

@@ -80,3 +80,16 @@ def test_clover_build():
     with context() as ctx, only(LINKS * 2 // 3):
         q.qcdw_clover_build(ctx, lat, U, got)
     assert _same(got, want)
+
+
+def test_clover_force():
+    """Copies of the links and spinors take 960 bytes a site beside Gam's 384."""
+    U, X, Y = _links(2, 0.1), _field(3, 2, V // 2, 4, 3), _field(4, 2, V // 2, 4, 3)
+    lat = q.make_lattice(L, -1)
+    want = torch.empty_like(U)
+    got = torch.full_like(want, float("nan"))
+    with context() as ctx:
+        q.qcdw_clover_force(ctx, lat, U, X, Y, 0.12, 1.1, want)
+    with context() as ctx, only(860 * V):
+        q.qcdw_clover_force(ctx, lat, U, X, Y, 0.12, 1.1, got)
+    assert _same(got, want)
