@@ -65,9 +65,9 @@ __global__ __launch_bounds__(256) void k_ms_total(const double* partials, int nb
     if (threadIdx.x == 0) *out = v;
 }
 
-// rn = r - alpha w and the partials of (rn, rn)
-__global__ __launch_bounds__(256) void k_ms_axpy_norm(const double2* __restrict__ r, double2* __restrict__ rn,
-                                                      const double2* __restrict__ w, const MsState* st, long n,
+// rn = r - alpha w (rn may be r) and the partials of (rn, rn)
+__global__ __launch_bounds__(256) void k_ms_axpy_norm(const double2* r, double2* rn, const double2* __restrict__ w,
+                                                      const MsState* st, long n,
                                                       double* partials)
 {
     const double a = st->a;
@@ -247,8 +247,10 @@ struct DrainOnExit {
 };
 
 // Device buffers of one solve (internal layout, n complex each) and the per-block dot partials (3 doubles per hop
-// block: hop partials, or one per vector block).  r[0] is the source and the true residual.
+// block: hop partials, or one per vector block).  r[0] is the source and the true residual.  group: iterations between
+// two updates of the shifted vectors, MS_CHECK with a residual kept of each, or 1 with the residual updated in place.
 struct MsBufs {
+    int group;
     void* r[MS_CHECK + 1];
     void *p, *w, *t1, *t2, *tmpo;
     double* part;
@@ -334,23 +336,25 @@ qcdw_status ms_cg(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B
     // MS_CHECK iterations; iterations enqueued after convergence change nothing (alpha = 0, no live shift).
     const size_t flags_off = offsetof(MsState, it);
     int at = 0;  // the buffer of the current residual
+    const int nr = B.group == 1 ? 1 : B.group + 1;
     for (int k = 0; k < maxiter && !h.done;) {
         const int m = std::min(MS_CHECK, maxiter - k);
         MsResiduals R{};
         for (int j = 0; j < m; j++) {
             HIPCHK(ctx, apply_normal(s, op, v, B, B.p, B.w, s0));
             hipLaunchKernelGGL(k_ms_alpha, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb_hop, ns);
-            const int next = (at + 1) % (MS_CHECK + 1);
+            const int next = (at + 1) % nr, slot = j % B.group;
             hipLaunchKernelGGL(k_ms_axpy_norm, dim3(B.nb), dim3(256), 0, s, (const double2*)B.r[at],
                                (double2*)B.r[next], (const double2*)B.w, (const MsState*)st, n, B.part);
             at = next;
-            R.r[j] = (const double2*)B.r[at];
-            hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb, ns, j);
+            R.r[slot] = (const double2*)B.r[at];
+            hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(256), 0, s, st, (const double*)B.part, B.nb, ns, slot);
             hipLaunchKernelGGL(k_ms_p, dim3(B.nb), dim3(256), 0, s, (double2*)B.p, (const double2*)B.r[at],
                                (const MsState*)st, n);
+            if (slot + 1 == B.group || j + 1 == m)
+                hipLaunchKernelGGL(k_shift_update, dim3(B.nb, ns), dim3(256), 0, s, (double2*)X, (double2*)P, R, n,
+                                   slot + 1, (const MsState*)st);
         }
-        hipLaunchKernelGGL(k_shift_update, dim3(B.nb, ns), dim3(256), 0, s, (double2*)X, (double2*)P, R, n, m,
-                           (const MsState*)st);
         HIPCHK(ctx, hipGetLastError());
         HIPCHK(ctx, hipMemcpyAsync(hd, (char*)st + flags_off, 4 * sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));
@@ -406,17 +410,23 @@ extern "C" qcdw_status qcdw_invert_multishift(qcdw_op* op, const void* b_e, void
     hipStream_t s = ctx->stream;
     const int nb = blas_blocks(n);
     // the residuals of a group, p, w, t1, t2, tmp_o, the packed b, a refinement's correction and direction, then
-    // X_i, P_i; the partials of one dot product; the solver state
-    constexpr int NR = MS_CHECK + 1, FIXED = NR + 8;
+    // X_i, P_i; the partials of one dot product; the solver state.  Where memory is too short for a group's residuals,
+    // one residual and an update of the shifted vectors per iteration.
+    int group = MS_CHECK, NR = MS_CHECK + 1;
     const int nb_hop = hop_blocks_nt(g, op->hop_nt[F64], op->hop_cg[F64]);
     PoolBuf buf, part, state;
-    HIPCHK(ctx, buf.alloc(vb * (FIXED + 2 * (size_t)n_shifts)));
+    if (buf.alloc(vb * (NR + 8 + 2 * (size_t)n_shifts)) != hipSuccess) {
+        group = NR = 1;
+        HIPCHK(ctx, buf.alloc(vb * (NR + 8 + 2 * (size_t)n_shifts)));
+    }
+    const int FIXED = NR + 8;
     HIPCHK(ctx, part.alloc((size_t)std::max(nb, 3 * nb_hop) * sizeof(double)));
     HIPCHK(ctx, state.alloc(sizeof(MsState)));
     DrainOnExit drain{s};
     char* base = (char*)buf.p;
     auto field = [&](int i) { return (void*)(base + i * vb); };
     MsBufs B{};
+    B.group = group;
     for (int i = 0; i < NR; i++) B.r[i] = field(i);
     B.p = field(NR);
     B.w = field(NR + 1);

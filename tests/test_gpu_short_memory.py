@@ -93,3 +93,30 @@ def test_clover_force():
     with context() as ctx, only(860 * V):
         q.qcdw_clover_force(ctx, lat, U, X, Y, 0.12, 1.1, got)
     assert _same(got, want)
+
+
+@pytest.mark.parametrize("maxiter", [1000, 7])
+def test_multishift(maxiter):
+    """The residuals of a group of iterations take four fields more; a run cut off in the middle of a group included."""
+    field = 6 * V * 16
+    b = _field(5, V // 2, 4, 3)
+    shifts = [0.3, 1e-2]
+    U = _links(6, 0.02)
+    want = [torch.empty_like(b) for _ in shifts]
+    got = [torch.full_like(b, float("nan")) for _ in shifts]
+
+    def solve(op, x):
+        try:
+            return q.qcdw_invert_multishift(op, b, x, shifts, maxiter=maxiter)[0]
+        except q.QcdwError as e:
+            assert maxiter == 7 and "within 7 iterations" in str(e)
+            return maxiter
+
+    with context() as ctx:
+        n = solve(q.Operator(ctx, q.make_lattice(L), U, 0.11, 1.0, "f64", 18), want)
+    with context() as ctx:
+        op = q.Operator(ctx, q.make_lattice(L), U, 0.11, 1.0, "f64", 18)
+        with only((9 + 4 + 2) * field):  # of the 17 fields with a group's residuals, 13 without
+            assert solve(op, got) == n
+    for g, w in zip(got, want):
+        assert bool(torch.isfinite(torch.view_as_real(w)).all()) and _same(g, w)
