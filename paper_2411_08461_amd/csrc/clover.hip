@@ -309,8 +309,10 @@ __device__ __forceinline__ bool invert_block(const double* p, double* o, double 
 // 1.8 kB per lane and read the paper's 144-byte records, a cache line per lane and load.
 // With 210 VGPRs two waves fit a SIMD; three (168 VGPRs) spill and are slower (252 against 179 us a call at
 // 16^3x32).  What bounds it is the links that miss the XCD's 4 MB L2 (each is read by 24 leaves): the two parities
-// of a tile next to each other and the tiles of a group swept along t (grouped_order) took 179 to 137 us.
-// Measured per call, with the plane-major copy: 16^3x32 137 us, 24^3x64 794 us (385 us and 2.92 ms before).
+// of a tile next to each other took 179 to 137 us there, and on larger lattices the tiles of a group are swept along t
+// (grouped_order: 24^3x64 827 to 768 us).
+// Measured per call, with the plane-major copy: 16^3x32 130 us, 24^3x64 768 us (385 us and 2.92 ms with a thread per
+// site).
 // OP: the operator's form; instead of C it writes, per parity and in the internal packing, A and A^-1 in FP64 and
 // A^-1 in the inner precision PL (lo nullptr: none).  C, the inverse and five repackings of whole fields as
 // kernels of their own moved 7.5 kB per site and took 570 us at 16^3x32 with the build; this form writes 1.3 kB and

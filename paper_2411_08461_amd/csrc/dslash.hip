@@ -12,10 +12,10 @@
 // projections of directions 2 gq and 2 gq + 1, so a site's four lanes share its loads and 4 V threads hide the
 // latency.  A block takes 64 sites of one parity; the blocks of the two parities of a tile run next to each
 // other, so that a link read as the forward link of one is still in the XCD's L2 as the backward link of the
-// other, and slices that are whole tiles are swept along t group by group (grouped_order).
+// other, and large slices of whole tiles are swept along t group by group (grouped_order).
 //
-// Measured, one call with its synchronisation: 24^3x64 400 us = 3.4 TB/s of the 1536 B per site (a device copy of
-// this part reaches 5.2 TB/s), 16^3x32 60 us, 4^4 20 us.  The pack-then-hop form took 1.6 ms of kernels at
+// Measured, one call with its synchronisation: 24^3x64 390 us = 3.5 TB/s of the 1536 B per site (a device copy of
+// this part reaches 5.2 TB/s), 16^3x32 59 us, 4^4 18 us.  The pack-then-hop form took 1.6 ms of kernels at
 // 24^3x64, and 50 ms with the allocation and release of its workspace.  What bounds it is the vector-memory
 // address path: the paper's records (144 B links, 192 B spinors) put the lanes of a load on as many cache lines
 // as there are sites, so the two lanes that need a link share its load (load_link_shared: 490 -> 437 us).  Four
@@ -152,8 +152,7 @@ __global__ __launch_bounds__(256) void k_dslash_paper(Geom g, const double2* __r
 hipError_t launch_dslash_paper(hipStream_t s, const Geom& g, const void* U, const void* clover, const void* psi,
                                void* out, double kappa, double csw)
 {
-    // Groups in tile order: 24^3x64 takes 27 of 108 tiles (437 -> 400 us; 12, 18, 36, 54: 421, 416, 412, 404),
-    // 16^3x32 its 16 (64 -> 60 us).
+    // Groups in tile order: 24^3x64 takes 27 of 108 tiles (groups of 12, 18, 36, 54: 421, 416, 412, 404 against 400 us)
     hipLaunchKernelGGL(k_dslash_paper<true>, dim3(2 * hop_blocks(g.Vh)), dim3(256), 0, s, g, (const double2*)U,
                        (const double*)clover, (const double2*)psi, (double2*)out, kappa, kappa * csw, 0,
                        grouped_order(g));

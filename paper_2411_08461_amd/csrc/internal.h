@@ -102,13 +102,17 @@ __host__ __device__ inline bool hop_cgroup_fits(const Geom& g, int cg)
     return cg == 0 || (cg > 0 && hop_ctiles(g) % cg == 0);
 }
 // Order of the 64-site tiles in kernels that run the two parities of a tile next to each other: 0 the eo order,
-// else the tiles of a group of G swept along t, so that what slice t shares with t - 1 and t + 1 is G tiles apart and
-// still in the XCD's L2.  Only for slices that are whole tiles (padded ones would leave lanes idle).
+// else the tiles of a group of G < tiles of a slice swept along t, so that what slice t shares with t - 1 and t + 1 is
+// G tiles apart and still in the XCD's L2.  Only for slices that are whole tiles (padded ones would leave lanes idle),
+// and of more than 32 of them: in the eo order neighbours along t are a slice apart, and up to 32 tiles of it stay in
+// L2 anyway.  In groups against the eo order: 32^4 (256 tiles, groups of 32) operator 461 and 535 us, clover build 940
+// and 1025; 24^3x64 (108, 27) 390 and 410, 768 and 827, force 1607 and 1666; 16x16x18x32 (36, 18) 62 and 64, 137 and
+// 141; 16^3x32 (32, groups of 16 to try) 57 and 59, but 153 and 130.
 inline int grouped_order(const Geom& g)
 {
-    if ((g.Lxh * g.Ly * g.Lz) % 64) return 0;
     const int nct = hop_ctiles(g);
-    for (int d = nct < 32 ? nct : 32; d >= 4; d--)
+    if (nct <= 32 || (g.Lxh * g.Ly * g.Lz) % 64) return 0;
+    for (int d = 32; d >= 4; d--)
         if (nct % d == 0) return d;
     return 0;
 }

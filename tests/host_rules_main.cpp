@@ -55,6 +55,22 @@ static int rhs64_groups()
     return 0;
 }
 
+// tile orders of the kernels on the paper's layouts: groups are proper ones of whole tiles, and every tile has one place
+static int tile_orders()
+{
+    EXPECT(grouped_order(lattice(24, 24, 24, 64)) == 27 && grouped_order(lattice(16, 16, 18, 4)) == 18);
+    EXPECT(grouped_order(lattice(16, 16, 16, 32)) == 0);  // one group would be the eo order
+    EXPECT(grouped_order(lattice(14, 14, 14, 32)) == 0);  // no whole tiles
+    for (int x = 2; x <= 32; x += 2)
+        for (int y = 2; y <= 32; y += 2)
+            for (int z = 2; z <= 32; z += 2) {
+                const Geom g = lattice(x, y, z, 4);
+                const int G = grouped_order(g), nct = hop_ctiles(g);
+                EXPECT(G == 0 || (G >= 4 && G < nct && nct % G == 0 && x / 2 * y * z == 64 * nct));
+            }
+    return 0;
+}
+
 // forms of the multi-RHS hop on lattices whose right-hand side does not fit the 32-bit byte offsets of 16-bit storage:
 // the forms with wider offsets are left, so that every call still has one
 static int mrhs_forms()
@@ -77,7 +93,7 @@ static int mrhs_forms()
 
 int main()
 {
-    if (vector_blocks() || rhs64_groups() || mrhs_forms()) return 1;
+    if (vector_blocks() || rhs64_groups() || tile_orders() || mrhs_forms()) return 1;
     std::puts("ok");
     return 0;
 }
