@@ -1170,7 +1170,7 @@ qcdw_status solve(Solver& S, const void* const* bs, void* const* xs, const qcdw_
             if (dropped)
                 HIPCHK(ctx, hipMemcpyAsync(dcoef + nprob, hc + nprob, nprob * sizeof(double), hipMemcpyHostToDevice,
                                            s));
-            HIPCHK(ctx, launch_axpy_hi(s, F32, 0.0, dcoef + nprob, W.xlo.p, W.xhi.p, n0, nprob, S.map, S.nmax));
+            HIPCHK(ctx, launch_axpy_hi(s, dcoef + nprob, W.xlo.p, W.xhi.p, n0, nprob, S.map, S.nmax));
         }
         for (int k = 0; k < nprob; k++) {
             if (done[k]) continue;

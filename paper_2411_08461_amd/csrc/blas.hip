@@ -34,21 +34,18 @@ __global__ __launch_bounds__(256) void k_norm2(const void* x, long n, double* pa
     block_sum_store<1>(v, partials + (long)blockIdx.y * gridDim.x + blockIdx.x);
 }
 
-template <class PB, class PY>
-__global__ __launch_bounds__(256) void k_xmy_norm2(const void* b, const void* y, double2* r, long n,
-                                                   double* partials, const long2* map)
+__global__ __launch_bounds__(256) void k_xmy_norm2(const double2* b, const double2* y, double2* r, long n,
+                                                   double* partials)
 {
     double v[1] = {0.0};
-    QCDW_VEC_RANGE(n, map)
-    QCDW_GRID_LOOP(e, nn)
+    QCDW_GRID_LOOP(e, n)
     {
-        const auto bb = PB::ld(b, off + e);
-        const auto yy = PY::ld(y, off + e);
-        const double re = (double)bb.re - (double)yy.re, im = (double)bb.im - (double)yy.im;
-        if (r) r[off + e] = make_double2(re, im);
+        const double2 bb = b[e], yy = y[e];
+        const double re = bb.x - yy.x, im = bb.y - yy.y;
+        if (r) r[e] = make_double2(re, im);
         v[0] += re * re + im * im;
     }
-    block_sum_store<1>(v, partials + (long)blockIdx.y * gridDim.x + blockIdx.x);
+    block_sum_store<1>(v, partials + blockIdx.x);
 }
 
 // one block per RHS: out[K x] = sum over the nb partials of RHS x
@@ -76,31 +73,27 @@ __global__ __launch_bounds__(256) void k_sum_hop_norms(const double* p0, const d
     block_sum_store<1>(v, out + blockIdx.x);
 }
 
-// out = scale_y in for RHS y (scales: per-RHS device array, or nullptr for `scale`)
+// out = scale in
 template <class PI, class PO>
-__global__ __launch_bounds__(256) void k_convert(const void* in, void* out, long n, double scale,
-                                                 const double* scales, const long2* map)
+__global__ __launch_bounds__(256) void k_convert(const void* in, void* out, long n, double scale)
 {
     using T = typename PO::real;
-    QCDW_VEC_RANGE(n, map)
-    const double sc = scales ? scales[blockIdx.y] : scale;
-    QCDW_GRID_LOOP(e, nn)
+    QCDW_GRID_LOOP(e, n)
     {
-        const auto a = PI::ld(in, off + e);
-        PO::st(out, off + e, cx<T>{(T)(sc * (double)a.re), (T)(sc * (double)a.im)});
+        const auto a = PI::ld(in, e);
+        PO::st(out, e, cx<T>{(T)(scale * (double)a.re), (T)(scale * (double)a.im)});
     }
 }
 
-// y += a_y x for RHS y (coefs: per-RHS device array, or nullptr for `a`)
-template <class PX>
-__global__ __launch_bounds__(256) void k_axpy_hi(double a, const double* coefs, const void* x, double2* y, long n,
+// y += a_y x for RHS y
+__global__ __launch_bounds__(256) void k_axpy_hi(const double* coefs, const void* x, double2* y, long n,
                                                  const long2* map)
 {
     QCDW_VEC_RANGE(n, map)
-    const double c = coefs ? coefs[blockIdx.y] : a;
+    const double c = coefs[blockIdx.y];
     QCDW_GRID_LOOP(e, nn)
     {
-        const auto xv = PX::ld(x, off + e);
+        const auto xv = P32::ld(x, off + e);
         double2 yv = y[off + e];
         yv.x += c * (double)xv.re;
         yv.y += c * (double)xv.im;
@@ -556,30 +549,12 @@ hipError_t launch_norm2(hipStream_t s, int prec, const void* x, long n, double* 
     return hipGetLastError();
 }
 
-template <class PB>
-static hipError_t xmy_b(hipStream_t s, int prec_y, const void* b, const void* y, void* r, long n, double* partials,
-                        int nrhs, const long2* map, int nb)
+hipError_t launch_xmy_norm2(hipStream_t s, const void* b, const void* y, void* r, long n, double* partials, double* out)
 {
-    const dim3 grid(nb, nrhs);
-    switch (prec_y) {
-    case F64: hipLaunchKernelGGL((k_xmy_norm2<PB, P64>), grid, dim3(256), 0, s, b, y, (double2*)r, n, partials, map); break;
-    case F32: hipLaunchKernelGGL((k_xmy_norm2<PB, P32>), grid, dim3(256), 0, s, b, y, (double2*)r, n, partials, map); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipSuccess;
-}
-
-hipError_t launch_xmy_norm2(hipStream_t s, int prec_b, int prec_y, const void* b, const void* y, void* r, long n,
-                            double* partials, double* out, int nrhs, const long2* map, long nmax)
-{
-    const int nb = blas_blocks(map ? nmax : n);
-    hipError_t e;
-    if (prec_b == F64) e = xmy_b<P64>(s, prec_y, b, y, r, n, partials, nrhs, map, nb);
-    else if (prec_b == F32) e = xmy_b<P32>(s, prec_y, b, y, r, n, partials, nrhs, map, nb);
-    else return hipErrorInvalidValue;
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sum_partials<1>, dim3(nrhs), dim3(256), 0, s, partials, nb, out);
-    return hipGetLastError();
+    const int nb = blas_blocks(n);
+    hipLaunchKernelGGL(k_xmy_norm2, dim3(nb), dim3(256), 0, s, (const double2*)b, (const double2*)y, (double2*)r, n,
+                       partials);
+    return launch_sum_partials(s, partials, nb, out);
 }
 
 hipError_t launch_sum_partials(hipStream_t s, const double* partials, int nb, double* out)
@@ -596,38 +571,33 @@ hipError_t launch_sum_hop_norms(hipStream_t s, const double* p0, const double* p
 }
 
 template <class PI>
-static hipError_t convert_in(hipStream_t s, int prec_out, const void* in, void* out, long n, double scale,
-                             const double* scales, int nrhs, const long2* map, int nb)
+static hipError_t convert_in(hipStream_t s, int prec_out, const void* in, void* out, long n, double scale)
 {
-    const dim3 grid(nb, nrhs);
+    const dim3 grid(blas_blocks(n));
     switch (prec_out) {
-    case F64: hipLaunchKernelGGL((k_convert<PI, P64>), grid, dim3(256), 0, s, in, out, n, scale, scales, map); break;
-    case F32: hipLaunchKernelGGL((k_convert<PI, P32>), grid, dim3(256), 0, s, in, out, n, scale, scales, map); break;
-    case BF16: hipLaunchKernelGGL((k_convert<PI, PBF16>), grid, dim3(256), 0, s, in, out, n, scale, scales, map); break;
-    case F16: hipLaunchKernelGGL((k_convert<PI, PF16>), grid, dim3(256), 0, s, in, out, n, scale, scales, map); break;
+    case F64: hipLaunchKernelGGL((k_convert<PI, P64>), grid, dim3(256), 0, s, in, out, n, scale); break;
+    case F32: hipLaunchKernelGGL((k_convert<PI, P32>), grid, dim3(256), 0, s, in, out, n, scale); break;
+    case BF16: hipLaunchKernelGGL((k_convert<PI, PBF16>), grid, dim3(256), 0, s, in, out, n, scale); break;
+    case F16: hipLaunchKernelGGL((k_convert<PI, PF16>), grid, dim3(256), 0, s, in, out, n, scale); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_convert(hipStream_t s, int prec_in, int prec_out, const void* in, void* out, long n, double scale,
-                          const double* scales, int nrhs, const long2* map, long nmax)
+hipError_t launch_convert(hipStream_t s, int prec_in, int prec_out, const void* in, void* out, long n, double scale)
 {
-    const int nb = blas_blocks(map ? nmax : n);
     switch (prec_in) {
-    case F64: return convert_in<P64>(s, prec_out, in, out, n, scale, scales, nrhs, map, nb);
-    case F32: return convert_in<P32>(s, prec_out, in, out, n, scale, scales, nrhs, map, nb);
-    case BF16: return convert_in<PBF16>(s, prec_out, in, out, n, scale, scales, nrhs, map, nb);
-    case F16: return convert_in<PF16>(s, prec_out, in, out, n, scale, scales, nrhs, map, nb);
+    case F64: return convert_in<P64>(s, prec_out, in, out, n, scale);
+    case F32: return convert_in<P32>(s, prec_out, in, out, n, scale);
+    case BF16: return convert_in<PBF16>(s, prec_out, in, out, n, scale);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_axpy_hi(hipStream_t s, int prec_x, double a, const double* coefs, const void* x, void* y, long n,
-                          int nrhs, const long2* map, long nmax)
+hipError_t launch_axpy_hi(hipStream_t s, const double* coefs, const void* x, void* y, long n, int nrhs,
+                          const long2* map, long nmax)
 {
-    QCDW_DISPATCH1(prec_x, k_axpy_hi, dim3(blas_blocks(map ? nmax : n), nrhs), dim3(256), 0, s, a, coefs, x,
-                   (double2*)y, n, map)
+    hipLaunchKernelGGL(k_axpy_hi, dim3(blas_blocks(map ? nmax : n), nrhs), dim3(256), 0, s, coefs, x, (double2*)y, n, map);
     return hipGetLastError();
 }
 

@@ -79,10 +79,7 @@ __device__ __forceinline__ void hop_finish(const HopArgs& a, int site, bool vali
 #pragma unroll
         for (int c = 0; c < 3; c++) wv[c] = valid ? P::ld(a.w, sp_idx(q, site, c, Vh)) : cx<T>{T(0), T(0)};
     }
-    if constexpr (EPI == EPI_NONE) {
-#pragma unroll
-        for (int c = 0; c < 3; c++) outv[c] = res[c];
-    } else if constexpr (EPI == EPI_XPAY_G5_SHIFT) {
+    if constexpr (EPI == EPI_XPAY_G5_SHIFT) {
         const T aa = q < 2 ? (T)a.a : -(T)a.a, sh = (T)a.shift;
 #pragma unroll
         for (int c = 0; c < 3; c++) outv[c] = (yv[c] - aa * res[c]) + sh * wv[c];
@@ -512,7 +509,6 @@ static hipError_t launch_hop_nt(hipStream_t s, int epi, int red, const HopArgs& 
         }                                                                                             \
         return hipGetLastError();                                                                     \
     }
-    QCDW_HOP_CASE(EPI_NONE, RED_NONE)
     QCDW_HOP_CASE(EPI_CLOV, RED_NONE)
     QCDW_HOP_CASE(EPI_CLOV_XPAY, RED_NONE)
     QCDW_HOP_CASE(EPI_CLOV_XPAY, RED_WDOT)

@@ -207,11 +207,9 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
 #pragma unroll
             for (int e = 0; e < 9; e++) ur[h][e] = L.fsg[h] * ur[h][e];
         }
-        if constexpr (EPI != EPI_NONE) {
-            T raw[27];
-            load_window<P>(a.clov, Vh, site, q, raw);
-            herm_coef(raw, q & 1, win);
-        }
+        T raw[27];
+        load_window<P>(a.clov, Vh, site, q, raw);
+        herm_coef(raw, q & 1, win);
     }
     auto clov_row = [&](const T (&m)[27], int i, T (&row)[11]) {
         // own entries (1,0), (2,0), (2,1) at 3, 5, 7; (i, j) and (j, i) are conjugates
@@ -251,29 +249,24 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
             if constexpr (HAS_Y) yv[c] = words_cx<P>(f.y.u, c);
             if constexpr (HAS_W) wv[c] = words_cx<P>(f.w.u, c);
         }
-        if constexpr (EPI == EPI_NONE) {
+        cx<T> ox[3], br[3];
 #pragma unroll
-            for (int c = 0; c < 3; c++) outv[c] = res[c];
-        } else {
-            cx<T> ox[3], br[3];
+        for (int c = 0; c < 3; c++) ox[c] = lane_cx(res[c], at_xor1);
 #pragma unroll
-            for (int c = 0; c < 3; c++) ox[c] = lane_cx(res[c], at_xor1);
+        for (int i = 0; i < 3; i++) {
+            T m[11];
+            clov_row(win, i, m);
+            const int j0 = i == 0 ? 1 : 0, j1 = i == 2 ? 1 : 2;
+            cx<T> s = {m[0] * res[i].re, m[0] * res[i].im};
+            cmac(s, cx<T>{m[1], m[2]}, res[j0]);
+            cmac(s, cx<T>{m[3], m[4]}, res[j1]);
 #pragma unroll
-            for (int i = 0; i < 3; i++) {
-                T m[11];
-                clov_row(win, i, m);
-                const int j0 = i == 0 ? 1 : 0, j1 = i == 2 ? 1 : 2;
-                cx<T> s = {m[0] * res[i].re, m[0] * res[i].im};
-                cmac(s, cx<T>{m[1], m[2]}, res[j0]);
-                cmac(s, cx<T>{m[3], m[4]}, res[j1]);
-#pragma unroll
-                for (int b = 0; b < 3; b++) cmac(s, cx<T>{m[5 + 2 * b], m[6 + 2 * b]}, ox[b]);
-                br[i] = s;
-            }
-            const T aa = (T)a.a;
-#pragma unroll
-            for (int c = 0; c < 3; c++) outv[c] = (EPI == EPI_CLOV) ? br[c] : yv[c] - aa * br[c];
+            for (int b = 0; b < 3; b++) cmac(s, cx<T>{m[5 + 2 * b], m[6 + 2 * b]}, ox[b]);
+            br[i] = s;
         }
+        const T aa = (T)a.a;
+#pragma unroll
+        for (int c = 0; c < 3; c++) outv[c] = (EPI == EPI_CLOV) ? br[c] : yv[c] - aa * br[c];
         if constexpr (MORE && OWN_AHEAD) fetch_own(f, rn);
 #pragma unroll
         for (int c = 0; c < 3; c++) outv[c] = P::rt(outv[c]);
@@ -483,8 +476,7 @@ __global__ __launch_bounds__(256) void hop_mrhs_mfma_kernel(HopArgs a, const Sca
     float win[27];
 #pragma unroll
     for (int e = 0; e < 27; e++) win[e] = 0.f;
-    if constexpr (EPI != EPI_NONE)
-        if (valid) load_window<P>(a.clov, Vh, site, q, win);
+    if (valid) load_window<P>(a.clov, Vh, site, q, win);
 
     // sign bits of e_j psi_perm(j) per direction (forward hop; the backward hop has the opposite sign):
     // x: e = -i, -i, +i, +i;  y: +1, -1, -1, +1;  z: -i, +i, +i, -i;  t: -1 for every spin
@@ -568,18 +560,13 @@ __global__ __launch_bounds__(256) void hop_mrhs_mfma_kernel(HopArgs a, const Sca
 #pragma unroll
             for (int c = 0; c < 3; c++) yv[c] = valid ? P::ld(a.y, off + sp_idx(q, site, c, Vh)) : cx<float>{0.f, 0.f};
         }
-        if constexpr (EPI == EPI_NONE) {
+        cx<float> ox[3], br[3];
 #pragma unroll
-            for (int c = 0; c < 3; c++) outv[c] = res[c];
-        } else {
-            cx<float> ox[3], br[3];
+        for (int c = 0; c < 3; c++) ox[c] = quad_dpp_cx<QUAD_XOR1>(res[c]);
+        herm_rows<true>(win, q & 1, res, ox, br);
+        const float aa = (float)a.a;
 #pragma unroll
-            for (int c = 0; c < 3; c++) ox[c] = quad_dpp_cx<QUAD_XOR1>(res[c]);
-            herm_rows<true>(win, q & 1, res, ox, br);
-            const float aa = (float)a.a;
-#pragma unroll
-            for (int c = 0; c < 3; c++) outv[c] = (EPI == EPI_CLOV) ? br[c] : yv[c] - aa * br[c];
-        }
+        for (int c = 0; c < 3; c++) outv[c] = (EPI == EPI_CLOV) ? br[c] : yv[c] - aa * br[c];
 #pragma unroll
         for (int c = 0; c < 3; c++) outv[c] = P::rt(outv[c]);
         if (valid) {

@@ -17,7 +17,6 @@ inline int real_bytes(int prec) { return prec == F64 ? 8 : prec == F32 ? 4 : 2; 
 
 // hop epilogues
 enum Epi {
-    EPI_NONE = 0,       // out = H psi
     EPI_CLOV = 1,       // out = B (H psi)
     EPI_CLOV_XPAY = 2,  // out = y - a B (H psi)
     EPI_XPAY_CLOVY = 3,  // out = B y - a (H psi)
@@ -181,13 +180,12 @@ hipError_t launch_norm2(hipStream_t s, int prec, const void* x, long n, double* 
 // one-double partials, [problem][stride][3]
 hipError_t launch_sum_hop_norms(hipStream_t s, const double* p0, const double* p1, int nb, int stride, const int* nbs,
                                 double* out, int nprob);
-hipError_t launch_xmy_norm2(hipStream_t s, int prec_b, int prec_y, const void* b, const void* y, void* r, long n,
-                            double* partials, double* out, int nrhs = 1, const long2* map = nullptr,
-                            long nmax = 0);  // r = b - y (FP64 r), out = ||r||^2
-hipError_t launch_convert(hipStream_t s, int prec_in, int prec_out, const void* in, void* out, long n, double scale,
-                          const double* scales = nullptr, int nrhs = 1, const long2* map = nullptr, long nmax = 0);
-hipError_t launch_axpy_hi(hipStream_t s, int prec_x, double a, const double* coefs, const void* x, void* y, long n,
-                          int nrhs = 1, const long2* map = nullptr, long nmax = 0);  // y(f64) += a x
+hipError_t launch_xmy_norm2(hipStream_t s, const void* b, const void* y, void* r, long n, double* partials,
+                            double* out);  // r = b - y (FP64; r may be null), out = ||r||^2
+hipError_t launch_convert(hipStream_t s, int prec_in, int prec_out, const void* in, void* out, long n, double scale);
+// y_k += a_k x_k (y FP64, x FP32) for the problems of a solve; coefs: a per problem on the device
+hipError_t launch_axpy_hi(hipStream_t s, const double* coefs, const void* x, void* y, long n, int nrhs,
+                          const long2* map, long nmax);
 hipError_t launch_clov_apply_internal(hipStream_t s, int prec, const Geom& g, const void* clov, const void* in,
                                       void* out);
 

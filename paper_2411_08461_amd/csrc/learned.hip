@@ -442,7 +442,7 @@ extern "C" qcdw_status qcdw_make_training_pairs(qcdw_op* op, const void* b, int 
         if (sk == QCDW_OK) break;                                    // converged: no error left to learn
         if (sk != QCDW_ENOCONV) return sk;
         HIPCHK(ctx, launch_pack_spinor(s, F64, g, xk.p, 0, c.p, 1.0));
-        HIPCHK(ctx, launch_xmy_norm2(s, F64, F64, a.p, c.p, e.p, n, (double*)part.p, (double*)res.p));
+        HIPCHK(ctx, launch_xmy_norm2(s, a.p, c.p, e.p, n, (double*)part.p, (double*)res.p));
         HIPCHK(ctx, matpc(s, op, view(op, F64), e.p, r.p, tmpo.p, RED_NONE, nullptr, nullptr, nullptr));
         HIPCHK(ctx, launch_norm2(s, F64, r.p, n, (double*)part.p, (double*)res.p + 1));
         double rn2;
@@ -532,7 +532,7 @@ qcdw_status qcdw_host::fgmres_run(qcdw_op* op, const Precond* precond, const voi
     // r = bhat - M_hat xe, returns ||r||
     auto schur_residual = [&](double& rn) -> qcdw_status {
         HIPCHK(ctx, matpc(s, op, v64, xe.p, tmp.p, tmpo.p, RED_NONE, nullptr, nullptr, nullptr));
-        HIPCHK(ctx, launch_xmy_norm2(s, F64, F64, bhat.p, tmp.p, r.p, n, dpart, dd));
+        HIPCHK(ctx, launch_xmy_norm2(s, bhat.p, tmp.p, r.p, n, dpart, dd));
         double v;
         CHK(rd(1, &v));
         rn = std::sqrt(v);
@@ -558,7 +558,7 @@ qcdw_status qcdw_host::fgmres_run(qcdw_op* op, const Precond* precond, const voi
             mm.y = p == 0 ? xe.p : xo.p;
             mm.a = op->kappa;
             HIPCHK(ctx, launch_hop(s, F64, v64.recon, EPI_XPAY_CLOVY, RED_NONE, mm));
-            HIPCHK(ctx, launch_xmy_norm2(s, F64, F64, p == 0 ? be.p : bo.p, tmp.p, nullptr, n, dpart, dd));
+            HIPCHK(ctx, launch_xmy_norm2(s, p == 0 ? be.p : bo.p, tmp.p, nullptr, n, dpart, dd));
             double v;
             CHK(rd(1, &v));
             r2 += v;

@@ -306,9 +306,9 @@ qcdw_status ms_cg(qcdw_ctx* ctx, qcdw_op* op, const PrecView& v, const MsBufs& B
     const size_t vb = (size_t)n * 16;
     double s0 = shifts[0];
     for (int i = 1; i < ns; i++) s0 = std::min(s0, shifts[i]);
-    HIPCHK(ctx, launch_convert(s, F64, F64, B.r[0], B.p, n, 1.0, nullptr));
+    HIPCHK(ctx, launch_convert(s, F64, F64, B.r[0], B.p, n, 1.0));
     for (int i = 0; i < ns; i++) {
-        HIPCHK(ctx, launch_convert(s, F64, F64, B.r[0], (char*)P + i * vb, n, 1.0, nullptr));
+        HIPCHK(ctx, launch_convert(s, F64, F64, B.r[0], (char*)P + i * vb, n, 1.0));
         HIPCHK(ctx, hipMemsetAsync((char*)X + i * vb, 0, vb, s));
     }
     double* hd = ctx->host_d;  // pinned
@@ -442,7 +442,7 @@ extern "C" qcdw_status qcdw_invert_multishift(qcdw_op* op, const void* b_e, void
     auto P = [&](int i) { return field(FIXED + n_shifts + i); };
 
     HIPCHK(ctx, launch_pack_spinor(s, F64, g, b_e, 0, bint, 1.0));
-    HIPCHK(ctx, launch_convert(s, F64, F64, bint, B.r[0], n, 1.0, nullptr));
+    HIPCHK(ctx, launch_convert(s, F64, F64, bint, B.r[0], n, 1.0));
     // The recurrence runs to half the tolerance, so that the true residuals (which drift from the
     // recurrence's by rounding) normally pass without refinement.
     MsState h;

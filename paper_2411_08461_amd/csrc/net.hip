@@ -572,14 +572,6 @@ __global__ __launch_bounds__(256) void k_train_output(TrainArgs n, const double2
     block_sum_store<1>(v, n.partials + blockIdx.x);
 }
 
-// out = sum of n partials, in a fixed order; one block
-__global__ __launch_bounds__(256) void k_sum_partials(const double* partials, int n, double* out)
-{
-    double v[1] = {0.0};
-    for (int b = threadIdx.x; b < n; b += 256) v[0] += partials[b];
-    block_sum_store<1>(v, out);
-}
-
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
 
 // Weight-gradient products.  Accumulator tile of 16 rows x 16 columns: v_mfma_f64_16x16x4 takes A[row][k] from lane
@@ -882,7 +874,7 @@ static hipError_t train_pair(hipStream_t s, const Geom& g, const TrainFields& f,
     n.W = (const float2*)f.W2;
     n.partials = loss;
     hipLaunchKernelGGL(k_train_output<H>, dim3(tiles), dim3(256), 0, s, n, (const double2*)e, en, f.gz);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, loss, tiles, dn);
+    if (const hipError_t e1 = launch_sum_partials(s, loss, tiles, dn); e1 != hipSuccess) return e1;
     // gh: the adjoint of layer 2 is a layer from even sites like layer 1
     TrainArgs adj{g, f.gauge32, f.gz, nullptr, f.gh, nullptr, (const float2*)f.Wt, nullptr, tiles, 0};
     hipLaunchKernelGGL(k_train_hidden<H>, dim3(2 * tiles), dim3(256), 0, s, adj);
