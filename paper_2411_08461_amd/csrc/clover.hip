@@ -110,29 +110,6 @@ __device__ __forceinline__ void add_antiherm_dn(double (&f)[9], const M3& p, con
     }
 }
 
-// site index (parity, checkerboard index) of coordinates
-struct Site {
-    int parity, cb;
-};
-
-__device__ __forceinline__ Site site_of(const Geom& g, const int (&c)[4])
-{
-    return {(c[0] + c[1] + c[2] + c[3]) & 1, ((c[3] * g.Lz + c[2]) * g.Ly + c[1]) * g.Lxh + (c[0] >> 1)};
-}
-
-// c + dm mu + dn nu, steps of at most one, periodic (mu, nu uniform over the wave)
-__device__ __forceinline__ Site shifted(const Geom& g, const int (&c)[4], int mu, int dm, int nu, int dn)
-{
-    const int L[4] = {g.Lx, g.Ly, g.Lz, g.Lt};
-    int o[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int v = c[i] + (i == mu ? dm : 0) + (i == nu ? dn : 0);
-        o[i] = v < 0 ? L[i] - 1 : (v == L[i] ? 0 : v);
-    }
-    return site_of(g, o);
-}
-
 __device__ __forceinline__ M3 ld_link(const LinkPlanes& U, int mu, Site s)
 {
     M3 r;
@@ -172,33 +149,33 @@ template <class Links>
 __device__ __forceinline__ void field_strength(const Links& U, const Geom& g, const int (&c)[4], int mu, int nu,
                                                double w, double (&out)[8])
 {
-    const Site x = site_of(g, c);
+    const Site x = site_step(g, c, mu, 0, nu, 0);
     double f[9];  // Q - Q^+: imaginary diagonal / 2, then the entries above it
 #pragma unroll
     for (int i = 0; i < 9; i++) f[i] = 0.0;
     // each leaf as a product of two half-leaves, the first two links in one order and the last two in the other:
     // two matrices are live, and only the anti-Hermitian part of their product is formed
     {  // upper-right: U_mu(x) U_nu(x+mu) [U_nu(x) U_mu(x+nu)]^+
-        const M3 p = mul(ld_link(U, mu, x), ld_link(U, nu, shifted(g, c, mu, 1, nu, 0)));
-        const M3 r = mul(ld_link(U, nu, x), ld_link(U, mu, shifted(g, c, mu, 0, nu, 1)));
+        const M3 p = mul(ld_link(U, mu, x), ld_link(U, nu, site_step(g, c, mu, 1, nu, 0)));
+        const M3 r = mul(ld_link(U, nu, x), ld_link(U, mu, site_step(g, c, mu, 0, nu, 1)));
         add_antiherm_nd(f, p, r);
     }
     {  // upper-left: U_nu(x) U_mu(x-mu+nu)^+ [U_mu(x-mu)^+ U_nu(x-mu)]^+
-        const Site xm = shifted(g, c, mu, -1, nu, 0);
-        const M3 p = mul_nd(ld_link(U, nu, x), ld_link(U, mu, shifted(g, c, mu, -1, nu, 1)));
+        const Site xm = site_step(g, c, mu, -1, nu, 0);
+        const M3 p = mul_nd(ld_link(U, nu, x), ld_link(U, mu, site_step(g, c, mu, -1, nu, 1)));
         const M3 r = mul_dn(ld_link(U, mu, xm), ld_link(U, nu, xm));
         add_antiherm_nd(f, p, r);
     }
     {  // lower-left: [U_nu(x-mu-nu) U_mu(x-mu)]^+ U_mu(x-mu-nu) U_nu(x-nu)
-        const Site xmn = shifted(g, c, mu, -1, nu, -1);
-        const M3 p = mul(ld_link(U, nu, xmn), ld_link(U, mu, shifted(g, c, mu, -1, nu, 0)));
-        const M3 r = mul(ld_link(U, mu, xmn), ld_link(U, nu, shifted(g, c, mu, 0, nu, -1)));
+        const Site xmn = site_step(g, c, mu, -1, nu, -1);
+        const M3 p = mul(ld_link(U, nu, xmn), ld_link(U, mu, site_step(g, c, mu, -1, nu, 0)));
+        const M3 r = mul(ld_link(U, mu, xmn), ld_link(U, nu, site_step(g, c, mu, 0, nu, -1)));
         add_antiherm_dn(f, p, r);
     }
     {  // lower-right: U_nu(x-nu)^+ U_mu(x-nu) [U_mu(x) U_nu(x+mu-nu)^+]^+
-        const Site xn = shifted(g, c, mu, 0, nu, -1);
+        const Site xn = site_step(g, c, mu, 0, nu, -1);
         const M3 p = mul_dn(ld_link(U, nu, xn), ld_link(U, mu, xn));
-        const M3 r = mul_nd(ld_link(U, mu, x), ld_link(U, nu, shifted(g, c, mu, 1, nu, -1)));
+        const M3 r = mul_nd(ld_link(U, mu, x), ld_link(U, nu, site_step(g, c, mu, 1, nu, -1)));
         add_antiherm_nd(f, p, r);
     }
     const double tr = (1.0 / 3.0) * (f[0] + f[1] + f[2]);

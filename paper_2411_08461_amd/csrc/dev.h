@@ -240,6 +240,24 @@ __device__ __forceinline__ void site_coords(const Geom& g, int i, int p, int& x,
     x = 2 * xh + ((p + y + z + t) & 1);
 }
 
+// a site by its parity and checkerboard index
+struct Site {
+    int parity, cb;
+};
+// the site reached from coordinates c by a step s1 along m1 and s2 along m2 (each -1, 0 or 1; periodic; the directions
+// uniform over the wave)
+__device__ __forceinline__ Site site_step(const Geom& g, const int (&c)[4], int m1, int s1, int m2, int s2)
+{
+    const int L[4] = {g.Lx, g.Ly, g.Lz, g.Lt};
+    int o[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int v = c[i] + (i == m1 ? s1 : 0) + (i == m2 ? s2 : 0);
+        o[i] = v < 0 ? L[i] - 1 : (v == L[i] ? 0 : v);
+    }
+    return {(o[0] + o[1] + o[2] + o[3]) & 1, ((o[3] * g.Lz + o[2]) * g.Ly + o[1]) * g.Lxh + (o[0] >> 1)};
+}
+
 // ---------------------------------------------------------------------------
 // block mapping: consecutive logical tiles on one XCD (workgroups are
 // dispatched round-robin over the 8 XCDs, each with its own L2)

@@ -38,23 +38,6 @@ namespace {
 
 using c3 = cx<double>[3][3];
 
-// the site reached from c by a step s1 along m1 and s2 along m2 (each -1, 0 or 1; the directions uniform over the
-// wave): its parity and checkerboard index
-struct Site {
-    int parity, cb;
-};
-__device__ __forceinline__ Site step(const Geom& g, const int (&c)[4], int m1, int s1, int m2, int s2)
-{
-    const int L[4] = {g.Lx, g.Ly, g.Lz, g.Lt};
-    int o[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const int v = c[i] + (i == m1 ? s1 : 0) + (i == m2 ? s2 : 0);
-        o[i] = v < 0 ? L[i] - 1 : (v == L[i] ? 0 : v);
-    }
-    return {(o[0] + o[1] + o[2] + o[3]) & 1, ((o[3] * g.Lz + o[2]) * g.Ly + o[1]) * g.Lxh + (o[0] >> 1)};
-}
-
 // DeGrand-Rossi gamma_mu: one nonzero per row, gamma_mu[s][perm] = ph
 __device__ __forceinline__ constexpr int gperm(int mu, int s) { return mu < 2 ? 3 - s : (s + 2) & 3; }
 __device__ __forceinline__ cx<double> gph(int mu, int s)
@@ -285,7 +268,7 @@ template <int D, class F>
 __device__ __forceinline__ void add_plaquette(const ForceFields<F>& f, const Geom& g, const int (&c)[4], int rho, int sig,
                                               int p, double sgn, Site y, Site yr, c3& acc)
 {
-    const Site yd = step(g, c, sig, D, sig, 0), yrd = step(g, c, rho, 1, sig, D);
+    const Site yd = site_step(g, c, sig, D, sig, 0), yrd = site_step(g, c, rho, 1, sig, D);
     c3 S, t, u;
     f.template link<(D > 0)>(sig, D > 0 ? y : yd, S);  // U4: from x+d to x
 #pragma unroll
@@ -325,7 +308,7 @@ __global__ __launch_bounds__(256, 2) void k_force_link(Geom g, ForceFields<F> f,
     const int site = tile * FS + lane;
     int c[4];
     site_coords(g, site < g.Vh ? site : g.Vh - 1, parity, c[0], c[1], c[2], c[3]);
-    const Site y = step(g, c, 0, 0, 0, 0), yr = step(g, c, rho, 1, rho, 0);
+    const Site y = site_step(g, c, 0, 0, 0, 0), yr = site_step(g, c, rho, 1, rho, 0);
     c3 acc;
 #pragma unroll
     for (int i = 0; i < 3; i++)

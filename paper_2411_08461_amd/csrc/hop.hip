@@ -236,10 +236,9 @@ __global__ __launch_bounds__(256) QCDW_HOP_ATTR void hop_kernel(HopArgs a)
     double* part = a.partials + 3 * (long)tile;
     if (a.cgroup > 0) {
         const Geom& g = a.g;
-        const int G = a.cgroup, St = g.Lxh * g.Ly * g.Lz;
-        const int grp = tile / (G * g.Lt), r = tile - grp * G * g.Lt;
-        const int t = r / G, ct = grp * G + (r - t * G);
-        const int c = ct * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+        const int St = g.Lxh * g.Ly * g.Lz;
+        int t;
+        const int ct = group_ctile(g, tile, a.cgroup, t), c = ct * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
         if constexpr (STG) {
             using T = typename P::real;
             constexpr int RUN = 4 * HOP_SITES_PER_BLOCK * 3;  // complex per staged slice run
@@ -383,9 +382,9 @@ __global__ __launch_bounds__(256, 2) void hop_rhs64_kernel(HopArgs a, const Scal
     int site = tile * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
     bool valid = site < g.Vh;
     if (a.cgroup > 0) {  // slice-group order, as in the single-RHS hop_kernel
-        const int G = a.cgroup, St = g.Lxh * g.Ly * g.Lz;
-        const int grp = tile / (G * g.Lt), rr = tile - grp * G * g.Lt;
-        const int t = rr / G, c = (grp * G + (rr - t * G)) * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+        const int St = g.Lxh * g.Ly * g.Lz;
+        int t;
+        const int c = group_ctile(g, tile, a.cgroup, t) * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
         site = t * St + c;
         valid = c < St;
     }

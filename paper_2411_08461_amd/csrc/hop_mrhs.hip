@@ -107,10 +107,9 @@ __global__ __launch_bounds__(256, P::cbytes == 16 ? 1 : 2) void hop_mrhs_kernel(
     int site;
     bool valid;
     if (a.cgroup > 0) {  // slice-group order, as in the single-RHS hop_kernel
-        const int G = a.cgroup, St = g.Lxh * g.Ly * g.Lz;
-        const int grp = tile / (G * g.Lt), rr = tile - grp * G * g.Lt;
-        const int t = rr / G, ct = grp * G + (rr - t * G);
-        const int c = ct * HOP_SITES_PER_BLOCK + ts;
+        const int St = g.Lxh * g.Ly * g.Lz;
+        int t;
+        const int c = group_ctile(g, tile, a.cgroup, t) * HOP_SITES_PER_BLOCK + ts;
         site = t * St + c;
         valid = c < St;
     } else {
@@ -417,10 +416,9 @@ __global__ __launch_bounds__(256) void hop_mrhs_mfma_kernel(HopArgs a, const Sca
     int site;
     bool valid;
     if (a.cgroup > 0) {
-        const int G = a.cgroup, St = g.Lxh * g.Ly * g.Lz;
-        const int grp = tile / (G * g.Lt), rr = tile - grp * G * g.Lt;
-        const int t = rr / G, ct = grp * G + (rr - t * G);
-        const int c = ct * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
+        const int St = g.Lxh * g.Ly * g.Lz;
+        int t;
+        const int c = group_ctile(g, tile, a.cgroup, t) * HOP_SITES_PER_BLOCK + (threadIdx.x >> 2);
         site = t * St + c;
         valid = c < St;
     } else {

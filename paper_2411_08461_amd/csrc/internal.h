@@ -115,12 +115,20 @@ inline int grouped_order(const Geom& g)
         if (nct % d == 0) return d;
     return 0;
 }
+// place k of a launch whose c-tiles are swept along t in groups of G: slice t and c-tile
+__device__ __forceinline__ int group_ctile(const Geom& g, int k, int G, int& t)
+{
+    const int grp = k / (G * g.Lt), r = k - grp * G * g.Lt;
+    t = r / G;
+    return grp * G + (r - t * G);
+}
 // the eo tile of place k in that order
 __device__ __forceinline__ int grouped_tile(const Geom& g, int k, int G)
 {
     if (G == 0) return k;
-    const int grp = k / (G * g.Lt), r = k - grp * G * g.Lt, t = r / G;
-    return t * hop_ctiles(g) + grp * G + (r - t * G);
+    int t;
+    const int ct = group_ctile(g, k, G, t);
+    return t * hop_ctiles(g) + ct;
 }
 // blocks (and reduction partials) of one single-RHS hop launch
 __host__ __device__ inline int hop_blocks_nt(const Geom& g, int nt, int cg)
