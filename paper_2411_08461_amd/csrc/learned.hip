@@ -492,8 +492,9 @@ qcdw_status qcdw_host::fgmres_run(qcdw_op* op, const Precond* precond, const voi
     hipStream_t s = ctx->stream;
     const PrecView v64 = view(op, F64);
 
-    // from the block cache (sixteen allocations and their releases each solve), except bases that are too
-    // large to be held after the solve; the stream is drained before the blocks go back
+    // from the block cache (sixteen allocations and their releases each solve), except bases of more than 4 GiB: they
+    // are not to be held idle after the solve, and cost it 1.1 ms for their allocation (two bases of 5.5 GB at 24^3x64,
+    // restart 64; 0.6 ms for two of 1.4 GB, 71 ms for two of 13 GB).  The stream is drained before the blocks go back
     PoolBuf be, bo, yo, ye, bhat, xe, xo, r, w, tmp, tmpo, part, coef, dres;
     DevBuf V, Z;
     V.pooled = Z.pooled = vb * (m + 1) <= (size_t)4 << 30;

@@ -906,9 +906,15 @@ qcdw_status mg_build_coarse(qcdw_mg* mg, qcdw_op* op)
     return QCDW_OK;
 }
 
-// Coarse sites up to which every block sums the partials of the launch before itself (each reads Vc x 8 doubles)
+// Coarse sites up to which every block sums the partials of the launch before itself (each reads Vc x 8 doubles: 64 MB
+// a launch at the limit, from L2); beyond, a launch of one block does it.  An outer step with 48 coarse iterations, by
+// every block and by a launch: 512 sites (16^3x32, 12 vectors) 656 and 855 us, 1024 771 and 984 (4 vectors 677 and 898,
+// 24 vectors 1182 and 1391); the two meet above 2048 (1222 and 1294, 3456 sites of 24^3x64 3311 and 2996), where a
+// launch's reads outgrow the L2s.
 constexpr int MG_FUSE = 1024;
-// iterations up to which the coarse solve is captured as one graph
+// Iterations up to which the coarse solve is captured as one graph: a bound on the graph that a set-up holds (two
+// nodes an iteration, four beyond MG_FUSE), no matter of speed.  An outer step at 16^3x32 (512 coarse sites) from the
+// graph and launch by launch: 24 iterations 612 and 599 us, 64 765 and 781, 128 997 and 1283, 256 1506 and 2209.
 constexpr int MG_GRAPH_ITERS = 128;
 
 // e ~ D_c^-1 rc / ||rc||: normalisation, coarse_iters iterations with early exit, as launches on stream s
