@@ -225,8 +225,8 @@ qcdw_status qcdw_dslash(qcdw_ctx *ctx, const qcdw_lattice *lat, const void *U, c
    clover field when clover is NULL, copies of inputs that share memory with out) taken from a fixed
    device array of QCDW_NOALLOC_MAX_BYTES that the library holds on each device it runs on until the
    process ends.  No device memory is allocated or freed.  Arguments, layouts and the result are
-   those of qcdw_dslash (the same kernel runs).  Lattices are admitted up to about 2.6 kB per site
-   (3.2 kB when clover is NULL) of the array: larger ones give QCDW_EINVAL with the size in the
+   those of qcdw_dslash (the same kernel runs).  Lattices are admitted up to about 2.0 kB per site
+   (2.6 kB when clover is NULL) of the array: larger ones give QCDW_EINVAL with the size in the
    message.  Calls on one device share the array, which keeps the last call's contents: calls
    that overlap on one device (several streams or threads) race, so the caller serialises them. */
 #define QCDW_NOALLOC_MAX_BYTES 67108864
@@ -234,7 +234,7 @@ qcdw_status qcdw_dslash_noalloc(qcdw_ctx *ctx, const qcdw_lattice *lat, const vo
                                 const void *psi, void *out, double kappa, double csw);
 
 /* Operator object (the getDirac + loadGauge step of Sec. III.B): packs U into
-   the internal site-major layout (reconstruct-12 when recon == 12, else 18),
+   the internal layouts (reconstruct-12 when recon == 12, else 18),
    builds the clover field, inverts A on both parities, and keeps FP64 copies
    plus copies in `inner` storage precision.  U is not referenced afterwards. */
 qcdw_status qcdw_op_create(qcdw_ctx *ctx, const qcdw_lattice *lat, const void *U, double kappa, double csw,
